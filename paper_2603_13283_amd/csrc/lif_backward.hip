@@ -21,393 +21,790 @@
 // of the events consumed before the spike (not a comparison of float32
 // times, which can round a spike onto the time of the event before it; the
 // offset t_s - t_k is then taken as 0).
-// P^m, P^s obey a reverse recurrence with the same per-event decays as the
-// forward scan, P_{k-1} = M P_k + (the spikes with out_k = k),
-// which k_event_adjoint walks backwards per (sample, segment, chunk of 64
-// neurons that fire), taking only neurons with spikes (the others have no
-// gradient): the firing neurons of each sample are listed in neuron order
-// first (k_bwd_live).  Each segment starts from the closed-form sums over
-// the (few) spikes that follow it, so segments are independent.  The walk
-// is staged like the forward walks (decays and times in LDS, weights of the
-// next group of events in flight).
+// With the suffix sums Q_s = sum_{s' >= s} mu_s' e^{-(t_s' - t_s)/t.} over a
+// neuron's spikes, P_k = Q_s e^{-(t_s - t_k)/t.} for the first spike s after
+// event k: between two spikes of the neuron P is a per-neuron constant times a
+// per-event exponential that all neurons share.  With times referred to a
+// multiple ref of kRefTs tau_s (so that no exponential leaves the float64 range)
+//   P_k = R_s H_k,  R_s = Q_s e^{-(t_s - ref)/t.},  H_k = e^{(t_k - ref)/t.},
+// R tabulated per spike and H per event before the walk: passing a spike is a
+// switch to the next R, and the walk evaluates no exponential.
+//
+// dL/dW sums one term per (event, neuron) into element (source, neuron).  As
+// global atomics these adds bound the walk (184 G adds/s on this card wherever
+// the rows lie, against 3500 G adds/s into LDS), so a workgroup keeps
+// the dL/dW block of 64 neurons and a range of at most kAdjRows channels in
+// LDS and walks, for those neurons, only the events of that range: the events
+// of each (sample, channel range) are listed in time order first
+// (k_bwd_setup counts, k_bwd_plan scans, k_bwd_scatter places them), every
+// (event, neuron) pair is still walked once.  One range needs no list.
 //
 // Both gradients are bitwise reproducible.  dL/dW sums contributions from
-// every sample and segment that see the same (channel, neuron): they are
+// every sample that sees the same (channel, neuron): they are
 // added as 64-bit fixed-point integers (integer addition is exact and order
 // free) with a power-of-two scale chosen per call so that no sum can
-// overflow (k_bwd_scale); dL/dt of an event sums over the neuron tiles,
-// chunks, whose partial sums are stored per chunk and added in chunk order.
+// overflow (k_bwd_plan); dL/dt of an event sums over the neuron tiles,
+// whose partial sums are stored per tile and added in tile order.
 #include <type_traits>
 
 #include "lif_common.hpp"
 #include "lif_host.hpp"
+#include "lif_scan.hpp"
 #include "lif_walk.hpp"
 
 namespace lif {
 
-struct BwdLayout {
-    int S, E_pad, tiles;
-    size_t dec, mu, klast, musum, scale, live, nlive, gw, gt, total;
+constexpr int kAdjThreads = 768;                 // threads of an adjoint workgroup
+constexpr int kAdjWaves = kAdjThreads / kWave;
+constexpr int kAdjRows = 318;                    // channels of a dL/dW block: 159 KB of LDS
+constexpr int kAdjMaxRanges = 1024;              // channel ranges that the event lists take
+constexpr int kListChunk = 1024;                 // events one wave counts or places
+constexpr int kCus = 256;
+constexpr int kPlanThreads = 1024;
+
+// How a call is split; a function of the sizes alone.
+struct BwdPlan {
+    int tiles;        // 64-neuron tiles
+    int nr, rows;     // channel ranges of `rows` channels
+    bool lds;         // dL/dW blocks in LDS (else global atomics)
+    int nch;          // list chunks per sample
+    int Q;            // parts of a (sample, range) list
+    int S;            // workgroups per (tile, range), which add to the same block
 };
+
+static BwdPlan bwd_plan(int B, int E_max, int C_in, int N)
+{
+    BwdPlan P{};
+    P.tiles = (N + kWave - 1) / kWave;
+    P.nr = (C_in + kAdjRows - 1) / kAdjRows;
+    // past kAdjMaxRanges ranges (about 290 000 channels) a range's list is a
+    // small part of the stream and the wave counters of the list build no
+    // longer fit: one range, dL/dW by global atomics
+    P.lds = P.nr <= kAdjMaxRanges;
+    if (!P.lds) P.nr = 1;
+    P.rows = (C_in + P.nr - 1) / P.nr;
+    P.nch = (E_max + kListChunk - 1) / kListChunk;
+    // parts: enough (sample, part) units for four per wave of a full chip,
+    // none longer than 1024 events and none much shorter than 128 (a unit
+    // starts with a search in every neuron's spikes)
+    const long long len = E_max / P.nr > 0 ? E_max / P.nr : 1;
+    const long long groups = (long long)P.tiles * P.nr;
+    const long long have = groups * (B > 0 ? B : 1);
+    long long Q = (4ll * kCus * kAdjWaves + have - 1) / have;
+    const long long three = (3ll * kAdjWaves + (B > 0 ? B : 1) - 1) / (B > 0 ? B : 1);   // units for each wave of a workgroup
+    Q = Q > three ? Q : three;
+    Q = Q > (len + 1023) / 1024 ? Q : (len + 1023) / 1024;
+    Q = Q < (len + 127) / 128 ? Q : (len + 127) / 128;
+    P.Q = (int)(Q < 1 ? 1 : Q);
+    // workgroups per block: the split that leaves the fewest compute units
+    // idle in the last round (one workgroup per compute unit at a time),
+    // a little against splitting, since split blocks are added by atomics
+    const long long units = (long long)(B > 0 ? B : 1) * P.Q;
+    const long long most = (units + kAdjWaves - 1) / kAdjWaves;
+    double best = 0.0;
+    P.S = 1;
+    for (int S = 1; S <= 64 && S <= most; ++S) {
+        const long long rounds = (groups * S + kCus - 1) / kCus;
+        const double cost = (double)rounds * (1.0 / S + 0.01);
+        if (S == 1 || cost < best) {
+            best = cost;
+            P.S = S;
+        }
+    }
+    return P;
+}
+
+// Reference of a time: the multiple of len = kRefTs tau_s at or before it, as an
+// index.  (Past 2e9 of them float32 times that differ are thousands of tau_s
+// apart; the index saturates there and the offset is bounded.)
+constexpr double kRefTs = 100.0;
+
+__device__ __forceinline__ int ref_index(double t, double inv_len) { return (int)fmin(fmax(t * inv_len, 0.0), 2.0e9); }
+
+__device__ __forceinline__ double ref_offset(double t, int idx, double len)
+{
+    return fmin(fma(-(double)idx, len, t), 4.0 * len);
+}
+
+// f^d (d >= 0) or g^-d, g = 1 / f.
+__device__ __forceinline__ double ref_pow(double f, double g, int d)
+{
+    double x = d < 0 ? g : f, r = 1.0;
+    for (unsigned e = (unsigned)(d < 0 ? -d : d); e; e >>= 1) {
+        if (e & 1u) r *= x;
+        x *= x;
+    }
+    return r;
+}
+
+// An event of a list: its time, source, place in the sample, reference, and
+// H = (e^{(t - ref)/tm}, e^{(t - ref)/ts}).
+struct alignas(32) ListEvent {
+    double Hm, Hs;
+    float t;
+    int src, k, ref;
+};
+
+__device__ __forceinline__ ListEvent list_event(const Model& m, float t, int src, int k)
+{
+    const double len = kRefTs * m.ts;
+    ListEvent e;
+    e.t = t;
+    e.src = src;
+    e.k = k;
+    e.ref = ref_index((double)t, 1.0 / len);
+    const double dr = ref_offset((double)t, e.ref, len);
+    e.Hm = exp(dr * m.inv_tm);
+    e.Hs = exp(dr * m.inv_ts);
+    return e;
+}
+
+struct BwdLayout {
+    BwdPlan P;
+    size_t q, ns, part, scale, cnt, start, list, gw, gt, total;
+};
+
+constexpr int kSetupBlocks = 2048;
 
 static BwdLayout bwd_layout(int B, int E_max, int C_in, int N, int s_max)
 {
     BwdLayout L{};
-    L.S = (E_max + kSeg - 1) / kSeg;
-    L.E_pad = L.S * kSeg;
+    L.P = bwd_plan(B, E_max, C_in, N);
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off += (bytes + 255) & ~(size_t)255; return o; };
-    L.tiles = (N + kWave - 1) / kWave;
-    L.dec = take((size_t)B * L.E_pad * sizeof(Decay));
-    L.mu = take((size_t)B * N * s_max * sizeof(double));
-    L.klast = take((size_t)B * N * sizeof(int32_t));
-    L.musum = take((size_t)B * N * sizeof(double));
-    L.scale = take(sizeof(double));
-    L.live = take((size_t)B * N * sizeof(int32_t));
-    L.nlive = take((size_t)B * sizeof(int32_t));
-    L.gw = take((size_t)C_in * N * sizeof(long long));
-    L.gt = take((size_t)L.tiles * B * E_max * sizeof(double));
+    L.q = take((size_t)B * N * s_max * sizeof(double2));
+    L.ns = take((size_t)B * N * sizeof(int32_t));
+    L.part = take(kSetupBlocks * sizeof(double));
+    L.scale = take(2 * sizeof(double));
+    const bool lists = L.P.nr > 1;
+    L.cnt = take(lists ? (size_t)B * L.P.nr * L.P.nch * sizeof(int32_t) : 0);
+    L.start = take(lists ? (size_t)B * (L.P.nr + 1) * sizeof(int32_t) : 0);
+    L.list = take((size_t)B * E_max * sizeof(ListEvent));
+    L.gw = take(L.P.lds && L.P.S == 1 ? 0 : (size_t)C_in * N * sizeof(long long));
+    L.gt = take((size_t)L.P.tiles * B * E_max * sizeof(double));
     L.total = off + 256;
     return L;
 }
 
-// Backward setup in one pass (grid-stride over every thread): the
-// fixed-point accumulators of dL/dW set to zero; the decays (A, D) per event,
-// dec[B][E_pad], identity past each sample's last event (so that the walks
-// stage whole segments); and per (sample, neuron) the reverse recurrence
-// over its spikes:
-//   lambda_s = g_s - ((V_th - V_reset)/tm) sum_{s'' > s} mu_s'' e^{-(t_s'' - t_s)/tm}
-//   mu_s     = -lambda_s / max(dV/dt(t_s), reg)
-// with the consumed-event count of its last spike (0 when silent): events
-// from there on feed no spike, and sum_s |mu_s|, which bounds the neuron's
-// P^m and P^s.
-__global__ __launch_bounds__(256) void k_bwd_setup(const float* __restrict__ ev_t, const int32_t* __restrict__ ev_n,
-                                                   int B, int E_max, int E_pad, int N, Model m,
-                                                   Decay* __restrict__ dec, long long* __restrict__ gw, size_t nW,
-                                                   const float* __restrict__ out_t, const int32_t* __restrict__ out_n,
-                                                   const float* __restrict__ out_i, const int32_t* __restrict__ out_k,
-                                                   const float* __restrict__ grad_out_t, double* __restrict__ mu,
-                                                   int32_t* __restrict__ klast, double* __restrict__ musum)
+// Suffix sums of one neuron's spike adjoints, last spike first (lambda_s and
+// mu_s as in spike_adjoints): ro[s] = (R^m_s, R^s_s), the sums over s' >= s of
+// mu_s' e^{-(t_s' - ref)/tm} and with ts, ref the spike's own reference.  Spikes are read kSufBatch at a time
+// (the recurrence waits for loads once per batch).  Returns sum_s |mu_s|.
+constexpr int kSufBatch = 4;
+
+__device__ __forceinline__ double spike_suffix_sums(const Model& m, int ns, const float* __restrict__ ts,
+                                                    const float* __restrict__ is, const float* __restrict__ g,
+                                                    double2* __restrict__ ro)
 {
+    const double len = kRefTs * m.ts;
+    const double jump = (m.th - m.vr) * m.inv_tm;
+    double Qm = 0.0, Qs = 0.0, tn = 0.0, asum = 0.0;
+    for (int s1 = ns - 1; s1 >= 0; s1 -= kSufBatch) {
+        float tb[kSufBatch], ib[kSufBatch], gb[kSufBatch];
+#pragma unroll
+        for (int u = 0; u < kSufBatch; ++u) {
+            const int s = max(s1 - u, 0);
+            tb[u] = ts[s];
+            ib[u] = is[s];
+            gb[u] = g[s];
+        }
+#pragma unroll
+        for (int u = 0; u < kSufBatch; ++u) {
+            const int s = s1 - u;
+            if (s < 0) break;
+            if (s + 1 < ns) {
+                const double dt = tn - (double)tb[u];
+                Qm *= exp(-dt * m.inv_tm);
+                Qs *= exp(-dt * m.inv_ts);
+            }
+            const double lam = (double)gb[u] - jump * Qm;
+            const double vp = fmax(((double)ib[u] - m.th) * m.inv_tm, m.reg);
+            const double mu = vp > 0.0 ? -lam / vp : 0.0;
+            Qm += mu;
+            Qs += mu;
+            tn = (double)tb[u];
+            asum += fabs(mu);
+            const double dr = ref_offset(tn, ref_index(tn, 1.0 / len), len);
+            ro[s] = make_double2(Qm * exp(-dr * m.inv_tm), Qs * exp(-dr * m.inv_ts));
+        }
+    }
+    return asum;
+}
+
+// Backward setup in one pass (grid-stride over every thread): the
+// fixed-point accumulators of dL/dW (where blocks are split) set to zero;
+// the suffix sums of every (sample, neuron)'s spike adjoints with its spike
+// count (0 when all its adjoints are exactly 0: such a neuron adds exactly 0
+// everywhere and is not walked; a NaN sum keeps it); per workgroup the largest
+// sum_s |mu_s| (NaN when one is NaN); and with one channel range the list of
+// every sample's events, else the events of each (sample, chunk) counted per
+// channel range, cnt[b][r][chunk], one wave per chunk.
+constexpr int kSetupThreads = 256;
+
+__global__ __launch_bounds__(kSetupThreads) void k_bwd_setup(
+    const float* __restrict__ ev_t, const int32_t* __restrict__ ev_src, const int32_t* __restrict__ ev_n, int B,
+    int E_max, int C_in, int N, Model m, long long* __restrict__ gw, size_t nW, const float* __restrict__ out_t, const int32_t* __restrict__ out_n,
+    const float* __restrict__ out_i, const int32_t* __restrict__ out_k, const float* __restrict__ grad_out_t,
+    double2* __restrict__ rtab, int32_t* __restrict__ ns_eff, double* __restrict__ part, int nr, int rows, int nch,
+    int32_t* __restrict__ cnt, ListEvent* __restrict__ list)
+{
+    __shared__ double s_m[kSetupThreads / kWave];
+    __shared__ int32_t s_cnt[kSetupThreads / kWave][kAdjMaxRanges];
     const size_t gtid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     const size_t gs = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = gtid; i < nW; i += gs) gw[i] = 0;
-    const size_t nD = (size_t)B * (size_t)E_pad;
-    for (size_t idx = gtid; idx < nD; idx += gs) {
-        const int b = (int)(idx / (size_t)E_pad), k = (int)(idx % (size_t)E_pad);
-        Decay d{1.0, 1.0, 0.0, 0.0};
-        if (k < clamp_count(ev_n[b], E_max)) {
-            const float* t = ev_t + (size_t)b * E_max;
-            const double dt = (double)t[k] - (k > 0 ? (double)t[k - 1] : 0.0);
-            d.A = exp(-dt * m.inv_tm);
-            d.D = exp(-dt * m.inv_ts);
-        }
-        dec[idx] = d;
-    }
+    const int lane = (int)threadIdx.x % kWave, wv = (int)threadIdx.x / kWave;
+    if (gw)
+        for (size_t i = gtid; i < nW; i += gs) gw[i] = 0;
     const size_t nn = (size_t)B * (size_t)N;
+    double mx = 0.0;
     for (size_t idx = gtid; idx < nn; idx += gs) {
-        const int ns = min(out_n[idx], m.s_max);
+        const int ns = max(min(out_n[idx], m.s_max), 0);
         const size_t o = idx * (size_t)m.s_max;
-        const double ms = spike_adjoints(m, ns, out_t + o, out_i + o, grad_out_t + o, mu + o);
-        musum[idx] = ms;
-        // a neuron whose spikes all have mu = 0 adds exactly 0 everywhere, so
-        // it is not walked (a NaN sum keeps it)
-        klast[idx] = ns > 0 && ms != 0.0 ? out_k[o + ns - 1] : 0;
+        const double ms = spike_suffix_sums(m, ns, out_t + o, out_i + o, grad_out_t + o, rtab + o);
+        ns_eff[idx] = ms != 0.0 ? ns : 0;
+        mx = ms != ms || mx != mx ? __builtin_nan("") : fmax(mx, ms);
+    }
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) {
+        const double o = __shfl_xor(mx, off, kWave);
+        mx = o != o || mx != mx ? __builtin_nan("") : fmax(mx, o);
+    }
+    if (lane == 0) s_m[wv] = mx;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int q = 1; q < kSetupThreads / kWave; ++q)
+            mx = s_m[q] != s_m[q] || mx != mx ? __builtin_nan("") : fmax(mx, s_m[q]);
+        part[blockIdx.x] = mx;
+    }
+    if (nr == 1) {
+        for (size_t i = gtid; i < (size_t)B * E_max; i += gs) {
+            const int b = (int)(i / (size_t)E_max), k = (int)(i % (size_t)E_max);
+            if (k < clamp_count(ev_n[b], E_max)) list[i] = list_event(m, ev_t[i], clamp_src(ev_src[i], C_in), k);
+        }
+        return;
+    }
+    const size_t nwv = gs / kWave;
+    for (size_t w = gtid / kWave; w < (size_t)B * nch; w += nwv) {
+        const int b = (int)(w / (size_t)nch), ch = (int)(w % (size_t)nch);
+        const int nb = clamp_count(ev_n[b], E_max);
+        for (int r = lane; r < nr; r += kWave) s_cnt[wv][r] = 0;
+        wave_lds_sync();
+        const int k1 = min((ch + 1) * kListChunk, nb);
+        for (int k = ch * kListChunk + lane; k < k1; k += kWave)
+            atomicAdd(&s_cnt[wv][clamp_src(ev_src[(size_t)b * E_max + k], C_in) / rows], 1);
+        wave_lds_sync();
+        for (int r = lane; r < nr; r += kWave) cnt[((size_t)b * nr + r) * nch + ch] = s_cnt[wv][r];
+        wave_lds_sync();
     }
 }
 
-// Fixed-point scale of the dL/dW sums (one workgroup): every contribution
+// Workgroup 0: the fixed-point scale of the dL/dW sums.  Every contribution
 // kappa (P^m - P^s) of a neuron is at most 2 kappa sum_s |mu_s| in size and a
 // sum takes at most one contribution per event of the batch, so with
 // bound = 2 kappa max_neuron(sum_s |mu_s|) (events in the batch) the scale
-// 2^(62 - ceil(log2 bound)) keeps every sum below 2^62.
-constexpr int kScaleThreads = 1024;
-
-__global__ __launch_bounds__(kScaleThreads) void k_bwd_scale(const double* __restrict__ musum, size_t nn,
-                                                             const int32_t* __restrict__ ev_n, int B, int E_max,
-                                                             double kappa, double* __restrict__ scale)
+// 2^(62 - ceil(log2 bound)) keeps every sum below 2^62.  A contribution is
+// then below 2^62 / events; scale[1] = 1 marks a call where that may reach
+// 2^51, or where a sum is not finite: its terms take the full conversion
+// (fx_term).  Workgroup 1 + b: the exclusive prefix sum of sample b's event
+// counts in (range, chunk) order, and where each range's list starts.
+__global__ __launch_bounds__(kPlanThreads) void k_bwd_plan(const double* __restrict__ part, int nparts,
+                                                   const int32_t* __restrict__ ev_n, int B, int E_max, double kappa,
+                                                   double* __restrict__ scale, int nr, int nch,
+                                                   int32_t* __restrict__ cnt, int32_t* __restrict__ start)
 {
-    __shared__ double s_max[kScaleThreads];
-    __shared__ double s_ev[kScaleThreads];
-    double mx = 0.0, ev = 0.0;
-    for (size_t i = threadIdx.x; i < nn; i += kScaleThreads) mx = fmax(mx, musum[i]);
-    for (int b = threadIdx.x; b < B; b += kScaleThreads) ev += (double)clamp_count(ev_n[b], E_max);
-    s_max[threadIdx.x] = mx;
-    s_ev[threadIdx.x] = ev;
-    __syncthreads();
-    for (int off = kScaleThreads / 2; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) {
-            s_max[threadIdx.x] = fmax(s_max[threadIdx.x], s_max[threadIdx.x + off]);
-            s_ev[threadIdx.x] += s_ev[threadIdx.x + off];
+    const int tid = (int)threadIdx.x, lane = tid % kWave, wv = tid / kWave;
+    if (blockIdx.x == 0) {
+        __shared__ double s_max[kPlanThreads / kWave], s_ev[kPlanThreads / kWave];
+        double mx = 0.0, ev = 0.0;
+        bool bad = false;
+        for (int i = tid; i < nparts; i += kPlanThreads) {
+            bad |= !isfinite(part[i]);
+            mx = fmax(mx, part[i]);
         }
-        __syncthreads();
+        for (int b = tid; b < B; b += kPlanThreads) ev += (double)clamp_count(ev_n[b], E_max);
+#pragma unroll
+        for (int off = kWave / 2; off > 0; off >>= 1) {
+            mx = fmax(mx, __shfl_xor(mx, off, kWave));
+            ev += __shfl_xor(ev, off, kWave);
+        }
+        if (lane == 0) {
+            s_max[wv] = mx;
+            s_ev[wv] = ev;
+        }
+        bad = __syncthreads_or(bad);
+        if (tid == 0) {
+            for (int q = 1; q < kPlanThreads / kWave; ++q) {
+                mx = fmax(mx, s_max[q]);
+                ev += s_ev[q];
+            }
+            const double bound = 2.0 * kappa * mx * fmax(ev, 1.0);
+            int ex = 0;
+            if (bound > 0.0 && isfinite(bound)) frexp(bound, &ex);    // bound < 2^ex
+            scale[0] = ldexp(1.0, 62 - ex);
+            scale[1] = bad || !(ev >= 4096.0) || !isfinite(bound) ? 1.0 : 0.0;
+        }
+        return;
     }
-    if (threadIdx.x == 0) {
-        const double bound = 2.0 * kappa * s_max[0] * fmax(s_ev[0], 1.0);
-        int ex = 0;
-        if (bound > 0.0 && isfinite(bound)) frexp(bound, &ex);    // bound < 2^ex
-        scale[0] = ldexp(1.0, 62 - ex);
-    }
-}
-
-// The neurons of each sample that fire, in neuron order (one workgroup per
-// sample: a ballot and a prefix sum over the waves per round of 256).
-constexpr int kLiveThreads = 256;
-
-__global__ __launch_bounds__(kLiveThreads) void k_bwd_live(const int32_t* __restrict__ klast, int N,
-                                                           int32_t* __restrict__ live, int32_t* __restrict__ nlive)
-{
-    __shared__ int s_cnt[kLiveThreads / kWave];
-    const int b = blockIdx.x, wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    const int b = (int)blockIdx.x - 1;
+    __shared__ int s_w[kPlanThreads / kWave];
+    int32_t* c = cnt + (size_t)b * nr * nch;
+    const int n = nr * nch;
     int base = 0;
-    for (int n0 = 0; n0 < N; n0 += kLiveThreads) {
-        const int n = n0 + (int)threadIdx.x;
-        const bool f = n < N && klast[(size_t)b * N + n] > 0;
-        const unsigned long long bal = __ballot(f);
-        const int below = __popcll(bal & ((1ull << lane) - 1ull));
-        if (lane == 0) s_cnt[wave] = __popcll(bal);
-        __syncthreads();
-        int off = base, tot = 0;
-        for (int q = 0; q < kLiveThreads / kWave; ++q) {
-            if (q < wave) off += s_cnt[q];
-            tot += s_cnt[q];
+    for (int i0 = 0; i0 < n; i0 += kPlanThreads) {
+        const int i = i0 + tid;
+        const int v = i < n ? c[i] : 0;
+        int incl = v;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int x = __shfl_up(incl, off, kWave);
+            if (lane >= off) incl += x;
         }
-        if (f) live[(size_t)b * N + off + below] = n;
+        if (lane == kWave - 1) s_w[wv] = incl;
+        __syncthreads();
+        int before = base, tot = 0;
+        for (int q = 0; q < kPlanThreads / kWave; ++q) {
+            if (q < wv) before += s_w[q];
+            tot += s_w[q];
+        }
+        const int ex = before + incl - v;
+        if (i < n) {
+            c[i] = ex;
+            if (i % nch == 0) start[(size_t)b * (nr + 1) + i / nch] = ex;
+        }
         base += tot;
         __syncthreads();
     }
-    if (threadIdx.x == 0) nlive[b] = base;
+    if (tid == 0) start[(size_t)b * (nr + 1) + nr] = base;
 }
 
-// Accumulators -> float32 outputs: dL/dW from fixed point, dL/dt as the sum
-// of the chunks' partial sums in chunk order (0 on padding).
+// The lists of several ranges: every event at its range's next place, in time
+// order (one wave per (sample, chunk); equal ranges among
+// 64 events ranked by ballots over the bits of the range).
+__global__ __launch_bounds__(kSetupThreads) void k_bwd_scatter(const float* __restrict__ ev_t,
+                                                               const int32_t* __restrict__ ev_src,
+                                                               const int32_t* __restrict__ ev_n, int B, int E_max,
+                                                               int C_in, Model m, int nr, int rows, int nch,
+                                                               const int32_t* __restrict__ cnt,
+                                                               ListEvent* __restrict__ list)
+{
+    __shared__ int32_t s_at[kSetupThreads / kWave][kAdjMaxRanges];
+    const int lane = (int)threadIdx.x % kWave, wv = (int)threadIdx.x / kWave;
+    const size_t w = (size_t)blockIdx.x * (kSetupThreads / kWave) + wv;
+    if (w >= (size_t)B * nch) return;
+    const int b = (int)(w / (size_t)nch), ch = (int)(w % (size_t)nch);
+    const int nb = clamp_count(ev_n[b], E_max);
+    const int k0 = ch * kListChunk, k1 = min(k0 + kListChunk, nb);
+    if (k0 >= k1) return;
+    int32_t* at = s_at[wv];
+    for (int r = lane; r < nr; r += kWave) at[r] = cnt[((size_t)b * nr + r) * nch + ch];
+    wave_lds_sync();
+    const unsigned long long below = (1ull << lane) - 1ull;
+    for (int k = k0 + lane; k - lane < k1; k += kWave) {
+        const bool ok = k < k1;
+        const size_t o = (size_t)b * E_max + (ok ? k : k0);
+        const int src = clamp_src(ev_src[o], C_in);
+        const float t = ev_t[o];
+        const int r = ok ? src / rows : 0;
+        unsigned long long same = __ballot(ok);
+        for (int bit = 1; bit < nr; bit <<= 1) {
+            const unsigned long long m = __ballot((r & bit) != 0);
+            same &= (r & bit) ? m : ~m;
+        }
+        const int pos = at[r] + __popcll(same & below);
+        wave_lds_sync();
+        if (ok) {
+            list[(size_t)b * E_max + pos] = list_event(m, t, src, k);
+            if ((same & below) == 0ull) at[r] = pos + __popcll(same);
+        }
+        wave_lds_sync();
+    }
+}
+
+// Accumulators -> float32 outputs: dL/dW from fixed point (where blocks are
+// split; else the walk has written it), dL/dt as the sum of the tiles'
+// partial sums in tile order (0 on padding).
 __global__ __launch_bounds__(256) void k_bwd_convert(const long long* __restrict__ gw, const double* __restrict__ scale,
                                                      float* __restrict__ grad_WT, size_t nW,
-                                                     const double* __restrict__ gt,
-                                                     const int32_t* __restrict__ nlive,
+                                                     const double* __restrict__ gt, int tiles,
                                                      const int32_t* __restrict__ ev_n, int E_max,
                                                      float* __restrict__ grad_ev_t, size_t nT)
 {
     const size_t gtid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     const size_t gs = (size_t)gridDim.x * blockDim.x;
-    const double inv = 1.0 / scale[0];
-    for (size_t i = gtid; i < nW; i += gs) grad_WT[i] = (float)((double)gw[i] * inv);
+    if (gw) {
+        const double inv = 1.0 / scale[0];
+        for (size_t i = gtid; i < nW; i += gs) grad_WT[i] = (float)((double)gw[i] * inv);
+    }
     if (gt)
         for (size_t i = gtid; i < nT; i += gs) {
             const int b = (int)(i / (size_t)E_max), k = (int)(i % (size_t)E_max);
             double s = 0.0;
-            if (k < clamp_count(ev_n[b], E_max)) {
-                const int chunks = (nlive[b] + kWave - 1) / kWave;
-                for (int q = 0; q < chunks; ++q) s += gt[(size_t)q * nT + i];
-            }
+            if (k < clamp_count(ev_n[b], E_max))
+                for (int q = 0; q < tiles; ++q) s += gt[(size_t)q * nT + i];
             grad_ev_t[i] = (float)s;
         }
 }
 
-// One wave per (sample, segment, chunk of 64 firing neurons), walking the
-// segment's events backwards: at event k, dL/dw += kappa (P^m - P^s) (one
-// fixed-point integer atomic per live lane) and the chunk's part of dL/dt_k,
-// the sum over lanes of w kappa (P^m/tm - P^s/ts), is stored; then P decays
-// to event k-1 and takes the spikes with out_k = k (those between events
-// k-1 and k).  A lane is live while its neuron has a spike after the event.
-constexpr int kSpkBatch = 8;
-constexpr int kPre = 4;
-
-__global__ __launch_bounds__(kWave * kWalkWaves) void k_event_adjoint(
-    const float* __restrict__ ev_t, const int32_t* __restrict__ ev_src, const int32_t* __restrict__ ev_n, int E_max,
-    int E_pad, const float* __restrict__ WT, int C_in, int N, int tiles, int S, int items, Model m,
-    const Decay* __restrict__ dec, const float* __restrict__ out_t, const int32_t* __restrict__ out_n,
-    const int32_t* __restrict__ out_k, const double* __restrict__ mu, const int32_t* __restrict__ klast,
-    const int32_t* __restrict__ live_list, const int32_t* __restrict__ nlive, const double* __restrict__ scale_p,
-    long long* __restrict__ gWT, double* __restrict__ gT, size_t nT)
+// A term v ks as a 64-bit integer, rounded to nearest even.  When it is below
+// 2^51 in size (not kWide), the integer is in the low bits of the sum with
+// 1.5 2^52, whose own bits are 0x43380000 in the high word: three instructions
+// against eleven.
+template <bool kWide>
+__device__ __forceinline__ unsigned long long fx_term(double v, double ks)
 {
-    __shared__ double2 s_ad[kWalkWaves][kSeg];
-    __shared__ float s_t[kWalkWaves][kSeg];
-    WalkCoords c;
-    if (!walk_coords<1>(items, tiles, S, ev_n, E_max, N, c)) return;
-    // the lane's neuron: entry tile * 64 + lane of the sample's list of
-    // firing neurons (chunks past the list have nothing to do)
-    const int nl = nlive[c.b];
-    if (c.tile * kWave >= nl) return;
-    const int lane = c.lane;
-    const int wv = (int)threadIdx.x / kWave;
-    c.live = c.tile * kWave + lane < nl;
-    c.n0 = c.live ? live_list[(size_t)c.b * N + c.tile * kWave + lane] : 0;
-    const int n = c.n0;
-    const float* tt = ev_t + (size_t)c.b * E_max;
-    const int kl = c.live ? klast[(size_t)c.b * N + n] : 0;
-    const int ns = c.live ? min(out_n[(size_t)c.b * N + n], m.s_max) : 0;
-    const bool liv = kl > c.k0;
-    // this chunk's part of dL/dt of the segment's events
-    double* gt = gT ? gT + (size_t)c.tile * nT + (size_t)c.b * E_max + c.k0 : nullptr;
-    if (__ballot(liv) == 0ull) {
-        if (gt && lane < c.cnt) gt[lane] = 0.0;
-        return;
+    if constexpr (kWide) return (unsigned long long)llrint(v * ks);
+    return (unsigned long long)__double_as_longlong(fma(v, ks, 0x1.8p52)) - 0x4338000000000000ull;
+}
+
+struct AdjArgs {
+    const float* ev_t;
+    const int32_t *ev_src, *ev_n;
+    const float* WT;
+    const float* out_t;
+    const int32_t *out_k, *ns;
+    const double2* r;
+    const double* scale;
+    const int32_t* start;
+    const ListEvent* list;
+    long long* gw;
+    float* grad_WT;
+    double* gt;
+    size_t nT;
+    double kappa, inv_tm, inv_ts, len, inv_len;            // len: kRefTs tau_s
+    double fm, fs, gm, gs;                                 // e^{-len/tm}, e^{-len/ts} and their reciprocals
+    int B, E_max, C_in, N, s_max, tiles, nr, rows, Q, S;
+};
+
+// P at time tk from the R of a neuron's spikes s .. ns - 1 (its first spike is
+// entry so), exponentials and all: the general form of P = R H.  A spike whose
+// float32 time lies before tk counts with offset 0.  (A call: inlined, the
+// constants of its exponentials would hold registers all through the walk.)
+__device__ __noinline__ double2 p_at(const float* ts, const double2* rr, int s, int ns, double tk, double tau_m,
+                                     double tau_s)
+{
+    const double len = kRefTs * tau_s, inv_tm = 1.0 / tau_m, inv_ts = 1.0 / tau_s;
+    double am = 0.0, as = 0.0;
+    double2 q1 = make_double2(0.0, 0.0);
+    for (;; ++s) {
+        const double t1 = (double)ts[s], dr = ref_offset(t1, ref_index(t1, 1.0 / len), len);
+        q1 = make_double2(rr[s].x * exp(dr * inv_tm), rr[s].y * exp(dr * inv_ts));       // Q_s
+        const double du = t1 - tk;
+        if (!(du < 0.0)) return make_double2(fma(q1.x, exp(-du * inv_tm), am), fma(q1.y, exp(-du * inv_ts), as));
+        if (s + 1 >= ns) return make_double2(am + q1.x, as + q1.y);
+        const double t2 = (double)ts[s + 1], d2 = ref_offset(t2, ref_index(t2, 1.0 / len), len), dt = t2 - t1;
+        am += q1.x - rr[s + 1].x * exp((d2 - dt) * inv_tm);                              // mu_s
+        as += q1.y - rr[s + 1].y * exp((d2 - dt) * inv_ts);
     }
-    const double scale = scale_p[0];
-    double2* lad = s_ad[wv];
-    float* lt = s_t[wv];
-    const Stage st = stage_segment(c, ev_src + (size_t)c.b * E_max + c.k0, dec + (size_t)c.b * E_pad + c.k0, WT,
-                                   C_in, N, lad, nullptr, nullptr);
-#pragma unroll
-    for (int h = 0; h < kSrcRegs; ++h) {
-        const int e = h * kWave + lane;
-        if (e < c.cnt) lt[e] = tt[c.k0 + e];
-    }
-    wave_lds_sync();
-    const int elast = c.k0 + c.cnt - 1;
-    const double tk = (double)lt[c.cnt - 1];
-    const size_t base = ((size_t)c.b * N + n) * (size_t)m.s_max;
-    const float* ts = out_t + base;
-    const int32_t* ks = out_k + base;
-    const double* mo = mu + base;
-    // One pass over the lane's spikes (from the first one past the
-    // segment's start, found by bisection when the list is long), in
-    // batches of kSpkBatch loaded together: the closed-form P at the
-    // segment's last event from the spikes after it, and the last kPre
-    // spikes inside the segment (pk[0] the latest).
-    int q0 = 0;
-    if (__ballot(liv && ns > 2 * kSpkBatch)) {
-        int hi = liv ? ns : 0;
-        while (q0 < hi) {
-            const int mid = (q0 + hi) >> 1;
-            if (ks[mid] > c.k0) hi = mid; else q0 = mid + 1;
+}
+
+// One workgroup per (64 neurons, channel range, slice of the (sample, part)
+// units); lanes are neurons and a wave takes one unit at a time (a counter in
+// LDS), walking its listed events backwards: at event k, with P = R H, dL/dw
+// += kappa (P^m - P^s) into the block in LDS and the tile's part of dL/dt_k,
+// the sum over lanes of w kappa (P^m/tm - P^s/ts), is stored; then a lane with
+// spikes between the listed event before it and event k switches its R.  The
+// spikes that a group of kGrp events passes are looked up before the group, all
+// lanes together (at most two per lane).  A group where a lane passes more, or
+// one whose float32 time lies before the event below it, and a block of 64
+// events over more than 3 len, go event by event through p_at.
+// kLds = false: dL/dW by global atomics; kTime: dL/dt wanted (else no weight is
+// read).
+// Bound by VALU issue (82 % busy at the first shape below, 69 % at the second):
+// about 30 instructions per (event, 64 neurons), float64 four cycles each.  H
+// and the rows come by lane reads: as LDS broadcasts they shared the pipe
+// with the adds and bounded the walk (1.44 against 0.97 ms).  Twelve waves of up
+// to 168 registers against sixteen of 128 with spills: 7.0 -> 5.9 ms at the
+// second shape with three units per wave.  With dL/dt, 700 -> 512, B = 128,
+// 10 k events: 0.97 ms; 32768 -> 2048, B = 16, 100 k events: 5.9 ms (one wave per
+// 64 events with global atomics: 3.49 and 24.7 ms).
+template <bool kLds, bool kTime>
+__global__ __launch_bounds__(kAdjThreads) void k_adjoint(const AdjArgs a)
+{
+    extern __shared__ unsigned long long s_acc[];          // [rows][64] sums
+    __shared__ int s_next;
+    const int lane = (int)threadIdx.x % kWave;
+    const int tile = (int)(blockIdx.x % (unsigned)a.tiles);
+    const int r = (int)((blockIdx.x / (unsigned)a.tiles) % (unsigned)a.nr);
+    const int slice = (int)(blockIdx.x / ((unsigned)a.tiles * (unsigned)a.nr));
+    const int c0 = r * a.rows, rows = kLds ? min(a.rows, a.C_in - c0) : 0;
+    const int n = tile * kWave + lane;
+    const bool live = n < a.N;
+    const int nc = live ? n : 0;
+    if (kLds)
+        for (int i = (int)threadIdx.x; i < rows * kWave; i += (int)blockDim.x) s_acc[i] = 0ull;
+    if (threadIdx.x == 0) s_next = 0;
+    __syncthreads();
+    const double scale = a.scale[0], ks = a.kappa * scale;
+    const bool wide = __builtin_amdgcn_readfirstlane(a.scale[1] != 0.0 ? 1 : 0) != 0;
+    const double ktm = a.kappa * a.inv_tm, kts = -a.kappa * a.inv_ts;
+    const bool lists = a.nr > 1;
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)a.WT, (short)0, (int)((uint32_t)a.C_in * (uint32_t)a.N * 4u), kRsrcWord3);
+    const int units = a.B * a.Q;
+    for (;;) {
+        int u = 0;
+        if (lane == 0) u = atomicAdd(&s_next, 1);
+        u = __builtin_amdgcn_readfirstlane(u);
+        const long long id = slice + (long long)u * a.S;
+        if (id >= units) break;
+        const int b = (int)id / a.Q, q = (int)id % a.Q;
+        const int nb = clamp_count(a.ev_n[b], a.E_max);
+        const int L0 = lists ? a.start[(size_t)b * (a.nr + 1) + r] : 0;
+        const int L1 = lists ? a.start[(size_t)b * (a.nr + 1) + r + 1] : nb;
+        const int per = ((L1 - L0 + a.Q - 1) / a.Q + kWave - 1) / kWave * kWave;
+        const int l0 = L0 + q * per, l1 = min(l0 + per, L1);
+        if (l0 >= l1) continue;
+        const ListEvent* ll = a.list + (size_t)b * a.E_max;
+        // a block of 64 listed events at l (lane i: event l + i, the last one
+        // again past l1)
+        auto load = [&](int l) { return ll[min(l + lane, l1 - 1)]; };
+        auto rl_f = [](float v, int l) {
+            return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
+        };
+        const size_t bn = (size_t)b * a.N + nc;
+        const int ns = live ? a.ns[bn] : 0;
+        const size_t so = bn * (size_t)a.s_max;            // the neuron's spikes
+        double* gt = kTime ? a.gt + (size_t)tile * a.nT + (size_t)b * a.E_max : nullptr;
+        int lb = l0 + ((l1 - l0 - 1) / kWave) * kWave;     // the topmost block
+        ListEvent cur = load(lb);
+        const int kfirst = __builtin_amdgcn_readfirstlane(ll[l0].k);
+        if (__ballot(ns > 0 && a.out_k[so + max(ns - 1, 0)] > kfirst) == 0ull) {
+            // no neuron fires after the unit's first event
+            if (kTime)
+                for (int l = l0 + lane; l < l1; l += kWave) gt[ll[l].k] = 0.0;
+            continue;
         }
-    }
-    double Pm = 0.0, Ps = 0.0;
-    int pk[kPre];
-    float pt[kPre];
-    double pm[kPre];
-#pragma unroll
-    for (int u = 0; u < kPre; ++u) {
-        pk[u] = -1;
-        pt[u] = 0.0f;
-        pm[u] = 0.0;
-    }
-    int nin = 0, sp = q0;                        // spikes inside the segment; first spike after it
-    for (int qb = q0; __ballot(liv && qb < ns); qb += kSpkBatch) {
-        int kq[kSpkBatch];
-        float tq[kSpkBatch];
-        double mq[kSpkBatch];
-#pragma unroll
-        for (int u = 0; u < kSpkBatch; ++u) {
-            const int q = min(qb + u, max(ns - 1, 0));
-            kq[u] = ks[q];
-            tq[u] = ts[q];
-            mq[u] = mo[q];
-        }
-#pragma unroll
-        for (int u = 0; u < kSpkBatch; ++u) {
-            if (!liv || qb + u >= ns) continue;
-            if (kq[u] > elast) {
-                const double du = fmax((double)tq[u] - tk, 0.0);
-                Pm += mq[u] * exp(-du * m.inv_tm);
-                Ps += mq[u] * exp(-du * m.inv_ts);
-            } else {
-                sp = qb + u + 1;
-                if (kq[u] > c.k0) {
-#pragma unroll
-                    for (int v = kPre - 1; v > 0; --v) {
-                        pk[v] = pk[v - 1];
-                        pt[v] = pt[v - 1];
-                        pm[v] = pm[v - 1];
-                    }
-                    pk[0] = kq[u];
-                    pt[0] = tq[u];
-                    pm[0] = mq[u];
-                    ++nin;
-                }
+        int cnt = l1 - lb;                                 // events of the block
+        int sp;                                            // first spike with out_k > k of the walk's event
+        {
+            const int kt = __builtin_amdgcn_readlane(cur.k, cnt - 1);
+            int lo = 0, hi = ns;
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (a.out_k[so + mid] > kt) hi = mid; else lo = mid + 1;
             }
+            sp = lo;
         }
-    }
-    // A wave where some lane has more than kPre spikes inside the segment (a
-    // burst) walks with each further spike loaded when it is reached (those
-    // loads then wait behind the atomics); otherwise the walk loads nothing
-    // but the weights.
-    const bool burst = __ballot(nin > kPre) != 0ull;
-    const double kap = m.kappa;
-    auto walk = [&](auto burst_tag) {
-        constexpr bool kBurst = decltype(burst_tag)::value;
-        int taken = 0;                           // spikes of the segment taken so far
-        int knext = pk[0];
-        double tnext = (double)pt[0], mnext = pm[0];
-        auto advance = [&]() {
-            ++taken;
-#pragma unroll
-            for (int u = 0; u + 1 < kPre; ++u) {
-                pk[u] = pk[u + 1];
-                pt[u] = pt[u + 1];
-                pm[u] = pm[u + 1];
+        // the next spike the walk meets, sp - 1, and k of the one after it
+        // (k = -1: none)
+        int k1 = -1, k2 = -1;
+        float t1 = 0.0f;
+        double2 R1 = make_double2(0.0, 0.0);
+        auto refill = [&]() {
+            k1 = k2 = -1;
+            if (sp >= 1) {
+                k1 = a.out_k[so + sp - 1];
+                t1 = a.out_t[so + sp - 1];
+                R1 = a.r[so + sp - 1];
             }
-            pk[kPre - 1] = -1;
-            knext = pk[0];
-            tnext = (double)pt[0];
-            mnext = pm[0];
-            if (kBurst && taken >= kPre) {
-                const int q = sp - 1 - taken;
-                const bool in = q >= 0 && taken < nin;
-                knext = in ? ks[max(q, 0)] : -1;
-                tnext = in ? (double)ts[max(q, 0)] : 0.0;
-                mnext = in ? mo[max(q, 0)] : 0.0;
+            if (sp >= 2) k2 = a.out_k[so + sp - 2];
+        };
+        if (ns > 0) refill();
+        // R of a spike at time t referred to the block's reference
+        int ref = -1;                                      // -1: none
+        auto refer = [&](double2 v, float t) {
+            const int d = ref_index((double)t, a.inv_len) - ref;
+            if (__builtin_expect(d != 0, 0)) {
+                v.x *= ref_pow(a.fm, a.gm, d);
+                v.y *= ref_pow(a.fs, a.gs, d);
+            }
+            return v;
+        };
+        auto load_w = [&](int woff, int g, float (&w)[kGrp]) {
+            if constexpr (kTime) {
+#pragma unroll
+                for (int j = 0; j < kGrp; ++j)
+                    w[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                         rsrc, (uint32_t)nc * 4u,
+                                                         __builtin_amdgcn_readlane(woff, g * kGrp + j), 0));
             }
         };
-        auto group = [&](int g, const float (&w)[kGrp][1]) {
-            double ca[kGrp];
-            long long ga[kGrp];
-            const int oreg = g * kGrp < kWave ? st.off[0] : st.off[kSrcRegs - 1];
+        // the walk: kWide as in fx_term
+        auto walk = [&](auto wide_tag) {
+            constexpr bool kWide = decltype(wide_tag)::value;
+            auto add_w = [&](unsigned long long x, int ro) {
+                if constexpr (kLds) atomicAdd(&s_acc[ro + lane], x);
+                else if (x != 0ull) atomicAdd((unsigned long long*)&a.gw[(size_t)ro + n], x);
+            };
+            const int rmul = kLds ? kWave : a.N;
+            double Rm = 0.0, Rs = 0.0;
+            float w[kGrp], wn[kGrp];
+            int woff = cur.src * a.N * 4;
+            load_w(woff, (cnt - 1) / kGrp, w);
+            auto take = [&]() {                            // R of spike sp
+                Rm = Rs = 0.0;
+                if (sp < ns) {
+                    const double2 v = refer(a.r[so + sp], a.out_t[so + sp]);
+                    Rm = v.x;
+                    Rs = v.y;
+                }
+            };
+            for (;;) {
+                const bool more = lb > l0;
+                ListEvent nxt = cur;
+                if (more) nxt = load(lb - kWave);
+                // the block's reference is its first event's; none (event by
+                // event) when the block spans more than 3 len
+                {
+                    int nref = __builtin_amdgcn_readlane(cur.ref, 0);
+                    if (__builtin_amdgcn_readlane(cur.ref, cnt - 1) - nref > 3) nref = -1;
+                    const bool moved = nref != ref;
+                    ref = nref;
+                    if (moved && ref >= 0) take();
+                }
+                // H of the block's events, referred to the block's reference
+                double hm = cur.Hm, hs = cur.Hs;
+                if (ref >= 0 && __ballot(cur.ref != ref)) {
+                    asm volatile("");
+                    const int d = min(max(cur.ref - ref, 0), 3);
+                    hm *= ref_pow(a.gm, a.fm, d);
+                    hs *= ref_pow(a.gs, a.fs, d);
+                }
+                const int row = (cur.src - c0) * rmul;
+                const int woff_n = nxt.src * a.N * 4;
+                // k and time of the event below the block (past the unit's
+                // first event spikes do not matter)
+                const int kbelow = __builtin_amdgcn_readlane(more ? nxt.k : cur.k, more ? kWave - 1 : 0);
+                const float tbelow = rl_f(more ? nxt.t : cur.t, more ? kWave - 1 : 0);
+                for (int g = (cnt - 1) / kGrp; g >= 0; --g) {
+                    const int klo = g > 0 ? __builtin_amdgcn_readlane(cur.k, g > 0 ? g * kGrp - 1 : 0) : kbelow;
+                    const int ne = min(kGrp, cnt - g * kGrp);
+                    const bool pass = k1 > klo;
+                    const bool any = __ballot(pass) != 0ull;
+                    bool any2 = false, slow = ref < 0;
+                    int x1 = -1, x2 = -1;                  // R switched after event x of the group
+                    double2 X1 = make_double2(0.0, 0.0), X2 = X1;
+                    if (any && !slow) {
+                        const bool pass2 = pass && k2 > klo;
+                        any2 = __ballot(pass2) != 0ull;
+                        int y1 = 0;
 #pragma unroll
-            for (int jj = kGrp - 1; jj >= 0; --jj) {
-                const int e = g * kGrp + jj;
-                ca[jj] = 0.0;
-                ga[jj] = 0;
-                if (e >= c.cnt) continue;
-                ga[jj] = liv ? llrint(kap * (Pm - Ps) * scale) : 0;
-                if (gt && liv) ca[jj] = (double)w[jj][0] * kap * (Pm * m.inv_tm - Ps * m.inv_ts);
-                if (e > 0) {
-                    const double2 ad = lad[e];
-                    Pm *= ad.x;
-                    Ps *= ad.y;
-                    const double tp = (double)lt[e - 1];
-                    // spikes between events e - 1 and e (out_k = e)
-                    while (knext >= c.k0 + e) {
-                        const double u = fmax(tnext - tp, 0.0);
-                        Pm += mnext * exp(-u * m.inv_tm);
-                        Ps += mnext * exp(-u * m.inv_ts);
-                        advance();
+                        for (int j = 0; j < kGrp; ++j)
+                            y1 += __builtin_amdgcn_readlane(cur.k, g * kGrp + j) < k1 ? 1 : 0;
+                        // the time of the listed event below (of event y1 - 1)
+                        const int el = g * kGrp + min(y1, kGrp - 1) - 1;
+                        const float te = __shfl(cur.t, max(el, 0), kWave);
+                        bool bad = pass && t1 < (el < 0 ? tbelow : te);
+                        float t2 = 0.0f;
+                        if (__builtin_expect(any2, 0)) {
+                            int y2 = 0;
+                            if (pass2) t2 = a.out_t[so + sp - 2];
+#pragma unroll
+                            for (int j = 0; j < kGrp; ++j)
+                                y2 += __builtin_amdgcn_readlane(cur.k, g * kGrp + j) < k2 ? 1 : 0;
+                            const int el2 = g * kGrp + min(y2, kGrp - 1) - 1;
+                            const float te2 = __shfl(cur.t, max(el2, 0), kWave);
+                            bad = bad || (pass2 && (t2 < (el2 < 0 ? tbelow : te2) ||
+                                                    (sp >= 3 && a.out_k[so + max(sp - 3, 0)] > klo)));
+                            x2 = pass2 ? y2 : -1;
+                        }
+                        slow = __ballot(bad) != 0ull;
+                        if (!slow) {
+                            if (pass) {
+                                x1 = y1;
+                                X1 = refer(R1, t1);
+                                --sp;
+                                if (pass2) {
+                                    X2 = refer(a.r[so + sp - 1], t2);
+                                    --sp;
+                                }
+                                refill();
+                            }
+                        }
+                    }
+                    if (g > 0) load_w(woff, g - 1, wn);
+                    else if (more) load_w(woff_n, kWave / kGrp - 1, wn);
+                    if (__builtin_expect(!slow, 1)) {
+                        double ca[kGrp / 2], c4[kGrp / 2];
+                        auto events = [&](auto full_tag) {
+                            constexpr bool kFull = decltype(full_tag)::value;
+#pragma unroll
+                            for (int jj = kGrp - 1; jj >= 0; --jj) {
+                                double cj = 0.0;
+                                if (kFull || jj < ne) {
+                                    const int e = g * kGrp + jj;
+                                    const double Pm = Rm * read_lane_double(hm, e), Ps = Rs * read_lane_double(hs, e);
+                                    add_w(fx_term<kWide>(Pm - Ps, ks), __builtin_amdgcn_readlane(row, e));
+                                    if constexpr (kTime) cj = (double)w[jj] * fma(ktm, Pm, kts * Ps);
+                                    if (any && __ballot(x1 == jj)) {
+                                        asm volatile("");          // a branch, not eight selects per event
+                                        if (x1 == jj) {
+                                            Rm = X1.x;
+                                            Rs = X1.y;
+                                        }
+                                    }
+                                    if (any2 && __ballot(x2 == jj)) {
+                                        asm volatile("");
+                                        if (x2 == jj) {
+                                            Rm = X2.x;
+                                            Rs = X2.y;
+                                        }
+                                    }
+                                }
+                                // (the first exchange of group_sum8 as soon as
+                                // both of its values are there)
+                                if constexpr (kTime) {
+                                    if (jj >= kGrp / 2) ca[jj - kGrp / 2] = cj;
+                                    else c4[jj] = swap_sum32(cj, ca[jj]);
+                                }
+                            }
+                        };
+                        if (ne == kGrp) events(std::true_type{});
+                        else events(std::false_type{});
+                        if constexpr (kTime) {
+                            const double s = group_sum4(c4, lane);
+                            const int j = ((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1);
+                            const int k = __shfl(cur.k, g * kGrp + j, kWave);
+                            if ((lane & 7) == 0 && j < ne) gt[k] = s;
+                        }
+                    } else {
+#pragma unroll 1
+                        for (int e = g * kGrp + ne - 1; e >= g * kGrp; --e) {
+                            double2 P = make_double2(0.0, 0.0);
+                            if (sp < ns) P = p_at(a.out_t + so, a.r + so, sp, ns, (double)rl_f(cur.t, e), 1.0 / a.inv_tm, 1.0 / a.inv_ts);
+                            add_w(fx_term<kWide>(P.x - P.y, ks), __builtin_amdgcn_readlane(row, e));
+                            if constexpr (kTime) {
+                                const float we = __builtin_bit_cast(
+                                    float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, (uint32_t)nc * 4u,
+                                                                                __builtin_amdgcn_readlane(woff, e), 0));
+                                double s = (double)we * fma(ktm, P.x, kts * P.y);
+#pragma unroll
+                                for (int off = kWave / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, kWave);
+                                if (lane == 0) gt[__builtin_amdgcn_readlane(cur.k, e)] = s;
+                            }
+                            const int kp = e > g * kGrp ? __builtin_amdgcn_readlane(cur.k, max(e - 1, 0)) : klo;
+                            while (sp > 0 && ns > 0 && a.out_k[so + sp - 1] > kp) --sp;
+                        }
+                        if (ref >= 0) take();
+                        if (ns > 0) refill();
+                    }
+                    if constexpr (kTime) {
+#pragma unroll
+                        for (int j = 0; j < kGrp; ++j) w[j] = wn[j];
                     }
                 }
-            }
-            // the group's weight-gradient terms after its walk, so that the
-            // waits for the next weights do not wait for the atomics
-#pragma unroll
-            for (int jj = 0; jj < kGrp; ++jj) {
-                const int e = g * kGrp + jj;
-                const int roff = __builtin_amdgcn_readlane(oreg, e & (kWave - 1));
-                if (ga[jj] != 0)
-                    atomicAdd((unsigned long long*)&gWT[(size_t)(roff >> 2) + (size_t)n],
-                              (unsigned long long)ga[jj]);
-            }
-            if (gt) {
-                const double r = group_sum8(ca, lane);
-                const int j = ((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1);
-                const int e = g * kGrp + j;
-                if ((lane & 7) == 0 && e < c.cnt) gt[e] = r;
+                if (!more) break;
+                cur = nxt;
+                woff = woff_n;
+                lb -= kWave;
+                cnt = kWave;
             }
         };
-        // groups from the last backwards, the weights of the next one in flight
-        const int ng = (c.cnt + kGrp - 1) / kGrp;
-        float wa[kGrp][1], wb[kGrp][1];
-        load_grp<1>(st, (ng - 1) * kGrp, wa);
-        for (int g = ng - 1; g >= 0; g -= 2) {
-            if (g >= 1) load_grp<1>(st, (g - 1) * kGrp, wb);
-            group(g, wa);
-            if (g < 1) break;
-            if (g >= 2) load_grp<1>(st, (g - 2) * kGrp, wa);
-            group(g - 1, wb);
+        if (__builtin_expect(wide, 0)) walk(std::true_type{});
+        else walk(std::false_type{});
+    }
+    if constexpr (kLds) {
+        __syncthreads();
+        const double inv = 1.0 / scale;
+        for (int i = (int)threadIdx.x; i < rows * kWave; i += (int)blockDim.x) {
+            const int nn = tile * kWave + i % kWave;
+            if (nn >= a.N) continue;
+            const size_t at = (size_t)(c0 + i / kWave) * a.N + nn;
+            const long long v = (long long)s_acc[i];
+            if (a.S == 1) a.grad_WT[at] = (float)((double)v * inv);
+            else if (v) atomicAdd((unsigned long long*)&a.gw[at], (unsigned long long)v);
         }
-    };
-    if (burst) walk(std::true_type{});
-    else walk(std::false_type{});
+    }
 }
 
 int backward_impl(const float* ev_t, const int32_t* ev_src, const int32_t* ev_n, int B, int E_max, const float* WT,
@@ -424,41 +821,70 @@ int backward_impl(const float* ev_t, const int32_t* ev_src, const int32_t* ev_n,
     if ((size_t)C_in * (size_t)N >= ((size_t)1 << 29)) return LIF_ERR_SIZE;   // 32-bit W^T byte offsets
     BwdLayout L = bwd_layout(B, E_max, C_in, N, p->s_max);
     if (ws_bytes < L.total) return LIF_ERR_WORKSPACE;
+    const BwdPlan& P = L.P;
+    const size_t wgs = (size_t)P.tiles * P.nr * P.S;
+    if ((size_t)B * ((E_max + kSeg - 1) / kSeg) * P.tiles > 0x7fffffff || wgs > 0x7fffffff ||
+        (size_t)B * P.Q > 0x3fffffff)
+        return LIF_ERR_SIZE;
     Model m = make_model(*p);
     char* base = (char*)(((uintptr_t)ws + 255) & ~(uintptr_t)255);
-    Decay* dec = (Decay*)(base + L.dec);
-    double* mu = (double*)(base + L.mu);
-    int32_t* klast = (int32_t*)(base + L.klast);
-    int32_t* live = (int32_t*)(base + L.live);
-    int32_t* nlive = (int32_t*)(base + L.nlive);
-    double* musum = (double*)(base + L.musum);
+    double2* q = (double2*)(base + L.q);
+    int32_t* ns = (int32_t*)(base + L.ns);
+    double* part = (double*)(base + L.part);
     double* scale = (double*)(base + L.scale);
-    long long* gw = (long long*)(base + L.gw);
+    const bool lists = P.nr > 1;
+    int32_t* cnt = lists ? (int32_t*)(base + L.cnt) : nullptr;
+    int32_t* start = lists ? (int32_t*)(base + L.start) : nullptr;
+    ListEvent* list = (ListEvent*)(base + L.list);
+    const bool direct = P.lds && P.S == 1;                 // the walk writes dL/dW itself
+    long long* gw = direct ? nullptr : (long long*)(base + L.gw);
     double* gt = grad_ev_t ? (double*)(base + L.gt) : nullptr;
-    size_t nW = (size_t)C_in * N, nT = (size_t)B * E_max, nn = (size_t)B * N;
-    const size_t nD = (size_t)B * L.E_pad;
-    {
-        size_t work = nW;
-        if (nD > work) work = nD;
-        if (nn > work) work = nn;
-        size_t blocks = (work + 255) / 256;
-        if (blocks > 2048) blocks = 2048;
-        if (blocks < 1) blocks = 1;
-        TIMED_LAUNCH("bwd_setup", k_bwd_setup, dim3((unsigned)blocks), dim3(256), 0, stream, ev_t, ev_n, B, E_max,
-                     L.E_pad, N, m, dec, gw, nW, out_t, out_n, out_i, out_k, grad_out_t, mu, klast, musum);
+    const size_t nW = (size_t)C_in * N, nT = (size_t)B * E_max, nn = (size_t)B * N;
+    const size_t chunks = (size_t)B * P.nch;
+    size_t work = nn;
+    if (gw && nW > work) work = nW;
+    if (lists && chunks * kWave > work) work = chunks * kWave;
+    if (!lists && nT > work) work = nT;
+    size_t blocks = (work + kSetupThreads - 1) / kSetupThreads;
+    blocks = blocks < 1 ? 1 : (blocks > kSetupBlocks ? kSetupBlocks : blocks);
+    TIMED_LAUNCH("bwd_setup", k_bwd_setup, dim3((unsigned)blocks), dim3(kSetupThreads), 0, stream, ev_t, ev_src,
+                 ev_n, B, E_max, C_in, N, m, gw, nW, out_t, out_n, out_i, out_k, grad_out_t, q, ns, part, P.nr, P.rows,
+                 P.nch, cnt, list);
+    TIMED_LAUNCH("bwd_plan", k_bwd_plan, dim3((unsigned)(1 + (lists ? B : 0))), dim3(kPlanThreads), 0, stream, part,
+                 (int)blocks, ev_n, B, E_max, m.kappa, scale, P.nr, P.nch, cnt, start);
+    if (lists && chunks)
+        TIMED_LAUNCH("bwd_scatter", k_bwd_scatter,
+                     dim3((unsigned)((chunks + kSetupThreads / kWave - 1) / (kSetupThreads / kWave))),
+                     dim3(kSetupThreads), 0, stream, ev_t, ev_src, ev_n, B, E_max, C_in, m, P.nr, P.rows, P.nch,
+                     cnt, list);
+    const size_t units = ((size_t)B * P.Q + P.S - 1) / P.S;
+    const int waves = (int)(units < 1 ? 1 : (units > kAdjWaves ? kAdjWaves : units));
+    const size_t lds = P.lds ? (size_t)P.rows * kWave * sizeof(long long) : 0;
+    const double len = kRefTs * m.ts;
+    const AdjArgs a{ev_t, ev_src, ev_n, WT, out_t, out_k, ns, q, scale, start, list, gw, grad_WT, gt, nT, m.kappa,
+                    m.inv_tm, m.inv_ts, len, 1.0 / len, exp(-len * m.inv_tm), exp(-len * m.inv_ts),
+                    exp(len * m.inv_tm), exp(len * m.inv_ts), B, E_max, C_in, N, m.s_max, P.tiles, P.nr, P.rows, P.Q,
+                    P.S};
+    auto adjoint = [&](auto kern) -> int {
+        // the block exceeds the default dynamic-LDS limit; the attribute is
+        // set on every call (for the current device; no state kept here)
+        if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)(kAdjRows * kWave * sizeof(long long))) != hipSuccess)
+            return LIF_ERR_HIP;
+        TIMED_LAUNCH("event_adjoint", kern, dim3((unsigned)wgs), dim3(kWave * waves), lds, stream, a);
+        return LIF_OK;
+    };
+    if (P.lds) rc = gt ? adjoint(k_adjoint<true, true>) : adjoint(k_adjoint<true, false>);
+    else rc = gt ? adjoint(k_adjoint<false, true>) : adjoint(k_adjoint<false, false>);
+    if (rc) return rc;
+    if (gw || gt) {
+        work = gw ? nW : 0;
+        if (gt && nT > work) work = nT;
+        blocks = (work + 255) / 256;
+        blocks = blocks < 1 ? 1 : (blocks > 2048 ? 2048 : blocks);
+        TIMED_LAUNCH("bwd_convert", k_bwd_convert, dim3((unsigned)blocks), dim3(256), 0, stream, gw, scale, grad_WT,
+                     nW, gt, P.tiles, ev_n, E_max, grad_ev_t, nT);
     }
-    TIMED_LAUNCH("bwd_scale", k_bwd_scale, dim3(1), dim3(kScaleThreads), 0, stream, musum, nn, ev_n, B, E_max,
-                 m.kappa, scale);
-    if (B > 0) TIMED_LAUNCH("bwd_live", k_bwd_live, dim3((unsigned)B), dim3(kLiveThreads), 0, stream, klast, N, live, nlive);
-    const int tiles = (N + kWave - 1) / kWave;
-    const size_t items = (size_t)B * L.S * tiles;
-    if (items > 0x7fffffff) return LIF_ERR_SIZE;
-    const unsigned blocks = (unsigned)((items + kWalkWaves - 1) / kWalkWaves);
-    if (items) TIMED_LAUNCH("event_adjoint", k_event_adjoint, dim3(blocks), dim3(kWave * kWalkWaves), 0, stream,
-                            ev_t, ev_src, ev_n, E_max, L.E_pad, WT, C_in, N, tiles, L.S, (int)items, m, dec, out_t,
-                            out_n, out_k, mu, klast, live, nlive, scale, gw, gt, nT);
-    TIMED_LAUNCH("bwd_convert", k_bwd_convert, dim3(1024), dim3(256), 0, stream, gw, scale, grad_WT, nW, gt, nlive,
-                 ev_n, E_max, grad_ev_t, nT);
     return check_launch();
 }
 

@@ -160,28 +160,56 @@ __device__ __forceinline__ void load_grp(const Stage& st, int e0, float (&w)[kGr
 
 // Sums over the 64 lanes of v[0..7] (one value per event of a group):
 // lane l ends with the sum of v[j] for j = 4 b5 + 2 b4 + b3 (b5, b4, b3 the
-// bits 5, 4, 3 of l), by a halving exchange (4 + 2 + 1 shuffles) and a
-// butterfly over the lane's 8-lane row (3 shuffles).
+// bits 5, 4, 3 of l).  Two halving exchanges by the half-wave and row swaps
+// (of a pair (a, b), v_permlane32_swap leaves {a low, b low} and {a high, b
+// high}, v_permlane16_swap the same for rows of 16 lanes, so one add sums
+// both), then DPP moves within the row: about 40 instructions and no LDS
+// crossbar traffic, against 100 and 20 lane permutes.
+__device__ __forceinline__ double swap_sum32(double a, double b)
+{
+    const unsigned long long x = (unsigned long long)__double_as_longlong(a), y = (unsigned long long)__double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    return __longlong_as_double((long long)(((unsigned long long)hi[0] << 32) | lo[0])) +
+           __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1]));
+}
+
+__device__ __forceinline__ double swap_sum16(double a, double b)
+{
+    const unsigned long long x = (unsigned long long)__double_as_longlong(a), y = (unsigned long long)__double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    return __longlong_as_double((long long)(((unsigned long long)hi[0] << 32) | lo[0])) +
+           __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1]));
+}
+
+// v + v of another lane of the row by a DPP control that permutes the row.
+template <int Ctrl>
+__device__ __forceinline__ double dpp_sum(double v)
+{
+    const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)u, Ctrl, 0xf, 0xf, true);
+    const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), Ctrl, 0xf, 0xf, true);
+    return v + __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+__device__ __forceinline__ double group_sum4(const double (&r4)[kGrp / 2], int lane)   // after the first exchange
+{
+    const double r0 = dpp_sum<0x128>(swap_sum16(r4[0], r4[2]));   // row rotate by 8
+    const double r1 = dpp_sum<0x128>(swap_sum16(r4[1], r4[3]));
+    double r = (lane & 8) ? r1 : r0;
+    r = dpp_sum<0x141>(r);            // half-row mirror: lane ^ 7
+    r = dpp_sum<0x1b>(r);             // quad reverse: lane ^ 3
+    r = dpp_sum<0xb1>(r);             // neighbours: lane ^ 1
+    return r;
+}
+
 __device__ __forceinline__ double group_sum8(const double (&v)[kGrp], int lane)
 {
-    const bool u32 = (lane & 32) != 0, u16 = (lane & 16) != 0, u8 = (lane & 8) != 0;
-    double r4[4];
+    double r4[kGrp / 2];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const double keep = u32 ? v[q + 4] : v[q], send = u32 ? v[q] : v[q + 4];
-        r4[q] = keep + __shfl_xor(send, 32, kWave);
-    }
-    double r2[2];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const double keep = u16 ? r4[q + 2] : r4[q], send = u16 ? r4[q] : r4[q + 2];
-        r2[q] = keep + __shfl_xor(send, 16, kWave);
-    }
-    double r = (u8 ? r2[1] : r2[0]) + __shfl_xor(u8 ? r2[0] : r2[1], 8, kWave);
-    r += __shfl_xor(r, 4, kWave);
-    r += __shfl_xor(r, 2, kWave);
-    r += __shfl_xor(r, 1, kWave);
-    return r;
+    for (int q = 0; q < kGrp / 2; ++q) r4[q] = swap_sum32(v[q], v[q + 4]);
+    return group_sum4(r4, lane);
 }
 
 }  // namespace lif

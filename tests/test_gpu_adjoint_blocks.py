@@ -1,0 +1,76 @@
+"""The backward walk at the edges of its split: channel ranges (318 channels
+fill a workgroup's LDS block), list chunks of 1024 events, blocks of 64 events,
+groups of 8, tiles of 64 neurons; calls below and above 4096 events (the two
+fixed-point conversions); spike bursts (several spikes of a neuron within a
+group), streams so sparse that a block of 64 events spans many time constants,
+and times far from 0.  Against the oracle, with the tolerances of the other
+gradient tests (_fwd_bwd)."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+from tests.parity import compare_grad
+from tests.test_gpu_backward import _dev, _dev_fwd, _fwd_bwd, env  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,C,N,n,T,gain", [
+    (1, 1, 1, 40, 0.05, 3.0),            # one channel, one neuron, less than a block
+    (2, 318, 64, 1024, 0.2, 14.0),       # one full range, one full list chunk
+    (2, 319, 65, 1025, 0.2, 14.0),       # two ranges, a chunk and an event, a tile and a neuron
+    (3, 637, 33, 2100, 0.3, 12.0),       # three ranges, over 4096 events in all
+    (5, 700, 130, 3000, 0.4, 12.0),      # the two-layer network's channels
+    (2, 40, 70, 2500, 0.05, 60.0),       # bursts: many spikes per group of events
+])
+def test_adjoint_edges(env, B, C, N, n, T, gain):
+    cfg = W.random_small(61, B=B, C=C, N=N, n_events=n, T=T, gain=gain)
+    _fwd_bwd(env, cfg.events, cfg.layers[0].WT, 61, s_max=512, label=f"B{B} C{C} N{N} n{n} T{T}")
+
+
+# (B, C, N, n, T, gain, t0): 64 events over thousands of tau_s; a stream that
+# starts 1500 s in (references far from 0 and, in float32, many spike times
+# rounded onto or before the event just before them)
+@pytest.mark.parametrize("B,C,N,n,T,gain,t0", [(2, 12, 20, 300, 90.0, 30.0, 0.0), (2, 60, 70, 3000, 0.4, 14.0, 1500.0)])
+def test_adjoint_long_and_late(env, B, C, N, n, T, gain, t0):
+    """The backward alone, both sides on the oracle's float32 spike train: at
+    such times the train's own rounding (an ulp is 7.6e-6 s at 90 s, 1.5e-3
+    of tau_s) is above the end-to-end bound."""
+    torch, lif = env
+    cfg = W.random_small(62, B=B, C=C, N=N, n_events=n, T=T, gain=gain)
+    ev, WT = cfg.events, cfg.layers[0].WT
+    ev_t = (ev.ev_t.astype(np.float64) + t0).astype(np.float32)
+    OP = oracle.LifParams(s_max=128)
+    r32 = oracle.forward(ev_t, ev.ev_src, ev.ev_n, WT, OP).rounded()
+    g = (np.random.default_rng(62).standard_normal(r32.out_t.shape) * np.isfinite(r32.out_t)).astype(np.float32)
+    oW, oT = oracle.backward(ev_t, ev.ev_src, ev.ev_n, WT, r32, g.astype(np.float64), OP)
+    d = [_dev(torch, a) for a in (ev_t, ev.ev_src, ev.ev_n, WT)]
+    gW, gT = lif.backward(*d, _dev_fwd(torch, lif, r32), _dev(torch, g), lif.Params(s_max=128))
+    torch.cuda.synchronize()
+    sW, sT = compare_grad(gW.cpu().numpy(), oW, label="gW"), compare_grad(gT.cpu().numpy(), oT, label="gT")
+    print(f"[case] t0={t0} T={T} spikes={int(r32.out_n.sum())} rel(gW)={sW:.2e} rel(gT)={sT:.2e}", flush=True)
+
+
+@pytest.mark.parametrize("n", [500, 5000])
+def test_adjoint_not_finite(env, n):
+    """A NaN and an infinite upstream gradient on one neuron each leave every
+    other neuron's dL/dW column as it is without them."""
+    torch, lif = env
+    cfg = W.random_small(63, B=2, C=30, N=66, n_events=n, T=0.4, gain=14.0)
+    ev, WT = cfg.events, cfg.layers[0].WT
+    d = [_dev(torch, a) for a in (ev.ev_t, ev.ev_src, ev.ev_n, WT)]
+    P = lif.Params(s_max=128)
+    out = lif.forward(*d, P)
+    g = torch.randn(out.out_t.shape, generator=torch.Generator(device="cuda:0").manual_seed(1), device="cuda:0")
+    base, _ = lif.backward(*d, out, g, P)
+    fired = (out.out_n[0] > 0).nonzero().flatten().tolist()
+    h = g.clone()
+    h[0, fired[0], 0] = float("nan")
+    h[0, fired[1], 0] = float("inf")
+    got, gT = lif.backward(*d, out, h, P)
+    torch.cuda.synchronize()
+    keep = [i for i in range(66) if i not in (fired[0], fired[1])]
+    # the bound of the fixed-point scale is not the same in the two calls
+    assert torch.allclose(got[:, keep], base[:, keep], rtol=1e-5, atol=1e-6 * float(base.abs().max()))
+    assert torch.isnan(gT[0]).any()
