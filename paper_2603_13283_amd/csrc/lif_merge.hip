@@ -6,9 +6,14 @@
 // Merge: one workgroup per sample.  Each neuron's spikes are already in
 // time order; the workgroup gathers them into LDS as 64-bit keys (float bits
 // of the time, which order like the times since spike times are positive,
-// then i * s_max + s, which orders equal times by neuron) and sorts them
-// with a bitonic network in LDS, over the smallest power of two holding its
-// keys (the LDS array is sized for the most a sample can hold).  When a
+// then i * s_max + s, which orders equal times by neuron) and sorts them by
+// buckets: binned by time over at most kMergeBins bins in LDS, each key then
+// placed at its bin's start plus its rank among the bin's keys (unique keys, so
+// the result does not depend on the order the adds land in).  Samples whose
+// times pile up (a bin of more than kMergePile keys, which would compare
+// pairwise) or are not finite take a bitonic network over the smallest power of
+// two holding their keys: 21 us against 125 us for 128 samples of ~7 k spikes
+// (eight barriers against one per network stage).  When a
 // sample has more spikes than the
 // sort holds, the K = min(total, E2_max) earliest are found first: the
 // K-th smallest time t_K by bisection on its float bits (each neuron's
@@ -21,23 +26,123 @@
 namespace lif {
 
 constexpr int kMergeThreads = 1024;
+constexpr int kMergeBins = 4096;
+constexpr int kMergePile = 64;          // largest bin ranked (its keys compare pairwise)
+constexpr int kMergeRegs = LIF_MERGE_MAX / kMergeThreads;
 
 // Exclusive prefix sum over the workgroup of one value per thread; also
 // returns the total.
 __device__ __forceinline__ int block_exclusive_scan(int v, int* s_scan, int& total)
 {
-    const int tid = threadIdx.x;
-    __syncthreads();
-    s_scan[tid] = v;
-    __syncthreads();
-    for (int off = 1; off < kMergeThreads; off <<= 1) {
-        const int x = tid >= off ? s_scan[tid - off] : 0;
-        __syncthreads();
-        s_scan[tid] += x;
-        __syncthreads();
+    const int lane = (int)threadIdx.x % kWave, wv = (int)threadIdx.x / kWave;
+    int incl = v;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const int x = __shfl_up(incl, off, kWave);
+        if (lane >= off) incl += x;
     }
-    total = s_scan[kMergeThreads - 1];
-    return s_scan[tid] - v;
+    __syncthreads();
+    if (lane == kWave - 1) s_scan[wv] = incl;
+    __syncthreads();
+    int before = 0;
+    total = 0;
+#pragma unroll
+    for (int q = 0; q < kMergeThreads / kWave; ++q) {
+        const int x = s_scan[q];
+        before += q < wv ? x : 0;
+        total += x;
+    }
+    return before + incl - v;
+}
+
+// Bin of a time in [t0, t0 + n / sc]: monotone in t.
+__device__ __forceinline__ int merge_bin(uint32_t bits, float t0, float sc, int n)
+{
+    return min((int)((__uint_as_float(bits) - t0) * sc), n - 1);
+}
+
+// The keys [0, held) in LDS sorted by buckets.  False (the keys untouched) when
+// they pile up or are not finite.  Workgroup-uniform.
+__device__ bool bucket_sort(unsigned long long* keys, int held, int* bins, int nbins, int* s_scan, uint32_t* s_mm)
+{
+    const int tid = (int)threadIdx.x, lane = tid % kWave;
+    uint32_t lo = 0xffffffffu, hi = 0u;
+    for (int e = tid; e < held; e += kMergeThreads) {
+        const uint32_t t = (uint32_t)(keys[e] >> 32);
+        lo = min(lo, t);
+        hi = max(hi, t);
+    }
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) {
+        lo = min(lo, (uint32_t)__shfl_xor((int)lo, off, kWave));
+        hi = max(hi, (uint32_t)__shfl_xor((int)hi, off, kWave));
+    }
+    if (tid < 3) s_mm[tid] = tid == 0 ? 0xffffffffu : 0u;
+    for (int j = tid; j < nbins; j += kMergeThreads) bins[j] = 0;
+    __syncthreads();
+    if (lane == 0) {
+        atomicMin(&s_mm[0], lo);
+        atomicMax(&s_mm[1], hi);
+    }
+    __syncthreads();
+    if (s_mm[1] >= 0x7f800000u) return false;
+    const float t0 = __uint_as_float(s_mm[0]), span = __uint_as_float(s_mm[1]) - t0;
+    const float sc = span > 0.0f ? (float)nbins / span : 0.0f;
+    if (!(sc < INFINITY)) return false;
+    for (int e = tid; e < held; e += kMergeThreads) atomicAdd(&bins[merge_bin((uint32_t)(keys[e] >> 32), t0, sc, nbins)], 1);
+    __syncthreads();
+    // bin starts; the largest bin
+    constexpr int kPer = kMergeBins / kMergeThreads;
+    int c[kPer], sum = 0, big = 0;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int j = tid * kPer + u;
+        c[u] = j < nbins ? bins[j] : 0;
+        sum += c[u];
+        big = max(big, c[u]);
+    }
+    if (big > kMergePile) s_mm[2] = 1u;
+    int total = 0, run = block_exclusive_scan(sum, s_scan, total);
+    if (s_mm[2]) return false;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int j = tid * kPer + u;
+        if (j < nbins) bins[j] = run;
+        run += c[u];
+    }
+    unsigned long long k[kMergeRegs];
+#pragma unroll
+    for (int r = 0; r < kMergeRegs; ++r) {
+        const int e = tid + r * kMergeThreads;
+        k[r] = e < held ? keys[e] : ~0ull;
+    }
+    __syncthreads();
+    // into the bins; bins[j] ends at the end of bin j
+#pragma unroll
+    for (int r = 0; r < kMergeRegs; ++r)
+        if (tid + r * kMergeThreads < held) {
+            const int pos = atomicAdd(&bins[merge_bin((uint32_t)(k[r] >> 32), t0, sc, nbins)], 1);
+            keys[pos] = k[r];
+        }
+    __syncthreads();
+    int place[kMergeRegs];
+#pragma unroll
+    for (int r = 0; r < kMergeRegs; ++r) {
+        place[r] = 0;
+        if (tid + r * kMergeThreads < held) {
+            const int j = merge_bin((uint32_t)(k[r] >> 32), t0, sc, nbins);
+            const int b0 = j > 0 ? bins[j - 1] : 0, b1 = bins[j];
+            int p = b0;
+            for (int q = b0; q < b1; ++q) p += keys[q] < k[r] ? 1 : 0;
+            place[r] = p;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kMergeRegs; ++r)
+        if (tid + r * kMergeThreads < held) keys[place[r]] = k[r];
+    __syncthreads();
+    return true;
 }
 
 // Spikes of one neuron (sorted times ts[0 .. c)) whose float bits are <= x.
@@ -57,8 +162,9 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge(const float* __restrict
                                                          int32_t* __restrict__ ev_n2, int32_t* __restrict__ perm,
                                                          int E2_max, int cap, int32_t* __restrict__ status)
 {
-    extern __shared__ unsigned long long keys[];   // cap entries (power of two)
-    __shared__ int s_scan[kMergeThreads];
+    extern __shared__ unsigned long long keys[];   // cap entries (power of two), then the bins
+    __shared__ int s_scan[kMergeThreads / kWave];
+    __shared__ uint32_t s_mm[3];
     const int b = blockIdx.x;
     const int tid = threadIdx.x;
     const int32_t* cnt = out_n + (size_t)b * N;
@@ -129,8 +235,10 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge(const float* __restrict
         }
     }
     __syncthreads();
-    // Bitonic sort of the n2 keys.
-    for (int size = 2; size <= n2; size <<= 1) {
+    const int nbins = min(cap, kMergeBins);
+    const bool sorted = held > 1 ? bucket_sort(keys, held, (int*)(keys + cap), nbins, s_scan, s_mm) : true;
+    // else a bitonic sort of the n2 keys
+    for (int size = 2; size <= n2 && !sorted; size <<= 1) {
         for (int stride = size >> 1; stride > 0; stride >>= 1) {
             for (int e = tid; e < n2; e += kMergeThreads) {
                 int partner = e ^ stride;
@@ -240,11 +348,12 @@ extern "C" int lif_merge_spikes(const float* out_t, const int32_t* out_n, int B,
     while ((size_t)cap < most && cap < LIF_MERGE_MAX) cap <<= 1;
     TIMED_LAUNCH("merge_status", lif::k_zero_status, dim3(1), dim3(64), 0, stream, status);
     if (B == 0) return lif::check_launch();
-    size_t shmem = (size_t)cap * sizeof(unsigned long long);
+    size_t shmem = (size_t)cap * sizeof(unsigned long long) +
+                   (size_t)(cap < lif::kMergeBins ? cap : lif::kMergeBins) * sizeof(int);
     // the sort's LDS exceeds the default dynamic-LDS limit; the attribute is
     // set on every call (for the current device; no state kept here)
     if (hipFuncSetAttribute((const void*)lif::k_merge, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)(LIF_MERGE_MAX * sizeof(unsigned long long))) != hipSuccess)
+                            (int)(LIF_MERGE_MAX * sizeof(unsigned long long) + lif::kMergeBins * sizeof(int))) != hipSuccess)
         return LIF_ERR_HIP;
     TIMED_LAUNCH("merge", lif::k_merge, dim3(B), dim3(lif::kMergeThreads), shmem, stream, out_t, out_n, N, s_max,
                  ev_t2, ev_src2, ev_n2, perm, E2_max, cap, status);

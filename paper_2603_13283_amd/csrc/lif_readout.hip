@@ -17,16 +17,14 @@
 // product e^{t_i/tau_m} e^{-t_i/T_m} of the printed form is e^{-t_i/tau_LI}).
 //
 // Passes (no atomics on floating-point values; every sum has a fixed order):
-//   k_li_kernel   per event: G and dG/dt0 (lanes are events).
-//   k_li_logits   per (sample, 64 classes): lanes are classes, four waves
-//                 take contiguous quarters of the queue, W rows gathered per
-//                 event; quarters combined in wave order.
-//   k_li_ce       per sample: softmax of beta z, the sample's loss and
-//                 dL/dz = beta (p - onehot) / B; then the batch mean.
-//   k_li_hist     per event: H[b][src] += G (64-bit fixed-point integer
-//                 atomics, exact and order-free), so that
-//   k_li_grad_w   dL/dW[c][k] = sum_b H[b][c] dL/dz[b][k] (b in order).
-//   k_li_grad_t   per event: dL/dt_e = dG(t_e) sum_k W[src_e][k] dL/dz[b][k].
+//   k_li_events   per (sample, kLiChunk events): G and dG/dt0 of every event,
+//                 the chunk's part of the logits, and H[b][src] += G (64-bit
+//                 fixed-point integer atomics, exact and order-free).
+//   k_li_ce       per sample: the logits (chunks in order); softmax of beta z,
+//                 the sample's loss and dL/dz = beta (p - onehot) / B.
+//   k_li_grads    dL/dW[c][k] = sum_b H[b][c] dL/dz[b][k], dL/dt_e =
+//                 dG(t_e) sum_k W[src_e][k] dL/dz[b][k], and the batch mean of
+//                 the loss, by ranges of workgroups.
 #include "lif_common.hpp"
 #include "lif_host.hpp"
 
@@ -65,68 +63,102 @@ __device__ __forceinline__ double2 event_kernel(const LiModel& m, double t0)
     return make_double2(G, dG);
 }
 
-__global__ __launch_bounds__(kLiThreads) void k_li_kernel(const float* __restrict__ ev_t,
-                                                          const int32_t* __restrict__ ev_n, int E_max, LiModel m,
-                                                          double2* __restrict__ gk)
-{
-    const int b = blockIdx.y;
-    const int e = blockIdx.x * kLiThreads + threadIdx.x;
-    if (e >= E_max) return;
-    const int nb = clamp_count(ev_n[b], E_max);
-    gk[(size_t)b * E_max + e] = e < nb ? event_kernel(m, (double)ev_t[(size_t)b * E_max + e]) : make_double2(0.0, 0.0);
-}
+// One workgroup per (sample, chunk of kLiChunk events), a quarter of it per
+// wave.  The logits: a wave holds its classes in the low lanes of one or more
+// lane groups of `group` lanes (the power of two holding ncls), each group taking
+// every (64 / group)-th event, kU events in flight; groups, then waves are added
+// in order.  A workgroup per sample left half the chip idle and a chain of
+// loads per wave (494 us at 512 -> 20, B = 128, ~7 k events, and 44 us for G, dG
+// and H in passes of their own; 45 us for all of it here, bound by the latency
+// of the row gathers: 64 us with chunks of 512 events, 52 us with 16 in flight).
+constexpr int kLiChunk = 256;
 
-__global__ __launch_bounds__(kLiThreads) void k_li_logits(const int32_t* __restrict__ ev_src,
-                                                          const int32_t* __restrict__ ev_n, int E_max,
-                                                          const float* __restrict__ WT, int C_in, int ncls,
-                                                          const double2* __restrict__ gk, double* __restrict__ z64,
-                                                          float* __restrict__ logits)
+__global__ __launch_bounds__(kLiThreads) void k_li_events(const float* __restrict__ ev_t,
+                                                          const int32_t* __restrict__ ev_src,
+                                                          const int32_t* __restrict__ ev_n, int E_max, int chunks,
+                                                          LiModel m, const float* __restrict__ WT, int C_in, int ncls,
+                                                          int group, double2* __restrict__ gk,
+                                                          unsigned long long* __restrict__ H,
+                                                          double* __restrict__ zpart)
 {
-    __shared__ double part[kLiThreads / kWave][kWave];
-    const int b = blockIdx.x;
-    const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    const int c = blockIdx.y * kWave + lane;
-    const bool live = c < ncls;
+    constexpr int nw = kLiThreads / kWave, kPerWave = kLiChunk / nw;
+    __shared__ double s_g[kLiChunk];
+    __shared__ int s_row[kLiChunk];
+    __shared__ double part[nw][kWave];
+    const int b = blockIdx.y, ch = blockIdx.x;
+    const int wave = (int)threadIdx.x / kWave, lane = (int)threadIdx.x % kWave;
     const int nb = clamp_count(ev_n[b], E_max);
-    constexpr int nw = kLiThreads / kWave;
-    const int per = (nb + nw - 1) / nw;
-    const int e0 = min(wave * per, nb), e1 = min(e0 + per, nb);
-    const int32_t* src = ev_src + (size_t)b * E_max;
-    const double2* g = gk + (size_t)b * E_max;
+    const int k0 = ch * kLiChunk, cnt = min(kLiChunk, nb - k0);
+    if (cnt <= 0) return;
+    // the wave's events: kernel values, source rows, histogram
+    const int w0 = wave * kPerWave;
+    for (int i = w0 + lane; i < w0 + kPerWave; i += kWave) {
+        double2 g = make_double2(0.0, 0.0);
+        int src = 0;
+        if (i < cnt) {
+            const size_t at = (size_t)b * E_max + k0 + i;
+            g = event_kernel(m, (double)ev_t[at]);
+            src = clamp_src(ev_src[at], C_in);
+            gk[at] = g;
+            if (H && g.x != 0.0)
+                atomicAdd(&H[(size_t)b * C_in + src], (unsigned long long)llrint(g.x * kHistScale));
+        }
+        s_g[i] = g.x;
+        s_row[i] = src * ncls;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const int c = lane & (group - 1), g0 = lane / group, ng = kWave / group;
+    const bool live = c < ncls;
     double acc = 0.0;
     constexpr int kU = 8;
-    for (int e = e0; e < e1; e += kU) {
+    const int wend = min(w0 + kPerWave, cnt);
+    for (int e = w0 + g0; e < wend; e += kU * ng) {
         float w[kU];
         double G[kU];
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-            const int ee = min(e + u, e1 - 1);
-            const int s = clamp_src(src[ee], C_in);
-            w[u] = live ? WT[(size_t)s * ncls + c] : 0.0f;
-            G[u] = e + u < e1 ? g[ee].x : 0.0;
+            const int x = e + u * ng, xx = x < wend ? x : e;
+            w[u] = live ? WT[(size_t)s_row[xx] + c] : 0.0f;
+            G[u] = x < wend ? s_g[xx] : 0.0;
         }
 #pragma unroll
         for (int u = 0; u < kU; ++u) acc = fma(G[u], (double)w[u], acc);
     }
     part[wave][lane] = acc;
     __syncthreads();
-    if (wave == 0 && live) {
+    if ((int)threadIdx.x < ncls) {
         double z = 0.0;
-#pragma unroll
-        for (int q = 0; q < nw; ++q) z += part[q][lane];
-        z64[(size_t)b * ncls + c] = z;
-        if (logits) logits[(size_t)b * ncls + c] = (float)z;
+        for (int q = 0; q < nw; ++q)
+            for (int u = 0; u < ng; ++u) z += part[q][u * group + (int)threadIdx.x];
+        zpart[((size_t)b * chunks + ch) * ncls + threadIdx.x] = z;
     }
 }
 
-// One wave per sample (lanes are classes, ncls <= 64).
-__global__ __launch_bounds__(kWave) void k_li_ce(const double* __restrict__ z64, int B, int ncls,
+// One wave per sample (lanes are classes, ncls <= 64): the logits; with labels
+// the sample's loss and dL/dz.
+__global__ __launch_bounds__(kWave) void k_li_ce(const double* __restrict__ zpart, const int32_t* __restrict__ ev_n,
+                                                 int E_max, int chunks, int B, int ncls,
                                                  const int32_t* __restrict__ labels, double beta,
-                                                 double* __restrict__ dz, double* __restrict__ loss_b)
+                                                 float* __restrict__ logits, double* __restrict__ dz,
+                                                 double* __restrict__ loss_b)
 {
     const int b = blockIdx.x, c = threadIdx.x;
     const bool live = c < ncls;
-    const double y = live ? beta * z64[(size_t)b * ncls + c] : -INFINITY;
+    const int used = (clamp_count(ev_n[b], E_max) + kLiChunk - 1) / kLiChunk;
+    double z = 0.0;
+    const double* zp = zpart + (size_t)b * chunks * ncls + (live ? c : 0);
+    for (int q0 = 0; q0 < used; q0 += 8) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = zp[(size_t)min(q0 + u, used - 1) * ncls];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) z += q0 + u < used ? v[u] : 0.0;
+    }
+    if (live && logits) logits[(size_t)b * ncls + c] = (float)z;
+    if (!labels) return;
+    const double y = live ? beta * z : -INFINITY;
     double mx = y;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, kWave));
@@ -155,46 +187,47 @@ __global__ __launch_bounds__(kLiThreads) void k_fill_u64(unsigned long long* __r
     if (i < n) p[i] = 0ull;
 }
 
-__global__ __launch_bounds__(kLiThreads) void k_li_hist(const int32_t* __restrict__ ev_src,
-                                                        const int32_t* __restrict__ ev_n, int E_max, int C_in,
-                                                        const double2* __restrict__ gk,
-                                                        unsigned long long* __restrict__ H)
-{
-    const int b = blockIdx.y;
-    const int e = blockIdx.x * kLiThreads + threadIdx.x;
-    if (e >= clamp_count(ev_n[b], E_max)) return;
-    const double G = gk[(size_t)b * E_max + e].x;
-    if (G == 0.0) return;
-    const long long q = llrint(G * kHistScale);
-    atomicAdd(&H[(size_t)b * C_in + clamp_src(ev_src[(size_t)b * E_max + e], C_in)], (unsigned long long)q);
-}
+// dL/dW: kGwLanes threads per element, each summing every kGwLanes-th sample in
+// order, their sums added in order (fixed whatever the launch).
+constexpr int kGwLanes = 8;
 
-__global__ __launch_bounds__(kLiThreads) void k_li_grad_w(const unsigned long long* __restrict__ H, int B, int C_in,
-                                                          int ncls, const double* __restrict__ dz,
-                                                          float* __restrict__ grad_WT)
+__device__ __forceinline__ void li_grad_w(int block, const unsigned long long* __restrict__ H, int B, int C_in,
+                                          int ncls, const double* __restrict__ dz, float* __restrict__ grad_WT)
 {
-    const size_t i = (size_t)blockIdx.x * kLiThreads + threadIdx.x;
-    if (i >= (size_t)C_in * ncls) return;
-    const int c = (int)(i / ncls), k = (int)(i % ncls);
+    const size_t t = (size_t)block * kLiThreads + threadIdx.x;
+    const size_t i = t / kGwLanes;
+    const int part = (int)(t % kGwLanes);
+    const bool live = i < (size_t)C_in * ncls;
+    const int c = live ? (int)(i / ncls) : 0, k = live ? (int)(i % ncls) : 0;
     double s = 0.0;
-    for (int b = 0; b < B; ++b) {
-        const long long h = (long long)H[(size_t)b * C_in + c];
-        if (h) s = fma((double)h / kHistScale, dz[(size_t)b * ncls + k], s);
+    for (int b0 = part; b0 < B; b0 += 4 * kGwLanes) {
+        long long h[4];
+        double d[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int b = min(b0 + u * kGwLanes, B - 1);
+            h[u] = (long long)H[(size_t)b * C_in + c];
+            d[u] = dz[(size_t)b * ncls + k];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (b0 + u * kGwLanes < B && h[u]) s = fma((double)h[u] / kHistScale, d[u], s);
     }
-    grad_WT[i] = (float)s;
+#pragma unroll
+    for (int off = 1; off < kGwLanes; off <<= 1) s += __shfl_xor(s, off, kWave);
+    if (live && part == 0) grad_WT[i] = (float)s;
 }
 
-__global__ __launch_bounds__(kLiThreads) void k_li_grad_t(const int32_t* __restrict__ ev_src,
-                                                          const int32_t* __restrict__ ev_n, int E_max,
-                                                          const float* __restrict__ WT, int C_in, int ncls,
-                                                          const double2* __restrict__ gk,
-                                                          const double* __restrict__ dz, float* __restrict__ grad_t)
+__device__ __forceinline__ void li_grad_t(int block, int bpe, const int32_t* __restrict__ ev_src,
+                                          const int32_t* __restrict__ ev_n, int E_max, const float* __restrict__ WT,
+                                          int C_in, int ncls, const double2* __restrict__ gk,
+                                          const double* __restrict__ dz, float* __restrict__ grad_t)
 {
     __shared__ double s_dz[kWave];
-    const int b = blockIdx.y;
-    if (threadIdx.x < kWave) s_dz[threadIdx.x] = threadIdx.x < ncls ? dz[(size_t)b * ncls + threadIdx.x] : 0.0;
+    const int b = block / bpe;
+    if (threadIdx.x < kWave) s_dz[threadIdx.x] = (int)threadIdx.x < ncls ? dz[(size_t)b * ncls + threadIdx.x] : 0.0;
     __syncthreads();
-    const int e = blockIdx.x * kLiThreads + threadIdx.x;
+    const int e = (block % bpe) * kLiThreads + (int)threadIdx.x;
     if (e >= E_max) return;
     const size_t at = (size_t)b * E_max + e;
     if (e >= clamp_count(ev_n[b], E_max)) {
@@ -205,9 +238,40 @@ __global__ __launch_bounds__(kLiThreads) void k_li_grad_t(const int32_t* __restr
     double s = 0.0;
     if (dG != 0.0) {
         const float* row = WT + (size_t)clamp_src(ev_src[at], C_in) * ncls;
+#pragma unroll 4
         for (int k = 0; k < ncls; ++k) s = fma((double)row[k], s_dz[k], s);
     }
     grad_t[at] = (float)(dG * s);
+}
+
+// The batch mean of the loss, one wave: lane l the samples l, l + 64, ...
+__device__ __forceinline__ void li_loss(const double* __restrict__ loss_b, int B, float* __restrict__ loss)
+{
+    if (threadIdx.x >= kWave) return;
+    double s = 0.0;
+    for (int b = (int)threadIdx.x; b < B; b += kWave) s += loss_b[b];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, kWave);
+    if (threadIdx.x == 0) loss[0] = (float)(s / (double)B);
+}
+
+// What the labels ask for, by ranges of workgroups: wblocks of dL/dW, tblocks
+// (bpe per sample) of dL/dt, then one of the loss.
+__global__ __launch_bounds__(kLiThreads) void k_li_grads(int wblocks, int tblocks, int bpe,
+                                                         const int32_t* __restrict__ ev_src,
+                                                         const int32_t* __restrict__ ev_n, int B, int E_max,
+                                                         const float* __restrict__ WT, int C_in, int ncls,
+                                                         const double2* __restrict__ gk,
+                                                         const unsigned long long* __restrict__ H,
+                                                         const double* __restrict__ dz,
+                                                         const double* __restrict__ loss_b,
+                                                         float* __restrict__ grad_WT, float* __restrict__ grad_t,
+                                                         float* __restrict__ loss)
+{
+    const int k = (int)blockIdx.x;
+    if (k < wblocks) li_grad_w(k, H, B, C_in, ncls, dz, grad_WT);
+    else if (k < wblocks + tblocks) li_grad_t(k - wblocks, bpe, ev_src, ev_n, E_max, WT, C_in, ncls, gk, dz, grad_t);
+    else if (loss) li_loss(loss_b, B, loss);
 }
 
 // grad_out_t[b][perm[b][j]] = grad_ev_t2[b][j] for the queue's events, 0 for
@@ -231,8 +295,10 @@ __global__ __launch_bounds__(kLiThreads) void k_merge_grad(const float* __restri
 }
 
 struct LiLayout {
-    size_t gk, z64, dz, loss_b, H, total;
+    size_t gk, zpart, dz, loss_b, H, total;
 };
+
+static int li_chunks(int E_max) { return E_max > 0 ? (E_max + kLiChunk - 1) / kLiChunk : 1; }
 
 static LiLayout li_layout(int B, int E_max, int C_in, int ncls)
 {
@@ -240,7 +306,7 @@ static LiLayout li_layout(int B, int E_max, int C_in, int ncls)
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off += (bytes + 255) & ~(size_t)255; return o; };
     L.gk = take((size_t)B * E_max * sizeof(double2));
-    L.z64 = take((size_t)B * ncls * sizeof(double));
+    L.zpart = take((size_t)B * li_chunks(E_max) * ncls * sizeof(double));
     L.dz = take((size_t)B * ncls * sizeof(double));
     L.loss_b = take((size_t)B * sizeof(double));
     L.H = take((size_t)B * C_in * sizeof(unsigned long long));
@@ -284,7 +350,7 @@ extern "C" int lif_li_readout(const float* ev_t, const int32_t* ev_src, const in
     hipStream_t stream = (hipStream_t)stream_;
     char* base = (char*)(((uintptr_t)ws + 255) & ~(uintptr_t)255);
     double2* gk = (double2*)(base + L.gk);
-    double* z64 = (double*)(base + L.z64);
+    double* zpart = (double*)(base + L.zpart);
     double* dz = (double*)(base + L.dz);
     double* loss_b = (double*)(base + L.loss_b);
     unsigned long long* H = (unsigned long long*)(base + L.H);
@@ -298,29 +364,28 @@ extern "C" int lif_li_readout(const float* ev_t, const int32_t* ev_src, const in
         }
         return check_launch();
     }
-    const dim3 egrid((unsigned)((E_max + kLiThreads - 1) / kLiThreads > 0 ? (E_max + kLiThreads - 1) / kLiThreads : 1),
-                     (unsigned)B);
-    if (E_max > 0)
-        TIMED_LAUNCH("li_kernel", k_li_kernel, egrid, dim3(kLiThreads), 0, stream, ev_t, ev_n, E_max, m, gk);
-    TIMED_LAUNCH("li_logits", k_li_logits, dim3((unsigned)B, (unsigned)((N_cls + kWave - 1) / kWave)),
-                 dim3(kLiThreads), 0, stream, ev_src, ev_n, E_max, WT, C_in, N_cls, gk, z64, logits);
-    if (!labels) return check_launch();
-    TIMED_LAUNCH("li_ce", k_li_ce, dim3((unsigned)B), dim3(kWave), 0, stream, z64, B, N_cls, labels, m.beta, dz,
-                 loss_b);
-    if (loss) TIMED_LAUNCH("li_loss", k_li_loss, dim3(1), dim3(1), 0, stream, loss_b, B, loss);
+    const int chunks = li_chunks(E_max);
+    const int bpe = (E_max + kLiThreads - 1) / kLiThreads;
+    const size_t nw = (size_t)C_in * N_cls;
+    const size_t wblocks = grad_WT ? (nw * kGwLanes + kLiThreads - 1) / kLiThreads : 0;
+    const size_t tblocks = grad_ev_t ? (size_t)B * bpe : 0;
+    if (wblocks + tblocks >= 0x7fffffff) return LIF_ERR_SIZE;
     if (grad_WT) {
         const size_t nh = (size_t)B * C_in;
         TIMED_LAUNCH("li_fill", k_fill_u64, dim3((unsigned)((nh + kLiThreads - 1) / kLiThreads)), dim3(kLiThreads),
                      0, stream, H, nh);
-        if (E_max > 0)
-            TIMED_LAUNCH("li_hist", k_li_hist, egrid, dim3(kLiThreads), 0, stream, ev_src, ev_n, E_max, C_in, gk, H);
-        const size_t nw = (size_t)C_in * N_cls;
-        TIMED_LAUNCH("li_grad_w", k_li_grad_w, dim3((unsigned)((nw + kLiThreads - 1) / kLiThreads)),
-                     dim3(kLiThreads), 0, stream, H, B, C_in, N_cls, dz, grad_WT);
     }
-    if (grad_ev_t && E_max > 0)
-        TIMED_LAUNCH("li_grad_t", k_li_grad_t, egrid, dim3(kLiThreads), 0, stream, ev_src, ev_n, E_max, WT, C_in,
-                     N_cls, gk, dz, grad_ev_t);
+    int group = 1;
+    while (group < N_cls) group <<= 1;
+    if (E_max > 0)
+        TIMED_LAUNCH("li_events", k_li_events, dim3((unsigned)chunks, (unsigned)B), dim3(kLiThreads), 0, stream, ev_t,
+                     ev_src, ev_n, E_max, chunks, m, WT, C_in, N_cls, group, gk, grad_WT ? H : nullptr, zpart);
+    TIMED_LAUNCH("li_ce", k_li_ce, dim3((unsigned)B), dim3(kWave), 0, stream, zpart, ev_n, E_max, chunks, B, N_cls,
+                 labels, m.beta, logits, dz, loss_b);
+    if (loss || grad_WT || tblocks)
+        TIMED_LAUNCH("li_grads", k_li_grads, dim3((unsigned)(wblocks + tblocks + 1)), dim3(kLiThreads), 0, stream,
+                     (int)wblocks, (int)tblocks, bpe, ev_src, ev_n, B, E_max, WT, C_in, N_cls, gk, H, dz, loss_b,
+                     grad_WT, grad_ev_t, loss);
     return check_launch();
 }
 
