@@ -40,7 +40,7 @@ def log(*a):
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_forward_700x256_b32.txt")
 L2_FILE = os.path.join(ROOT, "profiles", "l2_forward_700x256_b32.txt")
-KERNEL_SOURCES = ("lif_forward.hip", "lif_common.hpp", "lif_host.hpp", "lif_walk.hpp")
+KERNEL_SOURCES = ("lif_forward.hip", "lif_ring.hpp", "lif_common.hpp", "lif_host.hpp", "lif_walk.hpp")
 
 
 def kernel_sources_sha256() -> str:

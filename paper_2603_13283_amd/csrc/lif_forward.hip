@@ -23,18 +23,19 @@
 //                events whose no-reset trajectory passes every screen holds
 //                no spike whatever happened before it; a flagged sub-block
 //                reserves a pool entry and stores its entering state there.
-//   k_resolve    per (sample, neuron) with flagged sub-blocks: walks only
-//                those, in time order.  Staging waves walk each flagged
-//                sub-block from its entering state (the no-reset state at
-//                every interval start) and compute each interval's crossing
-//                key, filling a ring of LDS windows ahead of the chain wave.
-//                Spikes found so far lower V by a known decaying amount (the
-//                reset deficit), which corrects the no-reset states exactly;
-//                an interval crosses iff its key is at least the deficit's
-//                current key (the interval rule of Sec. 3.2.2, one compare
-//                per interval).  The spike time is solved by bracketed Newton
-//                (Appendix D.1), V is hard-reset and the same interval is
-//                tested again from the spike (Appendix E.2).
+//   k_resolve    per (sample, neuron) with flagged sub-blocks, one wave: walks
+//                only those, in time order, passing over every sub-block whose
+//                key bound (stored by the check pass) lies below the key of
+//                the current reset deficit.  The wave rebuilds the no-reset
+//                state at every interval start of four sub-blocks at a time
+//                and computes each interval's crossing key.  Spikes found so
+//                far lower V by a known decaying amount (the reset deficit),
+//                which corrects the no-reset states exactly; an interval
+//                crosses iff its key is at least the deficit's current key
+//                (the interval rule of Sec. 3.2.2, one compare per interval).
+//                The spike time is solved by bracketed Newton (Appendix D.1),
+//                V is hard-reset and the same interval is tested again from
+//                the spike (Appendix E.2).
 // The sequential baseline k_sequential (Appendix E.3) runs the same interval
 // rule and root solve one event at a time per (sample, neuron).
 #include "lif_common.hpp"
@@ -69,9 +70,18 @@ __device__ __forceinline__ double crossing_key(const Model& m, double crit, doub
     return log(crit) + t0 * m.inv_tm;
 }
 
-// A wait inside a workgroup that does not end within this many polls is an
-// internal error (reported in the status words instead of waiting for ever).
-constexpr int kSpinLimit = 1 << 22;
+// Upper bound, as a float, of the crossing keys of a sub-block's intervals from
+// the largest value z of its screens (V / kappa; screen_value) and its last
+// event's time: an interval's crit is at most V_lin's tangent bound minus th, so
+// key <= ln(kappa z - th) + t_last / tm.  The margins cover the hardware
+// logarithm, the rounding to float and the rounding of the interval states
+// (the 1e-9 of th_lo).  Below the deficit's key, none of the intervals crosses.
+__device__ __forceinline__ float key_bound(const Model& m, double z, double t_last)
+{
+    const double x = fmax(fma(m.kappa, z, -m.th), 0.0) + 1e-9 * fmax(1.0, m.th);
+    const float f = (float)((double)__logf((float)x) + 1e-5 + t_last * m.inv_tm);
+    return f + fabsf(f) * 0x1p-22f;
+}
 
 // Per-sample counters (pool use, work-list length) each take their
 // own 128-byte line: many waves update them with atomics, and atomics on one
@@ -211,7 +221,7 @@ __global__ __launch_bounds__(kWave * kWalkWaves) void k_aggregate(
     Decay* __restrict__ dec, double2* __restrict__ segm, double2* __restrict__ agg, int32_t* __restrict__ status,
     uint32_t* __restrict__ counters, size_t n_counters, uint32_t* __restrict__ listed, size_t nn,
     int32_t* __restrict__ out_n, float* __restrict__ out_t, float* __restrict__ out_i, int32_t* __restrict__ out_k,
-    size_t n_out)
+    size_t n_out, int tmB)
 {
     {
         // resets for the later passes: status words, per-sample counters,
@@ -234,7 +244,7 @@ __global__ __launch_bounds__(kWave * kWalkWaves) void k_aggregate(
     }
     __shared__ double2 s_ad[kWalkWaves][kSeg];
     WalkCoords c;
-    if (!walk_coords<NPL>(items, tiles, S, ev_n, E_max, N, c)) return;
+    if (!walk_coords<NPL>(items, tiles, S, ev_n, E_max, N, c, tmB)) return;
     double2* lad = s_ad[threadIdx.x / kWave];
     // the decays of the segment's events (identity past the sample's last
     // event); the first tile's wave stores them, and the segment's composed
@@ -255,8 +265,7 @@ __global__ __launch_bounds__(kWave * kWalkWaves) void k_aggregate(
             segm[(size_t)c.b * S + c.seg] = make_double2(exp(-T * m.inv_tm), exp(-T * m.inv_ts));
         }
     }
-    const Stage st = stage_segment(c, ev_src + (size_t)c.b * E_max + c.k0, nullptr, WT, C_in, N, lad, nullptr,
-                                   nullptr);
+    const Stage st = stage_segment(c, ev_src + (size_t)c.b * E_max + c.k0, nullptr, WT, C_in, N, lad, nullptr);
     double U[NPL], J[NPL];
 #pragma unroll
     for (int i = 0; i < NPL; ++i) U[i] = J[i] = 0.0;
@@ -354,58 +363,32 @@ __global__ __launch_bounds__(kWave * kCarryWaves) void k_carry(
     }
 }
 
-// Screen of one group of intervals.  The coarse test bounds every interval
-// of the group at once: with X = U - J at each interval start, the largest X
-// and J over the group and the group's largest slope glk,
-//   max_j [X_j + max(J_j - th, 0) lk_j] <= max X + max(max J - th, 0) glk,
-// so a group that fails it holds no interval that passes screen_value.  The
-// (rare) groups that pass are walked again from their entering state with
-// the exact per-interval screen.  Returns the largest exact screen value
-// (-inf when the coarse test rejects the group for every lane).
+// Screen of one group of intervals on the walk itself: z takes the largest
+// screen_value.  (A coarse bound per group first, with a second walk of the
+// groups that pass it, costs 6 instead of 8 float64 operations per
+// neuron-event, but of a layer that fires nearly every group passes for some
+// lane: VALU-bound at 21 instructions, 2.44 ms at 32768 -> 2048, B = 16, 100 k
+// events.)
 template <int NPL>
 __device__ __forceinline__ void screen_grp(const Model& m, const double2* __restrict__ lad,
-                                           const double* __restrict__ llk, double glk, int e0, int n,
+                                           const double* __restrict__ llk, int e0, int n,
                                            const float (&w)[kGrp][NPL], double (&U)[NPL], double (&J)[NPL],
                                            double (&z)[NPL])
 {
-    double Ug[NPL], Jg[NPL], xm[NPL], jm[NPL];
-#pragma unroll
-    for (int i = 0; i < NPL; ++i) {
-        Ug[i] = U[i];
-        Jg[i] = J[i];
-        xm[i] = -INFINITY;
-        jm[i] = -INFINITY;
-    }
-    auto track = [&](int j) {
+    auto take = [&](int j) {
+        const double lk = llk[e0 + j];
         const double2 ad = lad[e0 + j];
 #pragma unroll
-        for (int i = 0; i < NPL; ++i) {
-            xm[i] = fmax(xm[i], U[i] - J[i]);
-            jm[i] = fmax(jm[i], J[i]);
-        }
+        for (int i = 0; i < NPL; ++i) z[i] = fmax(z[i], screen_value(m, U[i], J[i], lk));
         step<NPL>(ad.x, ad.y, w[j], U, J);
     };
     if (n >= kGrp) {
 #pragma unroll
-        for (int j = 0; j < kGrp; ++j) track(j);
+        for (int j = 0; j < kGrp; ++j) take(j);
     } else {
 #pragma unroll
         for (int j = 0; j < kGrp; ++j)
-            if (j < n) track(j);
-    }
-    bool pass = false;
-#pragma unroll
-    for (int i = 0; i < NPL; ++i) pass |= fma(fmax(jm[i] - m.th, 0.0), glk, xm[i]) >= m.thk_lo;
-    if (__ballot(pass) == 0ull) return;
-#pragma unroll
-    for (int j = 0; j < kGrp; ++j) {
-        if (j < n) {
-            const double lk = llk[e0 + j];
-            const double2 ad = lad[e0 + j];
-#pragma unroll
-            for (int i = 0; i < NPL; ++i) z[i] = fmax(z[i], screen_value(m, Ug[i], Jg[i], lk));
-            step<NPL>(ad.x, ad.y, w[j], Ug, Jg);
-        }
+            if (j < n) take(j);
     }
 }
 
@@ -424,30 +407,33 @@ __device__ __forceinline__ void screen_grp(const Model& m, const double2* __rest
 // rebuilds that sub-block's entering state from the segment's carried
 // state).  The wave writes the entering states; the first segment to flag a
 // neuron appends it to the sample's work list.
+template <bool kBounds>
 __global__ __launch_bounds__(kWave * kWalkWaves) void k_check(
     const float* __restrict__ ev_t, const int32_t* __restrict__ ev_src, const int32_t* __restrict__ ev_n, int E_max,
     int E_pad, const float* __restrict__ WT, int C_in, int N, int tiles, int S, int items, Model m,
-    const Decay* __restrict__ dec, const double2* __restrict__ carry, uint32_t* __restrict__ mask,
-    double2* __restrict__ pool,
+    const Decay* __restrict__ dec, double2* carry, uint32_t* __restrict__ mask, double2* __restrict__ pool,
     uint32_t* __restrict__ pool_count, uint32_t pool_cap, uint32_t* __restrict__ listed,
     uint32_t* __restrict__ work, uint32_t* __restrict__ nwork)
+// kBounds: key bounds are stored for k_resolve.  carry: a pair whose flagged
+// sub-blocks all have pool entries no longer needs its carried state (only its
+// own wave reads it before), and the four sub-blocks' bounds (key_bound; -inf
+// when not flagged) take its place.
 // work: per-sample lists of the neurons with flagged sub-blocks (capacity N
 // each); nwork: per-sample list lengths.
 {
     constexpr int NPL = 1;                  // one neuron per lane (occupancy)
     __shared__ double2 s_ad[kWalkWaves][kSeg];
     __shared__ double s_lk[kWalkWaves][kSeg];
-    __shared__ double s_gk[kWalkWaves][kGrpPerSeg];
     __shared__ double2 s_ent[kWalkWaves][kSubPerSeg][kWave];   // entering state of each sub-block
+    __shared__ float s_kb[kBounds ? kWalkWaves : 1][kSubPerSeg][kWave];   // and its key bound
     WalkCoords c;
     if (!walk_coords<NPL>(items, tiles, S, ev_n, E_max, N, c)) return;
     const int lane = c.lane;
     const int wv = threadIdx.x / kWave;
     double2* lad = s_ad[wv];
     double* llk = s_lk[wv];
-    double* lgk = s_gk[wv];
     const Stage st = stage_segment(c, ev_src + (size_t)c.b * E_max + c.k0, dec + (size_t)c.b * E_pad + c.k0, WT,
-                                   C_in, N, lad, llk, lgk);
+                                   C_in, N, lad, llk);
     const size_t row = ((size_t)c.b * S + c.seg) * N + c.n0;
     const unsigned long long below = (1ull << lane) - 1ull;
     double U[NPL], J[NPL];
@@ -469,7 +455,11 @@ __global__ __launch_bounds__(kWave * kWalkWaves) void k_check(
     load_grp<NPL>(st, 0, wa);
     for (int q = 0; q < kSubPerSeg; ++q) {
         const int q0 = q * kSub;
-        if (q0 >= c.cnt) break;
+        if constexpr (kBounds) s_kb[wv][q][lane] = -INFINITY;
+        if (q0 >= c.cnt) {
+            if constexpr (kBounds) continue;
+            break;
+        }
         double U0[NPL], J0[NPL], z[NPL];
 #pragma unroll
         for (int i = 0; i < NPL; ++i) {
@@ -478,10 +468,10 @@ __global__ __launch_bounds__(kWave * kWalkWaves) void k_check(
             z[i] = -INFINITY;
         }
         load_grp<NPL>(st, q0 + kGrp, wb);
-        screen_grp<NPL>(m, lad, llk, lgk[2 * q], q0, c.cnt - q0, wa, U, J, z);
+        screen_grp<NPL>(m, lad, llk, q0, c.cnt - q0, wa, U, J, z);
         if (q0 + kGrp < c.cnt) {
             load_grp<NPL>(st, q0 + kSub, wa);
-            screen_grp<NPL>(m, lad, llk, lgk[2 * q + 1], q0 + kGrp, c.cnt - q0 - kGrp, wb, U, J, z);
+            screen_grp<NPL>(m, lad, llk, q0 + kGrp, c.cnt - q0 - kGrp, wb, U, J, z);
         }
         if (last_seg && q0 + kSub >= c.cnt && open_lk > 0.0) {
 #pragma unroll
@@ -489,9 +479,14 @@ __global__ __launch_bounds__(kWave * kWalkWaves) void k_check(
                 z[i] = fmax(z[i], J[i] > m.th ? fma(J[i] - m.th, open_lk, U[i] - J[i]) : U[i] - J[i]);
         }
         s_ent[wv][q][lane] = make_double2(U0[0], J0[0]);
-#pragma unroll
-        for (int i = 0; i < NPL; ++i)
-            if (c.live && z[i] >= m.thk_lo) msk[i] |= 1u << q;
+        const bool flag = c.live && z[0] >= m.thk_lo;
+        if (flag) msk[0] |= 1u << q;
+        if constexpr (kBounds) {
+            if (__ballot(flag)) {
+                const double tl = (double)ev_t[(size_t)c.b * E_max + c.k0 + min(q0 + kSub, c.cnt) - 1];
+                if (flag) s_kb[wv][q][lane] = key_bound(m, z[0], tl);
+            }
+        }
     }
     // Pool entries of the wave's flagged sub-blocks: one reservation, slots
     // in lane order (exclusive prefix sum of the per-lane counts).
@@ -515,6 +510,11 @@ __global__ __launch_bounds__(kWave * kWalkWaves) void k_check(
 #pragma unroll
         for (int i = 0; i < NPL; ++i) {
             if (c.live) mask[row + i] = msk[i] | (base << kMaskBits);
+            if constexpr (kBounds) {
+                if (c.live && msk[i] && base + (uint32_t)__popc(msk[i]) <= pool_cap)
+                    *reinterpret_cast<float4*>(&carry[row + i]) =
+                        make_float4(s_kb[wv][0][lane], s_kb[wv][1][lane], s_kb[wv][2][lane], s_kb[wv][3][lane]);
+            }
             for (uint32_t mm = msk[i]; mm; mm &= mm - 1u) {
                 if (base < pool_cap) pool[(size_t)c.b * pool_cap + base] = s_ent[wv][__builtin_ctz(mm)][lane];
                 ++base;
@@ -600,73 +600,91 @@ __device__ __forceinline__ double rl_double(double v, int l)
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
+// Flagged sub-blocks of the whole call, by every wave.
+__device__ __forceinline__ unsigned long long flagged_total(const uint32_t* __restrict__ pool_count, int B)
+{
+    unsigned long long f = 0;
+    for (int b = (int)threadIdx.x % kWave; b < B; b += kWave) f += pool_count[(size_t)b * kCtr];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) f += __shfl_xor(f, off, kWave);
+    return f;
+}
+
+// Status words fixed once the check pass has run, by the grid's last wave (the
+// only writer of these words in the call): events consumed, flagged sub-blocks,
+// sub-blocks past the pool's capacity.
+__device__ __forceinline__ void resolve_status(const int32_t* __restrict__ ev_n, int B, int E_max,
+                                               const uint32_t* __restrict__ pool_count, uint32_t pool_cap,
+                                               int32_t* __restrict__ status)
+{
+    const int lane = (int)threadIdx.x % kWave;
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x >= blockDim.x - kWave) {
+        unsigned long long ev = 0, fl = 0, fb = 0;
+        for (int bb = lane; bb < B; bb += kWave) {
+            ev += (unsigned long long)clamp_count(ev_n[bb], E_max);
+            const uint32_t pc = pool_count[(size_t)bb * kCtr];
+            fl += pc;
+            fb += pc > pool_cap ? pc - pool_cap : 0u;
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            ev += __shfl_xor(ev, off, kWave);
+            fl += __shfl_xor(fl, off, kWave);
+            fb += __shfl_xor(fb, off, kWave);
+        }
+        if (lane == 0) {
+            auto sat = [](unsigned long long x) { return (int32_t)(x > 0x7fffffffull ? 0x7fffffffull : x); };
+            status[LIF_ST_EVENTS] = sat(ev);
+            status[LIF_ST_CAND_BLOCKS] = sat(fl);
+            status[LIF_ST_WALKED_BLOCKS] = sat(fl);
+            status[LIF_ST_POOL_FALLBACK] = sat(fb);
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
-// Resolve pass: one workgroup of four waves per neuron that has flagged
-// sub-blocks (the work lists of the check pass).  Intervals outside flagged
-// sub-blocks provably hold no spike.  The flagged sub-blocks are taken in
-// time order:
+// Resolve pass: one wave per neuron that has flagged sub-blocks (the work lists
+// of the check pass).  Intervals outside flagged sub-blocks provably hold no
+// spike.  The flagged sub-blocks are taken in time order:
 //   * Candidate list: per chunk of kChunkEv events, the sub-block masks (two
 //     segments per lane) are compacted into a time-ordered list in LDS with
-//     one wave prefix sum, with the pool slot of every candidate.
-//   * Windows of kWinCand candidates (kWinIv intervals) in a ring of kRing
-//     LDS buffers: the staging waves (waves 1..3, windows in turn) walk the
-//     window's sub-blocks and fill its buffer while the chain wave (wave 0)
-//     works on an earlier one; a ready word per buffer and a consumed count
-//     hand the buffers over (no barrier per window).
-//   * The chain searches a window 64 intervals at a time: interval i crosses
-//     iff key_i >= K, the key of the current reset deficit (crossing_key), so
-//     one ballot finds the earliest crossing.  Its spike time is solved
-//     wave-uniform, the deficit and K are raised, and the search resumes at
-//     the same interval (a second spike in it, App. E.2 restart).
-//   * The open interval after the sample's last event is one more slot of
-//     the window holding the sample's last sub-block.
+//     one wave prefix sum, with the pool slot and key bound of every
+//     candidate; candidates whose bound lies below the key K of the current
+//     reset deficit cannot hold a crossing and are left out.
+//   * Windows: the next kWinCand candidates whose bound still reaches K (one
+//     ballot per 64), one interval per lane.  The loads of the window after
+//     the one at work are in flight.
+//   * Interval i crosses iff key_i >= K (crossing_key), so one ballot finds
+//     the window's earliest crossing.  Its spike time is solved wave-uniform,
+//     the deficit and K are raised, and the search resumes at the same
+//     interval (a second spike in it, App. E.2 restart).
+//   * The open interval after the sample's last event follows the window
+//     that holds the sample's last sub-block.
 //   * Spikes are buffered in LDS and written out kWave at a time.
+// Most flagged sub-blocks lie in the wake of a spike, where the no-reset V is
+// above threshold but the true one is not: the key bounds leave a few windows
+// per spike of them.
 // ---------------------------------------------------------------------------
 constexpr int kChunkEv = 8192;                   // events per chunk of the candidate list
 constexpr int kChunkSeg = kChunkEv / kSeg;       // segments per chunk
 constexpr int kSegPerLane = kChunkSeg / kWave;   // mask words per lane
 static_assert(kChunkSeg % kWave == 0 && kSubPerSeg <= 8, "chunk layout; 3-bit sub-block field of a candidate");
 constexpr int kCandCap = kChunkSeg * kSubPerSeg; // candidates of one chunk
-constexpr int kCandPerStep = kWave / kSub;       // candidates per 64 intervals
-constexpr int kWinCand = kCandPerStep;           // candidates per window (one interval per lane)
-constexpr int kWinIv = kWinCand * kSub;          // intervals per window
-static_assert(kWinIv == kWave, "one window interval per lane");
-constexpr int kOpenIv = kWinIv;                  // window slot of the open interval
-constexpr int kRing = 8;                         // window buffers
-constexpr int kResolveWaves = 4;                 // the chain wave and three staging waves
+constexpr int kWinCand = kWave / kSub;           // candidates per window (one interval per lane)
+constexpr int kResolveWaves = 4;                 // independent waves of a workgroup
 
-struct WinBuf {
-    double key[kWinIv + 1];                      // crossing key (NaN: no interval)
-    double v0[kWinIv + 1], i0[kWinIv + 1];       // no-reset (V, I) at the interval start
-    float t0[kWinIv + 1];                        // interval start (time of the event before it; 0 for the first)
-    float t1[kWinIv + 1];                        // interval end (its closing event's time)
-};
+// The line between the two passes (see where they are launched).
+constexpr unsigned long long kRingMost = 65536;  // flagged sub-blocks of a call
+constexpr size_t kRingDense = (size_t)1 << 22;   // sub-blocks of a call, flagged or not
 
 struct ResolveLds {
     uint32_t cand[kCandCap];                     // (segment in chunk << 3) | sub-block
     uint32_t slot[kCandCap];                     // pool slot of each candidate (kNoSlot: none)
-    WinBuf win[kRing];
+    float kub[kCandCap];                         // key bound
     double sp_t0[kWave], sp_y[kWave];            // spike buffer: interval start, e^{-u/tm},
     float si[kWave];                             // I at the spike,
     int32_t sk[kWave];                           // events consumed before the spike
-    double open_len;                             // length of the open interval (t_end - last event)
-    int ntot;                                    // candidates of the chunk (chain wave -> both)
-    int ready[kRing];                            // 1 + window index staged in each buffer
-    double kmax[kRing];                          // largest key of each buffer's window (NaN keys left out)
-    int consumed;                                // windows the chain has finished
-    int stop;                                    // the chain reached s_max
-    unsigned long long kpub;                     // bits of the chain's current deficit key K
 };
-
-__device__ __forceinline__ int lds_load(const int* p)
-{
-    return __hip_atomic_load(const_cast<int*>(p), __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-__device__ __forceinline__ void lds_store(int* p, int v)
-{
-    __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
 
 // Entering no-reset state of sub-block kq0 (of the segment whose first
 // event is k0) from the segment's carried state (U, J), for a sub-block past
@@ -766,139 +784,46 @@ __device__ __forceinline__ double exp_lower(double x)
     return (1.0 - 0x1p-10) * (double)fminf(__expf((float)x), 3.0e38f);
 }
 
-// A staging wave's window: candidates c0 .. c0 + kWinCand - 1 of the chunk,
-// lane l taking interval j = l % kSub of candidate c0 + l / kSub.  Every lane
-// loads its own interval's closing event (source, decays, times) and its
-// candidate's entering state (stage_load, issued before the wait for the
-// window's buffer), then its weight; the 16
-// lanes of a candidate (one row) take the no-reset states of the sub-block by
-// a scan of its event maps (row_states), lane j the state at its interval's
-// start (after event j - 1) and end, and the interval's crossing key.  Candidates past the pool's capacity take
-// their entering state from rebuild_entry.  open_last: the window holds the
-// sample's last sub-block, and the open interval after its last event is
-// staged too.
-struct StageIn {
+// A window's loads: lane l takes interval j = l % kSub of candidate c (of lanes
+// l / kSub; none when c < 0): its closing event's source, decays and times and the
+// candidate's entering state.
+struct WinIn {
     int k, sc;
     bool ok;
-    uint32_t slot;
+    uint32_t cw, slot;
     double A, D;
     float ta, tb;
     double2 u0;
 };
 
-__device__ __forceinline__ StageIn stage_load(const ResolveLds& sh, int c0, int tot, int seg0, int nb,
-                                              const float* __restrict__ tt, const int32_t* __restrict__ src,
-                                              const Decay* __restrict__ d, const double2* __restrict__ pool)
+__device__ __forceinline__ WinIn win_load(const ResolveLds& sh, int c, int seg0, int nb, const float* __restrict__ tt,
+                                          const int32_t* __restrict__ src, const Decay* __restrict__ d,
+                                          const double2* __restrict__ pool)
 {
-    const int lane = (int)threadIdx.x % kWave;
-    const int j = lane % kSub, r = lane / kSub;
-    const int c = c0 + r;
-    const int cc = min(c, tot - 1);
-    const uint32_t cw = sh.cand[cc];
-    StageIn in;
+    const int j = (int)threadIdx.x % kSub, cc = max(c, 0);
+    WinIn in;
+    in.cw = sh.cand[cc];
     in.slot = sh.slot[cc];
-    const int kq = (seg0 + (int)(cw >> 3)) * kSeg + (int)(cw & 7u) * kSub;
-    in.ok = c < tot && kq + j < nb;
-    in.k = min(kq + j, nb - 1);
+    const int k = (seg0 + (int)(in.cw >> 3)) * kSeg + (int)(in.cw & 7u) * kSub + j;
+    in.ok = c >= 0 && k < nb;
+    in.k = min(k, nb - 1);
     in.sc = src[in.k];
-    const Decay dk = d[in.k];
-    in.A = dk.A;
-    in.D = dk.D;
+    const double2 ad = *reinterpret_cast<const double2*>(&d[in.k]);       // (A, D)
+    in.A = ad.x;
+    in.D = ad.y;
     in.ta = tt[max(in.k - 1, 0)];
     in.tb = tt[in.k];
     in.u0 = pool[in.slot != kNoSlot ? in.slot : 0u];    // the pool holds at least one entry
     return in;
 }
 
-__device__ __forceinline__ void stage_window(ResolveLds& sh, WinBuf& w, const Model& m, const StageIn& in, int c0,
-                                             int tot, int seg0, int b, int n, int nb, int S, int N, int C_in,
-                                             const int32_t* __restrict__ src, const Decay* __restrict__ d,
-                                             const float* __restrict__ WT, const double2* __restrict__ carry,
-                                             bool open_last, double& kmax)
-{
-    const int lane = (int)threadIdx.x % kWave;
-    const int r = lane / kSub;
-    const int c = c0 + r;
-    const int k = in.k, sc = in.sc;
-    const bool ok = in.ok;
-    const double2 ad = make_double2(in.A, in.D);
-    const float ta = in.ta, tb = in.tb;
-    double2 u0 = in.u0;
-    const float wv = WT[(size_t)clamp_src(sc, C_in) * (size_t)N + n];
-    if (__ballot(c < tot && in.slot == kNoSlot)) {
-        const int nc = min(kWinCand, tot - c0);
-        for (int x = 0; x < nc; ++x) {
-            if (sh.slot[c0 + x] != kNoSlot) continue;
-            const uint32_t cx = sh.cand[c0 + x];
-            const int seg = seg0 + (int)(cx >> 3);
-            const double2 cs = carry[((size_t)b * S + seg) * N + n];
-            const double2 e = rebuild_entry(cs.x, cs.y, seg * kSeg, seg * kSeg + (int)(cx & 7u) * kSub, n, N, C_in,
-                                            src, d, WT);
-            if (x == r) u0 = e;
-        }
-    }
-    double U0, J0, U, J;
-    row_states(u0, ad.x, ad.y, wv, U0, J0, U, J);
-    const double V0 = v_of(m, U0, J0), I0 = J0;
-    const double V1 = v_of(m, U, J);
-    const double t0 = k > 0 ? (double)ta : 0.0, t1 = (double)tb;
-    // The deficit of the spikes the chain has found so far, decayed to the
-    // interval's start, bounds the true deficit there from below (the chain
-    // works on earlier windows, and later spikes only add to it), so the
-    // no-crossing screen of the true state is safe with it (with a lower
-    // bound of that deficit, exp_lower).  Most intervals of a neuron that has
-    // fired fail it; the crossing key is computed only when some lane passes.
-    const double Kp = __longlong_as_double((long long)__hip_atomic_load(&sh.kpub, __ATOMIC_RELAXED,
-                                                                        __HIP_MEMORY_SCOPE_WORKGROUP));
-    const double L = t1 - t0;
-    const bool maybe = ok && L > 0.0 &&
-                       (V0 - exp_lower(Kp - t0 * m.inv_tm)) + (I0 > m.th ? (I0 - m.th) * (L * m.inv_tm) : 0.0) >=
-                           m.th_lo;
-    double key = __builtin_nan("");
-    double crit, hi, fhi;
-    if (__ballot(maybe)) {
-        crossing_data(m, V0, I0, V1, L, ad.x, ad.y, crit, hi, fhi);
-        if (maybe) key = crossing_key(m, crit, t0);
-    }
-    w.key[lane] = key;
-    double km = key;
-    w.v0[lane] = V0;
-    w.i0[lane] = I0;
-    w.t0[lane] = k > 0 ? ta : 0.0f;
-    w.t1[lane] = tb;
-    if (open_last && ok && k == nb - 1) {
-        // the open interval after the sample's last event (the same screen)
-        const double Lo = m.t_end - t1;
-        const bool mo = Lo > 0.0 &&
-                        (V1 - exp_lower(Kp - t1 * m.inv_tm)) + (J > m.th ? (J - m.th) * (Lo * m.inv_tm) : 0.0) >=
-                            m.th_lo;
-        double ko = __builtin_nan("");
-        if (mo) {
-            open_interval_data(m, V1, J, Lo, crit, hi, fhi);
-            ko = crossing_key(m, crit, t1);
-        }
-        w.key[kOpenIv] = ko;
-        w.v0[kOpenIv] = V1;
-        w.i0[kOpenIv] = J;
-        w.t0[kOpenIv] = tb;
-        sh.open_len = m.t_end - t1;
-        km = fmax(km, w.key[kOpenIv]);
-    }
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) km = fmax(km, __shfl_xor(km, off, kWave));
-    if (lane == 0) kmax = km;
-}
-
 // Wave-uniform resolve state of one neuron: the reset deficit of the spikes
-// so far is D(t) = dref e^{-(t - tref)/tm} for t after the latest spike,
-// with tref the start of the interval that spike lies in (the deficit is
-// carried in that interval's frame), and K = ln(dref) + tref/tm its key.
+// so far is D(t) = dref e^{-(t - tref)/tm} for t after the latest spike (dref =
+// 0: none yet), and K <= ln(dref) + tref/tm its key (a lower bound within
+// 1e-4, for the candidates' key bounds).
 struct Chain {
     int ns;              // spikes so far
     double dref, tref, K;
-    double ylast;        // e^{-u/tm} of the latest spike (its offset u in its interval)
-    int lastw, lasti;    // window and interval of the latest spike
-    bool capped;
 };
 
 // Spikes [from, to) from the LDS buffer to the outputs (coalesced); the
@@ -907,116 +832,41 @@ __device__ __forceinline__ void flush_spikes(ResolveLds& sh, const Model& m, int
                                              float* __restrict__ si, int32_t* __restrict__ sk)
 {
     const int lane = (int)threadIdx.x % kWave;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_lds_sync();
     if (from + lane < to) {
         const int q = (from + lane) % kWave;
         st[from + lane] = (float)(sh.sp_t0[q] - m.tm * log(sh.sp_y[q]));
         if (si) si[from + lane] = sh.si[q];
         if (sk) sk[from + lane] = sh.sk[q];
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
 }
 
-// The spike in window interval i (the earliest crossing the search found):
-// the deficit at the interval start, the spike time (polynomial solve when
-// tau_m / tau_s is an integer plus one, else bracketed Newton on the
-// interval's closed-form maximum), the spike into the LDS buffer, and the
-// raised deficit in the interval's frame.  Returns false at s_max.
+// Offset u of the spike in an interval of length L from the no-reset state
+// (V0, I0) with deficit Dk at its start, after y = ylo when the latest spike
+// lies in it too (V1, A, D: its end state and decays); all wave-uniform.
+// Returns y = e^{-u/tm} and e^{-u r} (polynomial solve when tau_m / tau_s is an
+// integer plus one, else bracketed Newton on the interval's closed-form
+// maximum).
 template <int PI>
-__device__ bool spike_at(ResolveLds& sh, const WinBuf& w, const Model& m, int i, int wg, int c0, int seg0, int nb,
-                         Chain& ch, float* __restrict__ st, float* __restrict__ si, int32_t* __restrict__ sk)
+__device__ __forceinline__ double spike_y(const Model& m, double V0, double I0, double V1, double L, double A, double D,
+                                          double Dk, double ylo, double& E2)
 {
-    const int lane = (int)threadIdx.x % kWave;
-    const double V0 = rl_double(w.v0[i], 0), I0 = rl_double(w.i0[i], 0);
-    const double t0 = (double)__builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, w.t0[i])));
-    const double Dk = ch.ns > 0 ? ch.dref * exp(-(t0 - ch.tref) * m.inv_tm) : 0.0;
-    const double ylo = (ch.ns > 0 && ch.lastw == wg && ch.lasti == i) ? ch.ylast : 1.0;
     const double kI = m.kappa * I0, c0v = V0 - Dk + kI;
-    double y = 0.0, E1 = 0.0, E2 = 0.0;
-    bool ok = false;
+    double y = 0.0;
     if constexpr (PI > 0) {
-        ok = root_poly<PI>(m, c0v, kI, ylo, y);
-        if (ok) E2 = ipow<PI>(y);
-    }
-    if (ok) {
-        E1 = rcp_refined(y);
-    } else {
-        // the exponential solve brackets the root in [0, hi] with the
-        // interval's closed-form maximum (interval_max)
-        const double L = i == kOpenIv ? sh.open_len : (double)w.t1[i] - t0;
-        double A = 0.0, D = 0.0, V1 = 0.0;
-        if (!isinf(L)) {
-            A = exp(-L * m.inv_tm);
-            D = exp(-L * m.inv_ts);
-            V1 = V0 * A + unit_kernel(m, L, A) * I0;
-        }
-        const IntervalMax im = interval_max(m, V0, I0, V1, L, A, D);
-        root_h(m, c0v, kI, 0.0, V0 - m.th - Dk, im.hi, im.Fhi - Dk, &E1, &E2, nullptr);
-        y = rcp_refined(E1);
-    }
-    int kev = nb;
-    if (i != kOpenIv) {
-        const uint32_t cw = sh.cand[c0 + i / kSub];
-        kev = (seg0 + (int)(cw >> 3)) * kSeg + (int)(cw & 7u) * kSub + i % kSub;
-    }
-    if (lane == 0) {
-        const int q = ch.ns % kWave;
-        sh.sp_t0[q] = t0;
-        sh.sp_y[q] = y;
-        sh.si[q] = (float)(I0 * (E2 * y));
-        sh.sk[q] = kev;
-    }
-    const double Dnew = Dk + m.dth * E1;
-    ch.dref = Dnew;
-    ch.tref = t0;
-    ch.K = log(Dnew) + t0 * m.inv_tm;
-    if (lane == 0)
-        __hip_atomic_store(&sh.kpub, (unsigned long long)__double_as_longlong(ch.K), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_WORKGROUP);
-    ch.ylast = y;
-    ch.lastw = wg;
-    ch.lasti = i;
-    ++ch.ns;
-    if (ch.ns % kWave == 0) flush_spikes(sh, m, ch.ns - kWave, ch.ns, st, si, sk);
-    if (ch.ns >= m.s_max) {
-        ch.capped = true;
-        return false;
-    }
-    return true;
-}
-
-// The chain wave's work on one window: its n_iv intervals (one per lane),
-// then (open_last) the open interval; one call site of the spike solve keeps
-// the kernel's code small.
-template <int PI>
-__device__ __forceinline__ void chain_window(ResolveLds& sh, const WinBuf& w, const Model& m, int wg, int c0, int n_iv,
-                                             bool open_last, int seg0, int nb, Chain& ch, float* __restrict__ st,
-                                             float* __restrict__ si, int32_t* __restrict__ sk)
-{
-    const int lane = (int)threadIdx.x % kWave;
-    const int nh = n_iv > 0 ? 1 : 0;
-    const int hend = open_last ? nh + 1 : nh;
-    const double kb = w.key[lane], ko = w.key[kOpenIv];
-    for (int h = 0; h < hend; ++h) {
-        const bool open = h == nh;
-        const double key = open ? ko : kb;
-        int from = 0;
-        for (;;) {
-            const unsigned long long cm = __ballot((open ? lane == 0 : lane >= from) && key >= ch.K);
-            if (cm == 0ull) break;
-            const int kl = __ffsll((long long)cm) - 1;
-            if (!spike_at<PI>(sh, w, m, open ? kOpenIv : h * kWave + kl, wg, c0, seg0, nb, ch, st, si, sk)) return;
-            from = kl;
+        if (root_poly<PI>(m, c0v, kI, ylo, y)) {
+            E2 = ipow<PI>(y);
+            return y;
         }
     }
+    const IntervalMax im = interval_max(m, V0, I0, V1, L, A, D);
+    double E1;
+    root_h(m, c0v, kI, 0.0, V0 - m.th - Dk, im.hi, im.Fhi - Dk, &E1, &E2, nullptr);
+    return rcp_refined(E1);
 }
 
-// Both waves of the workgroup call this for the same neuron and pass the
-// same barriers (one per chunk; candidate counts and the stop flag pass
-// through LDS).  Returns the spike count on the chain wave, 0 on the
-// staging wave.
+// One neuron by one wave; returns its spike count.
 template <int PI>
 __device__ int resolve_neuron(ResolveLds& sh, int b, int n, const float* __restrict__ ev_t,
                               const int32_t* __restrict__ ev_src, const int32_t* __restrict__ ev_n, int E_max,
@@ -1024,34 +874,41 @@ __device__ int resolve_neuron(ResolveLds& sh, int b, int n, const float* __restr
                               const Decay* __restrict__ dec, const double2* __restrict__ carry,
                               const uint32_t* __restrict__ mask, uint32_t pool_cap, const double2* __restrict__ pool,
                               float* __restrict__ out_t, int32_t* __restrict__ out_n, float* __restrict__ out_i,
-                              int32_t* __restrict__ out_k, int32_t* __restrict__ status)
+                              int32_t* __restrict__ out_k)
 {
     const int lane = (int)threadIdx.x % kWave;
-    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-    const bool chain = wv == 0;               // wave 0 resolves, waves 1.. stage (wave-uniform)
-    // the chain is the critical path: its instructions go first on its SIMD
-    if (chain) __builtin_amdgcn_s_setprio(3);
-    // a wait that does not end within kSpinLimit polls is an internal error:
-    // it is reported and the neuron is stopped instead of waiting for ever
-    auto give_up = [&]() {
-        if (lane == 0) atomicOr(&status[LIF_ST_FLAGS], LIF_WARN_INTERNAL);
-        lds_store(&sh.stop, 1);
-    };
-    if (threadIdx.x == 0) {
-        sh.consumed = 0;
-        sh.stop = 0;
-        sh.kpub = (unsigned long long)__double_as_longlong(-INFINITY);
-        for (int r = 0; r < kRing; ++r) sh.ready[r] = 0;
-    }
-    // the first chunk's mask words are loaded together with the event count
-    // (words past the sample's segments are dropped below)
-    uint32_t mw[kSegPerLane];
-#pragma unroll
-    for (int h = 0; h < kSegPerLane; ++h) {
-        const int sj = lane * kSegPerLane + h;
-        mw[h] = chain && sj < S ? mask[((size_t)b * S + sj) * N + n] : 0u;
-    }
+    const size_t row0 = (size_t)b * S * N + n;            // mask and carry of segment j: row0 + j N
+    // a chunk's mask words (lane l: segments kSegPerLane l + h of it) are loaded
+    // two chunks ahead and its key bounds one chunk ahead; words past the
+    // sample's segments are dropped when used
     const int nb = __builtin_amdgcn_readfirstlane(clamp_count(ev_n[b], E_max));
+    const int Sb = (nb + kSeg - 1) / kSeg;
+    uint32_t mw[kSegPerLane], m1[kSegPerLane];
+    float4 kb[kSegPerLane];
+    auto load_mask = [&](int seg0, uint32_t (&w)[kSegPerLane]) {
+#pragma unroll
+        for (int h = 0; h < kSegPerLane; ++h) {
+            const int sj = seg0 + lane * kSegPerLane + h;
+            w[h] = sj < S ? mask[row0 + (size_t)sj * N] : 0u;
+        }
+    };
+    auto flagged = [&](int seg0, uint32_t w, int h) {
+        return seg0 + lane * kSegPerLane + h < Sb ? w & ((1u << kSubPerSeg) - 1u) : 0u;
+    };
+    // (+inf where a pair's sub-blocks do not all have pool entries)
+    auto load_bounds = [&](int seg0, const uint32_t (&w)[kSegPerLane]) {
+#pragma unroll
+        for (int h = 0; h < kSegPerLane; ++h) {
+            const uint32_t mv = flagged(seg0, w[h], h);
+            kb[h] = make_float4(INFINITY, INFINITY, INFINITY, INFINITY);
+            if (mv && (w[h] >> kMaskBits) + (uint32_t)__popc(mv) <= pool_cap)
+                kb[h] = *reinterpret_cast<const float4*>(
+                    &carry[row0 + (size_t)(seg0 + lane * kSegPerLane + h) * N]);
+        }
+    };
+    load_mask(0, mw);
+    load_mask(kChunkSeg, m1);
+    load_bounds(0, mw);
     const float* tt = ev_t + (size_t)b * E_max;
     const int32_t* src = ev_src + (size_t)b * E_max;
     const Decay* d = dec + (size_t)b * E_pad;
@@ -1059,175 +916,271 @@ __device__ int resolve_neuron(ResolveLds& sh, int b, int n, const float* __restr
     float* st = out_t + idx * (size_t)m.s_max;
     float* si = out_i ? out_i + idx * (size_t)m.s_max : nullptr;
     int32_t* sk = out_k ? out_k + idx * (size_t)m.s_max : nullptr;
-    const int Sb = (nb + kSeg - 1) / kSeg;
-    const bool has_open = __builtin_amdgcn_readfirstlane(nb > 0 && m.t_end > (double)tt[max(nb - 1, 0)] ? 1 : 0) != 0;
-    __syncthreads();                          // the ring is reset
-
-    Chain ch{0, 0.0, 0.0, -INFINITY, 1.0, -1, -1, false};
-    int wbase = 0;                            // windows of earlier chunks
-    bool stop = false;
-    for (int seg0 = 0; seg0 < Sb && !stop; seg0 += kChunkSeg) {
-        // ---- this chunk's flagged sub-blocks as a time-ordered list, with
-        // slots; lane l takes segments seg0 + kSegPerLane l + h
-        if (chain) {
-            uint32_t mv[kSegPerLane];
-            int pc = 0;
+    Chain ch{0, 0.0, 0.0, -INFINITY};
+    bool more = true;                                     // false at s_max
+    for (int seg0 = 0; seg0 < Sb && more; seg0 += kChunkSeg) {
+        // ---- this chunk's flagged sub-blocks as a time-ordered list.  Before
+        // the first spike every one of them is a candidate, and neither the
+        // list nor its first window waits for the bounds.
+        const bool all = ch.ns == 0;
+        uint32_t keep[kSegPerLane];
+        int pc = 0;
 #pragma unroll
-            for (int h = 0; h < kSegPerLane; ++h) {
-                const int sj = seg0 + lane * kSegPerLane + h;
-                if (seg0 > 0) mw[h] = sj < Sb ? mask[((size_t)b * S + sj) * N + n] : 0u;
-                mv[h] = sj < Sb ? (mw[h] & ((1u << kSubPerSeg) - 1u)) : 0u;
-                pc += __popc(mv[h]);
-            }
-            int ex = pc;
+        for (int h = 0; h < kSegPerLane; ++h) {
+            keep[h] = flagged(seg0, mw[h], h);
+            if (!all) {
+                const float k4[4] = {kb[h].x, kb[h].y, kb[h].z, kb[h].w};
 #pragma unroll
-            for (int off = 1; off < kWave; off <<= 1) {
-                const int v = __shfl_up(ex, off, kWave);
-                if (lane >= off) ex += v;
+                for (int q = 0; q < kSubPerSeg; ++q)
+                    if (!((double)k4[q] >= ch.K)) keep[h] &= ~(1u << q);
             }
-            const int ctot = rl_int(ex, kWave - 1);
-            ex -= pc;
-            // candidates and their pool slots (consecutive per segment)
-            int o = ex;
-#pragma unroll
-            for (int h = 0; h < kSegPerLane; ++h) {
-                uint32_t mm = mv[h], rel = mw[h] >> kMaskBits;
-                while (mm) {
-                    sh.cand[o] = ((uint32_t)(lane * kSegPerLane + h) << 3) | (uint32_t)__builtin_ctz(mm);
-                    sh.slot[o] = rel < pool_cap ? (uint32_t)b * pool_cap + rel : kNoSlot;
-                    ++o;
-                    ++rel;
-                    mm &= mm - 1u;
-                }
-            }
-            if (lane == 0) sh.ntot = ctot;
+            pc += __popc(keep[h]);
         }
-        __syncthreads();
-        const int tot = __builtin_amdgcn_readfirstlane(sh.ntot);
-        const int nwin = (tot + kWinCand - 1) / kWinCand;
-        if (tot > 0) {
-            // the open interval is taken after the window holding the sample's
-            // last sub-block, when that sub-block is flagged (it is the last
-            // candidate of the last chunk)
-            const uint32_t cwl = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.cand[tot - 1]);
-            const bool open_here = has_open && (seg0 + (int)(cwl >> 3)) * kSeg + (int)(cwl & 7u) * kSub + kSub >= nb;
-            if (!chain) {
-                for (int wi = wv - 1; wi < nwin; wi += kResolveWaves - 1) {
-                    const int wg = wbase + wi, buf = wg % kRing;
-                    // this window's loads go out before the wait for its buffer
-                    const StageIn cur = stage_load(sh, wi * kWinCand, tot, seg0, nb, tt, src, d, pool);
-                    bool halt = false;
-                    for (int spin = 0;; ++spin) {
-                        halt = lds_load(&sh.stop) != 0;
-                        if (halt || lds_load(&sh.consumed) >= wg - kRing + 1) break;
-                        if (spin >= kSpinLimit) {
-                            give_up();
-                            halt = true;
-                            break;
-                        }
-                        __builtin_amdgcn_s_sleep(1);
-                    }
-                    if (halt) break;
-                    stage_window(sh, sh.win[buf], m, cur, wi * kWinCand, tot, seg0, b, n, nb, S, N, C_in, src, d,
-                                 WT, carry, open_here && wi == nwin - 1, sh.kmax[buf]);
-                    lds_store(&sh.ready[buf], wg + 1);
-                }
-            } else {
-                for (int wi = 0; wi < nwin;) {
-                    const int wg = wbase + wi, buf = wg % kRing;
-                    bool late = false;
-                    for (int spin = 0; lds_load(&sh.ready[buf]) != wg + 1; ++spin) {
-                        if (spin >= kSpinLimit || lds_load(&sh.stop) != 0) {
-                            if (spin >= kSpinLimit) give_up();
-                            late = true;
-                            break;
-                        }
-                        __builtin_amdgcn_s_sleep(1);
-                    }
-                    if (late) break;
-                    // the run of windows wi, wi + 1, ... staged already (lane q
-                    // looks at window wi + q), and the first of them whose
-                    // largest key reaches the current deficit's key: the
-                    // windows before it hold no crossing and are passed over
-                    const int bq = (wg + lane) % kRing;
-                    const bool rdy = lane < kRing && wi + lane < nwin && lds_load(&sh.ready[bq]) == wg + lane + 1;
-                    const int nr = __builtin_ctzll(~__ballot(rdy));
-                    const unsigned long long hit = __ballot(lane < nr && sh.kmax[bq] >= ch.K);
-                    if (hit == 0ull) {
-                        wi += nr;
-                        lds_store(&sh.consumed, wg + nr);
-                        continue;
-                    }
-                    wi += __builtin_ctzll(hit);
-                    const int wh = wbase + wi, c0 = wi * kWinCand;
-                    chain_window<PI>(sh, sh.win[wh % kRing], m, wh, c0, min(kWinCand, tot - c0) * kSub,
-                                     open_here && wi == nwin - 1, seg0, nb, ch, st, si, sk);
-                    ++wi;
-                    lds_store(&sh.consumed, wh + 1);
-                    if (ch.capped) {
-                        lds_store(&sh.stop, 1);
-                        break;
+        int ex = pc;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int v = __shfl_up(ex, off, kWave);
+            if (lane >= off) ex += v;
+        }
+        const int tot = rl_int(ex, kWave - 1);
+        const int o0 = ex - pc;
+        {
+            int o = o0;
+#pragma unroll
+            for (int h = 0; h < kSegPerLane; ++h) {
+                const uint32_t mv = flagged(seg0, mw[h], h), rel = mw[h] >> kMaskBits;
+#pragma unroll
+                for (int q = 0; q < kSubPerSeg; ++q) {
+                    if (keep[h] & (1u << q)) {
+                        const uint32_t r = rel + (uint32_t)__popc(mv & ((1u << q) - 1u));
+                        sh.cand[o] = ((uint32_t)(lane * kSegPerLane + h) << 3) | (uint32_t)q;
+                        sh.slot[o] = r < pool_cap ? (uint32_t)b * pool_cap + r : kNoSlot;
+                        ++o;
                     }
                 }
             }
         }
-        wbase += nwin;
-        __syncthreads();                      // both waves are done with the chunk's list
-        stop = __builtin_amdgcn_readfirstlane(lds_load(&sh.stop)) != 0;
+        wave_lds_sync();
+        // the lane's candidate of the next window at or after `from` whose
+        // bound reaches K (-1: none), the window's size in wn; moves `from`
+        // past it
+        int from = 0, wn = 0;
+        auto select = [&](double K) {
+            int mine = -1;
+            wn = 0;
+            while (from < tot && wn < kWinCand) {
+                const int i = from + lane;
+                unsigned long long hit = __ballot(i < tot && (double)sh.kub[min(i, tot - 1)] >= K);
+                int last = from + kWave;
+                while (hit && wn < kWinCand) {
+                    const int f = __builtin_ctzll(hit);
+                    if (lane / kSub == wn) mine = from + f;
+                    ++wn;
+                    hit &= hit - 1ull;
+                    if (wn == kWinCand) last = from + f + 1;
+                }
+                from = last;
+            }
+            return mine;
+        };
+        auto load_wt = [&](const WinIn& in) { return WT[(size_t)clamp_src(in.sc, C_in) * (size_t)N + n]; };
+        // the first window: the first kWinCand candidates (all of the list
+        // reach K)
+        wn = min(tot, kWinCand);
+        from = wn;
+        int c = lane / kSub < wn ? lane / kSub : -1;
+        WinIn in{};
+        float wv = 0.0f;
+        if (wn > 0) in = win_load(sh, c, seg0, nb, tt, src, d, pool);
+        {
+            int o = o0;
+#pragma unroll
+            for (int h = 0; h < kSegPerLane; ++h) {
+                const float k4[4] = {kb[h].x, kb[h].y, kb[h].z, kb[h].w};
+#pragma unroll
+                for (int q = 0; q < kSubPerSeg; ++q)
+                    if (keep[h] & (1u << q)) sh.kub[o++] = k4[q];
+            }
+        }
+        wave_lds_sync();
+        if (wn > 0) wv = load_wt(in);
+        uint32_t m2[kSegPerLane];
+        load_mask(seg0 + 2 * kChunkSeg, m2);
+        load_bounds(seg0 + kChunkSeg, m1);
+        while (wn > 0) {
+            // the next window, loaded while this one is at work, on the
+            // expectation of a spike in this one: at its first interval's
+            // start or later, so the deficit's key will be at least Kp
+            const int from_c = from, ns_c = ch.ns;
+            const double tf = (double)__builtin_bit_cast(
+                float, rl_int(__builtin_bit_cast(int, in.k > 0 ? in.ta : 0.0f), 0));
+            const double Dp = fma(ch.dref, exp_lower(-(tf - ch.tref) * m.inv_tm), m.dth);
+            const double Kp = fmax(ch.K, (double)__logf(fminf((float)Dp, 3.0e38f)) - 1e-5 + tf * m.inv_tm);
+            int c_n = select(Kp);
+            WinIn nx = in;
+            float wvn = 0.0f;
+            if (wn > 0) nx = win_load(sh, c_n, seg0, nb, tt, src, d, pool);
+            // ---- the window: interval states, keys, crossings
+            if (__ballot(c >= 0 && (double)sh.kub[max(c, 0)] >= ch.K)) {
+                double2 u0 = in.u0;
+                unsigned long long lost = __ballot(c >= 0 && in.slot == kNoSlot);
+                while (lost) {
+                    const int l = __builtin_ctzll(lost);
+                    const uint32_t cx = (uint32_t)rl_int((int)in.cw, l);
+                    const int seg = seg0 + (int)(cx >> 3);
+                    const double2 cs = carry[row0 + (size_t)seg * N];
+                    const double2 e = rebuild_entry(cs.x, cs.y, seg * kSeg, seg * kSeg + (int)(cx & 7u) * kSub, n, N,
+                                                    C_in, src, d, WT);
+                    if (lane / kSub == l / kSub) u0 = e;
+                    lost &= ~(0xffffull << (l / kSub * kSub));
+                }
+                double U0, J0, U, J;
+                row_states(u0, in.A, in.D, wv, U0, J0, U, J);
+                double V0 = v_of(m, U0, J0), I0 = J0, V1 = v_of(m, U, J), A = in.A, D = in.D;
+                float t0f = in.k > 0 ? in.ta : 0.0f;
+                double L = (double)in.tb - (double)t0f;
+                bool ok = in.ok && L > 0.0;
+                int kev = in.k;
+                const unsigned long long end = __ballot(in.ok && in.k == nb - 1);
+                if (wn > 0) wvn = load_wt(nx);
+                // the window's intervals, then (after the sample's last
+                // event) the open interval, on lane 0
+#pragma unroll 1
+                for (int open = 0; open < 2; ++open) {
+                    if (open) {
+                        if (!end || !more) break;
+                        const int l = __builtin_ctzll(end);
+                        V0 = rl_double(V1, l);
+                        I0 = rl_double(J, l);
+                        t0f = __builtin_bit_cast(float, rl_int(__builtin_bit_cast(int, in.tb), l));
+                        L = m.t_end - (double)t0f;
+                        A = D = V1 = 0.0;
+                        if (!isinf(L)) {
+                            A = exp(-L * m.inv_tm);
+                            D = exp(-L * m.inv_ts);
+                            V1 = V0 * A + unit_kernel(m, L, A) * I0;
+                        }
+                        ok = lane == 0 && L > 0.0;
+                        kev = nb;
+                    }
+                    // the deficit at the interval's start, and the no-crossing
+                    // screen of the true state
+                    const double t0 = (double)t0f;
+                    double x = exp(-(t0 - ch.tref) * m.inv_tm), Dl = ch.dref * x;
+                    ok = ok && (V0 - Dl) + (I0 > m.th ? (I0 - m.th) * (L * m.inv_tm) : 0.0) >= m.th_lo;
+                    if (__ballot(ok) == 0ull) continue;
+                    // crossing iff Dl a <= g (interval_max)
+                    double g = V1 - m.th, a = A;
+                    const bool inner = I0 > m.th && I0 * D < m.th;
+                    if (__ballot(ok && inner)) {
+                        const double gi = V0 + m.kappa * I0 - m.th_1k * exp(m.ts_tm * log(I0 * m.inv_th));
+                        g = inner ? gi : g;
+                        a = inner ? 1.0 : a;
+                    }
+                    int at = 0;
+                    double ylo = 1.0;
+                    for (;;) {
+                        const unsigned long long cm = __ballot(lane >= at && ok && Dl * a <= g);
+                        if (cm == 0ull) break;
+                        const int f = __builtin_ctzll(cm);
+                        if (f != at) ylo = 1.0;
+                        at = f;
+                        const double Is = rl_double(I0, at), ts0 = (double)__builtin_bit_cast(
+                                                                 float, rl_int(__builtin_bit_cast(int, t0f), at));
+                        const double Dk = rl_double(Dl, at);
+                        double E2;
+                        const double y = spike_y<PI>(m, rl_double(V0, at), Is, rl_double(V1, at), rl_double(L, at),
+                                                     rl_double(A, at), rl_double(D, at), Dk, ylo, E2);
+                        if (lane == 0) {
+                            const int q = ch.ns % kWave;
+                            sh.sp_t0[q] = ts0;
+                            sh.sp_y[q] = y;
+                            sh.si[q] = (float)(Is * (E2 * y));
+                            sh.sk[q] = rl_int(kev, at);
+                        }
+                        // the deficit raised by dth e^{u/tm} in the interval's
+                        // frame
+                        const double xa = rl_double(x, at);
+                        if (ch.ns > 0 && xa > 1e-30) {
+                            ch.dref = fma(m.dth, rcp_refined(y * xa), ch.dref);
+                        } else {
+                            ch.dref = fma(m.dth, rcp_refined(y), Dk);
+                            ch.tref = ts0;
+                            x = exp(-(t0 - ts0) * m.inv_tm);
+                        }
+                        Dl = ch.dref * x;
+                        ylo = y;
+                        ++ch.ns;
+                        if (ch.ns % kWave == 0) flush_spikes(sh, m, ch.ns - kWave, ch.ns, st, si, sk);
+                        more = ch.ns < m.s_max;
+                        if (!more) break;
+                    }
+                    ch.K = ch.ns > 0 ? (double)__logf(fminf((float)ch.dref, 3.0e38f)) - 1e-5 + ch.tref * m.inv_tm
+                                     : -INFINITY;
+                    if (!more) break;
+                }
+                if (!more) break;
+            }
+            if (ch.ns == ns_c) {                          // no spike: the next window by the K there is
+                from = from_c;
+                c_n = select(ch.K);
+                if (wn > 0) {
+                    nx = win_load(sh, c_n, seg0, nb, tt, src, d, pool);
+                    wvn = load_wt(nx);
+                }
+            }
+            c = c_n;
+            in = nx;
+            wv = wvn;
+        }
+        wave_lds_sync();                                  // the list is rewritten by the next chunk
+#pragma unroll
+        for (int h = 0; h < kSegPerLane; ++h) {
+            mw[h] = m1[h];
+            m1[h] = m2[h];
+        }
     }
-    if (!chain) return 0;
     flush_spikes(sh, m, ch.ns - ch.ns % kWave, ch.ns, st, si, sk);
     if (lane == 0) out_n[idx] = ch.ns;
     return ch.ns;
 }
 
 // Work-list driven: the per-sample lists of neurons built by the check pass
-// are taken as one concatenated list, entry w by workgroup w mod gridDim.x.
-// Status counts are added once per workgroup.
+// are taken as one concatenated list.  Wave w of the grid (the workgroups' first
+// waves first) takes entry w, then, when the list is longer than the grid, the
+// next one that no wave has taken (a counter, read an entry ahead; on a shorter
+// list thousands of waves would wait 15 us in line for it).  Status counts are
+// added once per workgroup.
 template <int PI>
 __global__ __launch_bounds__(kWave * kResolveWaves) void k_resolve(
     const float* __restrict__ ev_t, const int32_t* __restrict__ ev_src, const int32_t* __restrict__ ev_n, int B,
     int E_max, const float* __restrict__ WT, int C_in, int N, int E_pad, int S, Model m,
     const Decay* __restrict__ dec, const double2* __restrict__ carry, const uint32_t* __restrict__ mask,
     uint32_t pool_cap, const double2* __restrict__ pool, const uint32_t* __restrict__ pool_count,
-    const uint32_t* __restrict__ work, const uint32_t* __restrict__ nwork, float* __restrict__ out_t,
-    int32_t* __restrict__ out_n, float* __restrict__ out_i, int32_t* __restrict__ out_k, int32_t* __restrict__ status)
+    const uint32_t* __restrict__ work, const uint32_t* __restrict__ nwork, uint32_t* __restrict__ taken,
+    unsigned long long most, float* __restrict__ out_t, int32_t* __restrict__ out_n, float* __restrict__ out_i, int32_t* __restrict__ out_k,
+    int32_t* __restrict__ status)
 {
-    __shared__ ResolveLds sh;
-    const int lane = (int)threadIdx.x % kWave;
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x >= blockDim.x - kWave) {
-        // status words fixed once the check pass has run (the only writer of
-        // these words in the call): events consumed, flagged sub-blocks,
-        // sub-blocks past the pool's capacity
-        unsigned long long ev = 0, fl = 0, fb = 0;
-        for (int bb = lane; bb < B; bb += kWave) {
-            ev += (unsigned long long)clamp_count(ev_n[bb], E_max);
-            const uint32_t pc = pool_count[(size_t)bb * kCtr];
-            fl += pc;
-            fb += pc > pool_cap ? pc - pool_cap : 0u;
-        }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            ev += __shfl_xor(ev, off, kWave);
-            fl += __shfl_xor(fl, off, kWave);
-            fb += __shfl_xor(fb, off, kWave);
-        }
-        if (lane == 0) {
-            auto sat = [](unsigned long long x) { return (int32_t)(x > 0x7fffffffull ? 0x7fffffffull : x); };
-            status[LIF_ST_EVENTS] = sat(ev);
-            status[LIF_ST_CAND_BLOCKS] = sat(fl);
-            status[LIF_ST_WALKED_BLOCKS] = sat(fl);
-            status[LIF_ST_POOL_FALLBACK] = sat(fb);
-        }
-    }
+    __shared__ ResolveLds s_lds[kResolveWaves];
+    const int lane = (int)threadIdx.x % kWave, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    ResolveLds& sh = s_lds[wv];
+    const uint32_t nwaves = gridDim.x * kResolveWaves;
+    resolve_status(ev_n, B, E_max, pool_count, pool_cap, status);
+    if (flagged_total(pool_count, B) <= most) return;                    // k_resolve_ring's
     // spikes and capped neurons of this workgroup's neurons, added to the
     // status words once at its end
+    __shared__ unsigned long long s_spikes;
+    __shared__ uint32_t s_capped;
+    if (threadIdx.x == 0) {
+        s_spikes = 0ull;
+        s_capped = 0u;
+    }
+    __syncthreads();
     unsigned long long spikes = 0;
     uint32_t capped = 0;
-    // Both waves walk the list the same way.  Running sum of the list
-    // lengths over groups of 64 samples (one load per lane, a wave prefix
-    // sum): entry w of the concatenated lists belongs to the first sample
-    // whose running sum exceeds w.
+    // Running sum of the list lengths over groups of 64 samples (one load per
+    // lane, a wave prefix sum): entry w of the concatenated lists belongs to
+    // the first sample whose running sum exceeds w.
     int b0 = 0;               // first sample of the current group
     uint32_t base = 0;        // entries of the samples before the group
     uint32_t incl = 0;        // running sum up to and including sample b0 + lane
@@ -1241,7 +1194,16 @@ __global__ __launch_bounds__(kWave * kResolveWaves) void k_resolve(
         incl = base + c;
     };
     load_group();
-    for (uint32_t w = blockIdx.x;; w += gridDim.x) {
+    uint32_t total = (uint32_t)rl_int((int)incl, kWave - 1);
+    for (int bb = kWave; bb < B; bb += kWave) {
+        uint32_t c = bb + lane < B ? nwork[(size_t)(bb + lane) * kCtr] : 0u;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) c += (uint32_t)__shfl_xor((int)c, off, kWave);
+        total += c;
+    }
+    uint32_t next = 0;
+    for (uint32_t w = wv * gridDim.x + blockIdx.x; w < total;
+         w = total > nwaves ? nwaves + (uint32_t)__builtin_amdgcn_readfirstlane((int)next) : total) {
         unsigned long long past = __ballot(b0 + lane < B && incl <= w);
         while (past == ~0ull) {              // w lies beyond the whole group
             base = (uint32_t)__shfl((int)incl, kWave - 1, kWave);
@@ -1254,25 +1216,35 @@ __global__ __launch_bounds__(kWave * kResolveWaves) void k_resolve(
         const int b = b0 + l;
         if (b0 >= B || l >= kWave || b >= B) break;
         const uint32_t before = l > 0 ? (uint32_t)__shfl((int)incl, l - 1, kWave) : base;
+        if (lane == 0 && total > nwaves) next = atomicAdd(taken, 1u);
         const uint32_t bn = (uint32_t)__builtin_amdgcn_readfirstlane((int)work[(size_t)b * N + (w - before)]);
         const int ns = resolve_neuron<PI>(sh, (int)(bn / (uint32_t)N), (int)(bn % (uint32_t)N), ev_t, ev_src, ev_n,
                                       E_max, WT, C_in, N, E_pad, S, m, dec, carry, mask, pool_cap, pool, out_t, out_n,
-                                      out_i, out_k, status);
+                                      out_i, out_k);
         spikes += (unsigned long long)ns;
         capped += ns >= m.s_max ? 1u : 0u;
     }
-    if (threadIdx.x == 0) {
-        const int32_t sp = (int32_t)(spikes > 0x7fffffffull ? 0x7fffffffull : spikes);
-        if (sp) {
-            atomicAdd(&status[LIF_ST_SPIKES], sp);
-            atomicAdd(&status[LIF_ST_ROOT_SOLVES], sp);
-        }
-        if (capped) {
-            atomicAdd(&status[LIF_ST_CAPPED], (int32_t)capped);
+    if (lane == 0 && spikes) {
+        atomicAdd(&s_spikes, spikes);
+        atomicAdd(&s_capped, capped);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && s_spikes) {
+        const int32_t sp = (int32_t)(s_spikes > 0x7fffffffull ? 0x7fffffffull : s_spikes);
+        atomicAdd(&status[LIF_ST_SPIKES], sp);
+        atomicAdd(&status[LIF_ST_ROOT_SOLVES], sp);
+        if (s_capped) {
+            atomicAdd(&status[LIF_ST_CAPPED], (int32_t)s_capped);
             atomicOr(&status[LIF_ST_FLAGS], LIF_WARN_SPIKE_CAP);
         }
     }
 }
+
+}  // namespace lif
+
+#include "lif_ring.hpp"
+
+namespace lif {
 
 // Status words of a sequential forward call, from what the pass wrote:
 // spikes and capped neurons from the counts, events from the queue lengths.
@@ -1466,8 +1438,8 @@ FwdLayout fwd_layout(int B, int E_max, int N, int pool_cap)
     // segment aggregates, overwritten in place by the carried states
     L.carry = take(BS * N * sizeof(double2));
     L.mask = take(BS * N * sizeof(uint32_t));
-    // per sample: pool use, work-list length
-    L.n_counters = 2 * (size_t)B * kCtr;
+    // per sample: pool use, work-list length; then the resolve's list counter
+    L.n_counters = (2 * (size_t)B + 1) * kCtr;
     L.counters = take(L.n_counters * sizeof(uint32_t));
     L.listed = take((size_t)B * N * sizeof(uint32_t));
     L.work = take((size_t)B * N * sizeof(uint32_t));
@@ -1513,21 +1485,30 @@ struct FwdPtrs {
     double2* pool;
 };
 
+// W^T past this size (half an XCD's L2): the aggregate pass goes tile by tile of
+// 256 neurons, so that an XCD gathers from few columns at a time (32768 -> 2048,
+// B = 16, 100 k events: 2.07 -> 1.59 ms; 2312 -> 1024, B = 64: 318 -> 303 us).  The
+// check pass, whose tiles are 64 neurons and which reads the carried states and
+// writes masks, stays sample-major (2.28 ms against 2.73 ms by tiles and 2.37 ms
+// by groups of four).
+constexpr size_t kTileMajorW = (size_t)2 << 20;
+
 template <int NPL>
 static void launch_walks(const FwdLayout& L, const FwdPtrs& P, const float* ev_t, const int32_t* ev_src,
                          const int32_t* ev_n, int B, int E_max, const float* WT, int C_in, int N, const Model& m,
                          int32_t* status, bool validate, int32_t* out_n, float* out_t, float* out_i, int32_t* out_k,
-                         hipStream_t stream, bool check = true)
+                         hipStream_t stream, bool check = true, bool bounds = false)
 {
     const int tiles = (N + kWave * NPL - 1) / (kWave * NPL);
     const size_t items = (size_t)B * L.S * tiles;
     const unsigned blocks = (unsigned)((items + kWalkWaves - 1) / kWalkWaves);
+    const int tmB = NPL == 4 && (size_t)C_in * N * sizeof(float) > kTileMajorW ? B : 0;
     // the aggregate pass also computes the decays and resets the counters and
     // status words (validation flags are ORed in after it)
     TIMED_LAUNCH("aggregate", k_aggregate<NPL>, dim3(blocks), dim3(kWave * kWalkWaves), 0, stream,
                  ev_t, ev_src, ev_n, E_max, L.E_pad, WT, C_in, N, tiles, L.S, (int)items, m, P.dec, P.segm,
                  P.carry, status, P.counters, L.n_counters, P.listed, (size_t)B * N, out_n, out_t, out_i, out_k,
-                 out_t ? (size_t)B * N * (size_t)m.s_max : (size_t)0);
+                 out_t ? (size_t)B * N * (size_t)m.s_max : (size_t)0, tmB);
     if (validate)
         TIMED_LAUNCH("validate", k_validate, dim3((unsigned)(((size_t)B * E_max + 255) / 256)), dim3(256), 0,
                      stream, ev_t, ev_src, ev_n, B, E_max, C_in, status);
@@ -1541,9 +1522,13 @@ static void launch_walks(const FwdLayout& L, const FwdPtrs& P, const float* ev_t
     const int ctl = (N + kWave - 1) / kWave;
     const size_t citems = (size_t)B * L.S * ctl;
     const unsigned cblocks = (unsigned)((citems + kWalkWaves - 1) / kWalkWaves);
-    TIMED_LAUNCH("check", k_check, dim3(cblocks), dim3(kWave * kWalkWaves), 0, stream,
-                 ev_t, ev_src, ev_n, E_max, L.E_pad, WT, C_in, N, ctl, L.S, (int)citems, m, P.dec, P.carry, P.mask,
-                 P.pool, P.pool_count, (uint32_t)L.pool_cap, P.listed, P.work, P.nwork);
+    auto run = [&](auto kern) {
+        TIMED_LAUNCH("check", kern, dim3(cblocks), dim3(kWave * kWalkWaves), 0, stream,
+                     ev_t, ev_src, ev_n, E_max, L.E_pad, WT, C_in, N, ctl, L.S, (int)citems, m, P.dec, P.carry, P.mask,
+                     P.pool, P.pool_count, (uint32_t)L.pool_cap, P.listed, P.work, P.nwork);
+    };
+    if (bounds) run(k_check<true>);
+    else run(k_check<false>);
 }
 
 int forward_impl(bool sequential, const float* ev_t, const int32_t* ev_src, const int32_t* ev_n, int B, int E_max,
@@ -1602,30 +1587,44 @@ int forward_impl(bool sequential, const float* ev_t, const int32_t* ev_src, cons
         return check_launch();
     }
     if (items_max == 0) return check_launch();
+    const bool bounds = (size_t)L.S * kSubPerSeg * nn > kRingDense;
     switch (pick_npl(WT, N)) {
     case 4: launch_walks<4>(L, P, ev_t, ev_src, ev_n, B, E_max, WT, C_in, N, m, status, validate, out_n, out_t, out_i,
-                            out_k, stream); break;
+                            out_k, stream, true, bounds); break;
     case 2: launch_walks<2>(L, P, ev_t, ev_src, ev_n, B, E_max, WT, C_in, N, m, status, validate, out_n, out_t, out_i,
-                            out_k, stream); break;
+                            out_k, stream, true, bounds); break;
     default: launch_walks<1>(L, P, ev_t, ev_src, ev_n, B, E_max, WT, C_in, N, m, status, validate, out_n, out_t,
-                             out_i, out_k, stream); break;
+                             out_i, out_k, stream, true, bounds); break;
     }
-    // Four-wave workgroups (a chain wave and three staging waves) over the
-    // concatenated per-sample lists, as many as are resident at once; one
-    // kernel per spike-time solver (the polynomial degree)
+    // Which resolve pass: the ring pass prepares every flagged sub-block and
+    // follows each chain with the least latency (700 -> 256, B = 32, 6 k flagged:
+    // 33 us against 50 us); the wave-per-neuron pass skips by key bounds
+    // (2312 -> 1024 in bursts, B = 64, 11 M flagged: 3.9 against 0.63 ms; 32768 ->
+    // 2048, B = 16, 18 M: 9.7 against 1.23 ms).  The ring pass costs about 0.4 ns
+    // a flagged sub-block beyond its chains, so the line lies where that reaches
+    // a chain's length (kRingMost).  The count is known on the device only: calls
+    // that could flag many launch both, and one of them leaves at once; calls whose
+    // dense bound is small launch the ring alone (the idle launch is 3 us).
     const unsigned rgrid = (unsigned)(nn < 1024 ? nn : 1024);
-    auto resolve = [&](auto kern) {
-        TIMED_LAUNCH("resolve", kern, dim3(rgrid), dim3(kWave * kResolveWaves), 0, stream,
-                     ev_t, ev_src, ev_n, B, E_max, WT, C_in, N, L.E_pad, L.S, m, P.dec, P.carry, P.mask,
-                     (uint32_t)L.pool_cap, P.pool, P.pool_count, P.work, P.nwork, out_t, out_n, out_i, out_k,
-                     status);
+    const bool both = bounds;
+    const size_t rwg = (nn + kResolveWaves - 1) / kResolveWaves;
+    const unsigned wgrid = (unsigned)(rwg < 1024 ? rwg : 1024);
+    auto resolve = [&](auto wave, auto ring) {
+        if (both)
+            TIMED_LAUNCH("resolve", wave, dim3(wgrid), dim3(kWave * kResolveWaves), 0, stream, ev_t, ev_src, ev_n, B,
+                         E_max, WT, C_in, N, L.E_pad, L.S, m, P.dec, P.carry, P.mask, (uint32_t)L.pool_cap, P.pool,
+                         P.pool_count, P.work, P.nwork, P.counters + 2 * (size_t)B * kCtr, kRingMost, out_t, out_n,
+                         out_i, out_k, status);
+        TIMED_LAUNCH("resolve", ring, dim3(rgrid), dim3(kWave * kRingWaves), 0, stream, ev_t, ev_src, ev_n, B,
+                     E_max, WT, C_in, N, L.E_pad, L.S, m, P.dec, P.carry, P.mask, (uint32_t)L.pool_cap, P.pool,
+                     P.pool_count, P.work, P.nwork, both ? kRingMost : ~0ull, out_t, out_n, out_i, out_k, status);
     };
     switch (m.p_int) {
-    case 1: resolve(k_resolve<1>); break;
-    case 2: resolve(k_resolve<2>); break;
-    case 3: resolve(k_resolve<3>); break;
-    case 4: resolve(k_resolve<4>); break;
-    default: resolve(k_resolve<0>); break;
+    case 1: resolve(k_resolve<1>, k_resolve_ring<1>); break;
+    case 2: resolve(k_resolve<2>, k_resolve_ring<2>); break;
+    case 3: resolve(k_resolve<3>, k_resolve_ring<3>); break;
+    case 4: resolve(k_resolve<4>, k_resolve_ring<4>); break;
+    default: resolve(k_resolve<0>, k_resolve_ring<0>); break;
     }
     return check_launch();
 }
@@ -1695,7 +1694,7 @@ __global__ __launch_bounds__(kWave * kWalkWaves) void k_reg_walk(
     float* lt = s_t[wv];
     const float* tt = ev_t + (size_t)c.b * E_max;
     const Stage st = stage_segment(c, ev_src + (size_t)c.b * E_max + c.k0, dec + (size_t)c.b * E_pad + c.k0, WT,
-                                   C_in, N, lad, nullptr, nullptr);
+                                   C_in, N, lad, nullptr);
     // lt[e] = start of interval k0 + e (the time of event k0 + e - 1, or 0)
 #pragma unroll
     for (int h = 0; h < kSrcRegs; ++h) {
@@ -2109,8 +2108,7 @@ __global__ __launch_bounds__(kWave * kWalkWaves) void k_regg_walk(
     const Decay* d = dec + (size_t)c.b * E_pad;
     const float2* rb = rec + (size_t)c.b * (E_max + 1) * N + n;
     const float* tt = ev_t + (size_t)c.b * E_max;
-    const Stage st = stage_segment(c, ev_src + (size_t)c.b * E_max + c.k0, d + c.k0, WT, C_in, N, lad, nullptr,
-                                   nullptr);
+    const Stage st = stage_segment(c, ev_src + (size_t)c.b * E_max + c.k0, d + c.k0, WT, C_in, N, lad, nullptr);
 #pragma unroll
     for (int h = 0; h < kSrcRegs; ++h) {
         const int e = h * kWave + lane;

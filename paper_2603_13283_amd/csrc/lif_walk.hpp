@@ -36,19 +36,27 @@ struct WalkCoords {
     bool live;                    // the lane holds neurons (n0 < N)
 };
 
+// Items are sample-major (all tiles of a segment side by side) or, with tmB = B >
+// 0, tile-major: a tile over all samples and segments (see kTileMajorW).
 template <int NPL>
 __device__ __forceinline__ bool walk_coords(int items, int tiles, int S, const int32_t* __restrict__ ev_n, int E_max,
-                                            int N, WalkCoords& c)
+                                            int N, WalkCoords& c, int tmB = 0)
 {
     // wave-uniform by construction; readfirstlane lets the compiler keep
     // everything derived from it (sources, decays) in scalar registers
     const int item = __builtin_amdgcn_readfirstlane(xcd_remap(blockIdx.x, gridDim.x) * kWalkWaves +
                                                     (int)threadIdx.x / kWave);
     if (item >= items) return false;
-    c.tile = item % tiles;
-    const int rest = item / tiles;
-    c.seg = rest % S;
-    c.b = rest / S;
+    if (tmB > 0) {
+        c.seg = item % S;
+        c.b = item / S % tmB;
+        c.tile = item / S / tmB;
+    } else {
+        c.tile = item % tiles;
+        const int rest = item / tiles;
+        c.seg = rest % S;
+        c.b = rest / S;
+    }
     c.lane = (int)threadIdx.x % kWave;
     c.nb = clamp_count(ev_n[c.b], E_max);
     c.k0 = c.seg * kSeg;
@@ -77,12 +85,10 @@ __device__ __forceinline__ void load_w(const float* __restrict__ p, float (&w)[N
 // Per-wave staging of a segment.  The sources of its events go to VGPRs
 // (lane l holds those of events l and l + 64) and are broadcast with one lane
 // read per event; the decays (A, D) and screen slopes lk go to the wave's
-// slice of LDS and are read back as wave-wide broadcasts; for the check pass
-// also the largest slope of each group of kGrp intervals.  The weights are
+// slice of LDS and are read back as wave-wide broadcasts.  The weights are
 // read with buffer loads whose per-event row offset is a scalar operand, so
 // a load in flight holds no address registers.
 constexpr int kGrp = 8;
-constexpr int kGrpPerSeg = kSeg / kGrp;
 static_assert(kSub == 2 * kGrp && kWave % kGrp == 0, "a sub-block is two groups; groups tile lane ranges");
 constexpr int kSrcRegs = kSeg / kWave;
 
@@ -104,8 +110,7 @@ constexpr int kRsrcWord3 = 0x00020000;
 
 __device__ __forceinline__ Stage stage_segment(const WalkCoords& c, const int32_t* __restrict__ ss,
                                                const Decay* __restrict__ sd, const float* __restrict__ WT, int C_in,
-                                               int N, double2* __restrict__ lad, double* __restrict__ llk,
-                                               double* __restrict__ lgk)
+                                               int N, double2* __restrict__ lad, double* __restrict__ llk)
 {
     Stage st;
     st.rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)WT, (short)0, (int)((uint32_t)C_in * (uint32_t)N * 4u),
@@ -122,15 +127,6 @@ __device__ __forceinline__ Stage stage_segment(const WalkCoords& c, const int32_
         }
     }
     wave_lds_sync();
-    if (lgk) {
-        if (c.lane < kGrpPerSeg) {
-            double g = 0.0;
-#pragma unroll
-            for (int j = 0; j < kGrp; ++j) g = fmax(g, llk[c.lane * kGrp + j]);
-            lgk[c.lane] = g;
-        }
-        wave_lds_sync();
-    }
     return st;
 }
 
