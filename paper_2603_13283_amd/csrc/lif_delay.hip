@@ -739,30 +739,27 @@ __global__ __launch_bounds__(kWave * kDRegWaves) void k_dreg_walk(
     const float* st = out_t + item * (size_t)m.s_max;
     const int32_t* sk = out_k + item * (size_t)m.s_max;
     float2* rb = rec ? rec + item * ((size_t)E_max + 1) : nullptr;
-    double su = 0.0, so = 0.0, nsil = 0.0, nspk = 0.0, vpm = 0.0;
-    auto take = [&](int j, double V0, double I0, double L, double A, double D, bool spiked, bool end_input) {
-        const RegArg ra = reg_vmax_arg(m, V0, I0, L, A, D);
-        const double vmax = ra.vmax;
+    double su = 0.0, so = 0.0, nint = 0.0, nspk = 0.0;
+    float vpm = 0.0f;
+    auto take = [&](int j, const RegArg& ra, double V0, double I0, double I1, bool spiked, bool end_input) {
+        const double h = m.th - ra.vmax;
+        const double hp = spiked ? -h : h;
+        const double hinge = fmax(hp, 0.0);
+        su += spiked ? 0.0 : hinge;
         if (spiked) {
-            so += fmax(vmax - m.th, 0.0);
+            so += hinge;
             nspk += 1.0;
-        } else {
-            su += fmax(m.th - vmax, 0.0);
-            nsil += 1.0;
         }
+        nint += 1.0;
         if (rb) {
-            const float sgn = spiked ? (vmax > m.th ? -1.0f : 0.0f) : (vmax < m.th ? 1.0f : 0.0f);
-            double slope = 0.0;
-            if (ra.at_start) {
-                slope = j > 0 ? (I0 - V0) * m.inv_tm : 0.0;
-                rb[j] = make_record(sgn, kRecStart, 1.0, 1.0, slope);
-            } else if (ra.at_end && end_input) {
-                slope = (I0 * D - vmax) * m.inv_tm;
-                rb[j] = make_record(sgn, kRecEnd, A, D, slope);
-            } else {                             // inside, or the end t_end of the open interval
-                rb[j] = make_record(sgn, kRecInside, ra.em, ra.es, 0.0);
-            }
-            if (sgn != 0.0f) vpm = fmax(vpm, fabs(slope));
+            const float sgn = hp > 0.0 ? (spiked ? -1.0f : 1.0f) : 0.0f;
+            const bool end = ra.at_end && end_input;     // (else inside, or the end t_end of the open interval)
+            const double v = ra.at_start ? (j > 0 ? I0 - V0 : 0.0) : I1 - ra.vmax;
+            const float sl = (float)(v * m.inv_tm);
+            const float code = ra.at_start ? kRecStartCode : (end ? kRecEndCode : (float)ra.em);
+            const float y = ra.at_start || end ? sl : (float)ra.es;
+            rb[j] = sgn == 0.0f ? make_float2(0.0f, 0.0f) : make_float2(sgn * code, y);
+            vpm = fmaxf(vpm, sgn != 0.0f && (ra.at_start || end) ? fabsf(sl) : 0.0f);
         }
     };
     double U = 0.0, J = 0.0;       // no-reset state after event f - 1
@@ -837,7 +834,11 @@ __global__ __launch_bounds__(kWave * kDRegWaves) void k_dreg_walk(
             if (ks < r) Dft += m.dth * exp(-(ap - (double)st[s]) * m.inv_tm);
             spiked |= ks == r;
         }
-        if (ok) take(r, v_of(m, U0, J0) - Dft, J0, L, A, D, spiked, true);
+        if (ok) {
+            const double V0 = v_of(m, U0, J0) - Dft, I1 = J0 * D;
+            const double V1 = fma(V0, A, m.kappa * J0 * (A - D));
+            take(r, reg_vmax_in(m, V0, J0, A, D, V1, I1), V0, J0, I1, spiked, true);
+        }
         // the carry: the state after the step's last event, its arrival and
         // the deficit there
         const double Un = fma(aU, U, bU), Jn = fma(aJ, J, bJ);
@@ -858,17 +859,21 @@ __global__ __launch_bounds__(kWave * kDRegWaves) void k_dreg_walk(
         const double A = isinf(L) ? 0.0 : exp(-L * m.inv_tm), D = isinf(L) ? 0.0 : exp(-L * m.inv_ts);
         bool spiked = false;
         for (int s = sp; s < ns; ++s) spiked |= sk[s] == nb;
-        if (lane == 0) take(nb, v_of(m, U, J) - Dc, J, L, A, D, spiked, false);
+        if (lane == 0) {
+            const double V0 = v_of(m, U, J) - Dc;
+            take(nb, reg_vmax_arg(m, V0, J, L, A, D), V0, J, J * D, spiked, false);
+        }
     }
 #pragma unroll
     for (int off = 1; off < kWave; off <<= 1) {
         su += __shfl_xor(su, off, kWave);
         so += __shfl_xor(so, off, kWave);
-        nsil += __shfl_xor(nsil, off, kWave);
+        nint += __shfl_xor(nint, off, kWave);
         nspk += __shfl_xor(nspk, off, kWave);
-        vpm = fmax(vpm, __shfl_xor(vpm, off, kWave));
+        vpm = fmaxf(vpm, __shfl_xor(vpm, off, kWave));
     }
     if (lane == 0) {
+        const double nsil = nint - nspk;
         const double u = nsil > 0.0 ? su / nsil : 0.0;
         const double o = nspk > 0.0 ? so / nspk : 0.0;
         ub[item] = u;
@@ -876,7 +881,7 @@ __global__ __launch_bounds__(kWave * kDRegWaves) void k_dreg_walk(
         if (under) under[item] = (float)u;
         if (over) over[item] = (float)o;
         if (counts) counts[item] = make_double2(nsil, nspk);
-        if (vpmax) vpmax[item] = vpm;
+        if (vpmax) vpmax[item] = (double)vpm;
     }
 }
 

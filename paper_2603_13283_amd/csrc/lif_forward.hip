@@ -1677,6 +1677,14 @@ namespace lif {
 // segment, neuron), the sums over the segment's active intervals of the
 // decays from the segment's start (the input event before it) to the
 // interval's argmax, local = (under: e^{-./tm}, e^{-./ts}; over: the same).
+// kRec: records and local sums for the gradient; kSlope: with end-point slopes
+// (dL/dt wanted).  Nearly every interval of a wave is without a spike on all of
+// its lanes and takes the straight path, and the lookup of the lane's next spike
+// stays in a register.  Bound by VALU issue (47 % busy) and the records' stores:
+// 700 -> 512, B = 128, 10 k events, 5.2 GB of records: 3.45 -> 1.89 ms (the
+// quotient, logarithm and spike lookups of every interval: 141 VALU, 92 scalar
+// instructions and 19 branches per event before, 71, 28 and 7 now).
+template <bool kRec, bool kSlope>
 __global__ __launch_bounds__(kWave * kWalkWaves) void k_reg_walk(
     const float* __restrict__ ev_t, const int32_t* __restrict__ ev_src, const int32_t* __restrict__ ev_n, int E_max,
     int E_pad, const float* __restrict__ WT, int C_in, int N, int tiles, int S, int items, Model m,
@@ -1685,24 +1693,26 @@ __global__ __launch_bounds__(kWave * kWalkWaves) void k_reg_walk(
     float2* __restrict__ rec, double4* __restrict__ local)
 {
     __shared__ double2 s_ad[kWalkWaves][kSeg];
+    __shared__ double s_c[kWalkWaves][kSeg];
     __shared__ float s_t[kWalkWaves][kSeg + 1];
     WalkCoords c;
     if (!walk_coords<1>(items, tiles, S, ev_n, E_max, N, c)) return;
     const int lane = c.lane, wv = (int)threadIdx.x / kWave;
     const int n = c.n0;
     double2* lad = s_ad[wv];
+    double* lc = s_c[wv];
     float* lt = s_t[wv];
     const float* tt = ev_t + (size_t)c.b * E_max;
-    const Stage st = stage_segment(c, ev_src + (size_t)c.b * E_max + c.k0, dec + (size_t)c.b * E_pad + c.k0, WT,
-                                   C_in, N, lad, nullptr);
+    const Decay* dd = dec + (size_t)c.b * E_pad + c.k0;
     // lt[e] = start of interval k0 + e (the time of event k0 + e - 1, or 0)
 #pragma unroll
     for (int h = 0; h < kSrcRegs; ++h) {
         const int e = h * kWave + lane;
+        lc[e] = dd[e].C;
         if (e < c.cnt) lt[e + 1] = tt[c.k0 + e];
     }
     if (lane == 0) lt[0] = c.k0 > 0 ? tt[c.k0 - 1] : 0.0f;
-    wave_lds_sync();
+    const Stage st = stage_segment(c, ev_src + (size_t)c.b * E_max + c.k0, dd, WT, C_in, N, lad, nullptr);
     const double2 cs = carry[((size_t)c.b * S + c.seg) * N + n];
     double U = cs.x, J = cs.y;
     // the neuron's spikes: the deficit at the segment's start from those of
@@ -1713,40 +1723,49 @@ __global__ __launch_bounds__(kWave * kWalkWaves) void k_reg_walk(
     const int ns = c.live ? min(out_n[(size_t)c.b * N + n], m.s_max) : 0;
     const double t_start = (double)lt[0];
     double Dft = 0.0;
-    int sp = 0;
-    while (sp < ns && ks[sp] < c.k0) {
-        Dft += m.dth * exp(-(t_start - (double)ts[sp]) * m.inv_tm);
+    int sp = 0, knext = ns > 0 ? ks[0] : -1;             // the next spike's interval (-1: none)
+    auto advance = [&]() {
         ++sp;
+        knext = sp < ns ? ks[sp] : -1;
+    };
+    while (knext >= 0 && knext < c.k0) {
+        Dft += m.dth * exp(-(t_start - (double)ts[sp]) * m.inv_tm);
+        advance();
     }
     double su = 0.0, so = 0.0;
-    int nsil = 0, nspk = 0;
-    float2* rb = rec ? rec + (size_t)c.b * (E_max + 1) * N + n : nullptr;
+    int nspk = 0, nint = c.cnt;
+    float2* rb = kRec ? rec + (size_t)c.b * (E_max + 1) * N + n : nullptr;
     double cdm = 1.0, cds = 1.0;                 // decays from the segment's start to the interval's start
     double4 loc = make_double4(0.0, 0.0, 0.0, 0.0);
-    auto take = [&](int j, double L, double A, double Dd, double t1) {
-        const double V0 = v_of(m, U, J) - Dft;
-        const RegArg ra = reg_vmax_arg(m, V0, J, L, A, Dd);
-        const double vmax = ra.vmax;
-        const bool spiked = sp < ns && ks[sp] == j;
-        if (spiked) {
-            so += fmax(vmax - m.th, 0.0);
-            ++nspk;
-        } else {
-            su += fmax(m.th - vmax, 0.0);
-            ++nsil;
+    auto take = [&](int j, const RegArg& ra, double V0, double I1, double A, double Dd, double t1, bool input_end) {
+        const double h = m.th - ra.vmax;
+        float sgn = h > 0.0 ? 1.0f : 0.0f;
+        double under = fmax(h, 0.0);
+        const bool spk = knext == j;
+        const bool any = __ballot(spk) != 0ull;
+        if (any) {
+            asm volatile("");
+            if (spk) {
+                so += fmax(-h, 0.0);
+                ++nspk;
+                under = 0.0;
+                sgn = h < 0.0 ? -1.0f : 0.0f;
+            }
         }
-        if (rb && c.live) {
-            const float sgn = spiked ? (vmax > m.th ? -1.0f : 0.0f) : (vmax < m.th ? 1.0f : 0.0f);
-            if (ra.at_start)
-                rb[(size_t)j * N] = make_record(sgn, kRecStart, 1.0, 1.0, j > 0 ? (J - V0) * m.inv_tm : 0.0);
-            else if (ra.at_end && j < c.nb)
-                rb[(size_t)j * N] = make_record(sgn, kRecEnd, A, Dd, (J * Dd - ra.vmax) * m.inv_tm);
-            else                                 // inside, or the end t_end of the open interval
-                rb[(size_t)j * N] = make_record(sgn, kRecInside, ra.em, ra.es, 0.0);
-            if (sgn > 0.0f) {
-                loc.x = fma(cdm, ra.em, loc.x);
-                loc.y = fma(cds, ra.es, loc.y);
-            } else if (sgn < 0.0f) {
+        su += under;
+        if constexpr (kRec) {
+            const bool end = ra.at_end && input_end;      // (the open interval's end t_end is no input time)
+            const float code = ra.at_start ? kRecStartCode : (end ? kRecEndCode : (float)ra.em);
+            float y = (float)ra.es;
+            if constexpr (kSlope) {
+                const double v = ra.at_start ? (j > 0 ? J - V0 : 0.0) : I1 - ra.vmax;
+                y = ra.at_start || end ? (float)(v * m.inv_tm) : y;
+            }
+            if (c.live) rb[(size_t)j * N] = make_float2(sgn * code, sgn == 0.0f ? 0.0f : y);
+            const double pm = sgn > 0.0f ? cdm : 0.0, ps = sgn > 0.0f ? cds : 0.0;
+            loc.x = fma(pm, ra.em, loc.x);
+            loc.y = fma(ps, ra.es, loc.y);
+            if (any && sgn < 0.0f) {
                 loc.z = fma(cdm, ra.em, loc.z);
                 loc.w = fma(cds, ra.es, loc.w);
             }
@@ -1755,9 +1774,11 @@ __global__ __launch_bounds__(kWave * kWalkWaves) void k_reg_walk(
         }
         // the deficit at the interval's end, with the spikes inside it
         Dft *= A;
-        while (sp < ns && ks[sp] == j) {
-            Dft += m.dth * exp(-(t1 - (double)ts[sp]) * m.inv_tm);
-            ++sp;
+        if (any) {
+            while (knext == j) {
+                Dft += m.dth * exp(-(t1 - (double)ts[sp]) * m.inv_tm);
+                advance();
+            }
         }
     };
     const int ng = (c.cnt + kGrp - 1) / kGrp;
@@ -1769,8 +1790,8 @@ __global__ __launch_bounds__(kWave * kWalkWaves) void k_reg_walk(
             const int e = g * kGrp + jj;
             if (e >= c.cnt) break;
             const double2 ad = lad[e];
-            const double t0 = (double)lt[e], t1 = (double)lt[e + 1];
-            take(c.k0 + e, t1 - t0, ad.x, ad.y, t1);
+            const double V0 = fma(m.kappa, U - J, -Dft), V1 = fma(V0, ad.x, lc[e] * J), I1 = J * ad.y;
+            take(c.k0 + e, reg_vmax_in(m, V0, J, ad.x, ad.y, V1, I1), V0, I1, ad.x, ad.y, (double)lt[e + 1], true);
             step1(ad, w[jj][0], U, J);
         }
     };
@@ -1786,10 +1807,12 @@ __global__ __launch_bounds__(kWave * kWalkWaves) void k_reg_walk(
         const double t0 = (double)lt[c.cnt];
         const double L = m.t_end - t0;
         const double A = isinf(L) ? 0.0 : exp(-L * m.inv_tm), Dd = isinf(L) ? 0.0 : exp(-L * m.inv_ts);
-        take(c.nb, L, A, Dd, m.t_end);
+        const double V0 = v_of(m, U, J) - Dft;
+        take(c.nb, reg_vmax_arg(m, V0, J, L, A, Dd), V0, J * Dd, A, Dd, m.t_end, false);
+        ++nint;
     }
-    if (c.live) part[((size_t)c.b * S + c.seg) * N + n] = make_double4(su, (double)nsil, so, (double)nspk);
-    if (local && c.live) local[((size_t)c.b * S + c.seg) * N + n] = loc;
+    if (c.live) part[((size_t)c.b * S + c.seg) * N + n] = make_double4(su, (double)(nint - nspk), so, (double)nspk);
+    if (kRec && c.live) local[((size_t)c.b * S + c.seg) * N + n] = loc;
 }
 
 // Per (sample, neuron): the sums over the segments in order, then the means
@@ -1805,6 +1828,7 @@ __global__ __launch_bounds__(256) void k_reg_reduce(const double4* __restrict__ 
     const int nb = clamp_count(ev_n[b], E_max);
     const int Sb = (nb + kSeg - 1) / kSeg;
     double su = 0.0, nsil = 0.0, so = 0.0, nspk = 0.0;
+#pragma unroll 8                   // (eight loads in flight: the sums alone are a chain of latencies)
     for (int s = 0; s < Sb; ++s) {
         const double4 p = part[((size_t)b * S + s) * N + n];
         su += p.x;
@@ -1825,33 +1849,59 @@ __global__ __launch_bounds__(256) void k_reg_reduce(const double4* __restrict__ 
     if (counts) counts[i] = make_double2(nsil, nspk);
 }
 
-// The two loss terms (one workgroup): per neuron the batch means and the
-// gates of the mean spike count against the target, then the means over the
-// neurons, each sum in a fixed order.
-constexpr int kRegThreads = 256;
+// The two loss terms.  Per neuron (a workgroup takes kMeanN of them, its rows
+// of threads every kMeanB-th sample) the batch means and the gates of the mean
+// spike count against the target; a neuron's two terms replace its first
+// sample's ub and ob, which only its own threads have read.  k_reg_loss then
+// takes the means over the neurons.  Every sum is in a fixed order.  One
+// workgroup walked the whole batch before: 112 -> 8 us at B = 128, N = 512.
+constexpr int kRegThreads = 256, kMeanN = 16, kMeanB = kRegThreads / kMeanN;
+
+__global__ __launch_bounds__(kRegThreads) void k_reg_mean(double* __restrict__ ub, double* __restrict__ ob,
+                                                          const int32_t* __restrict__ out_n, int B, int N, int s_max,
+                                                          double c_target, double2* __restrict__ gates)
+{
+    __shared__ double4 s_p[kMeanB][kMeanN];
+    const int nl = (int)threadIdx.x % kMeanN, bl = (int)threadIdx.x / kMeanN;
+    const int n = (int)blockIdx.x * kMeanN + nl;
+    double4 p = make_double4(0.0, 0.0, 0.0, 0.0);
+    if (n < N) {
+#pragma unroll 4
+        for (int b = bl; b < B; b += kMeanB) {
+            const size_t i = (size_t)b * N + n;
+            const double cnt = (double)min(out_n[i], s_max);
+            p.x += cnt;
+            p.y += ub[i];
+            p.z += ob[i];
+            p.w += fmax(cnt / c_target - 1.0, 0.0) * ob[i];
+        }
+    }
+    s_p[bl][nl] = p;
+    __syncthreads();
+    if (bl == 0 && n < N) {
+        for (int q = 1; q < kMeanB; ++q) {
+            const double4 o = s_p[q][nl];
+            p.x += o.x;
+            p.y += o.y;
+            p.z += o.z;
+            p.w += o.w;
+        }
+        const double cb = p.x / (double)B;
+        const double gu = fmax(1.0 - cb / c_target, 0.0), go = fmax(cb / c_target - 1.0, 0.0);
+        ub[n] = gu * (p.y / (double)B) + go * (p.z / (double)B);
+        ob[n] = p.w;
+        if (gates) gates[n] = make_double2(gu, go);
+    }
+}
 
 __global__ __launch_bounds__(kRegThreads) void k_reg_loss(const double* __restrict__ ub, const double* __restrict__ ob,
-                                                          const int32_t* __restrict__ out_n, int B, int N, int s_max,
-                                                          double c_target, float* __restrict__ loss,
-                                                          double2* __restrict__ gates)
+                                                          int N, float* __restrict__ loss)
 {
     __shared__ double s_reg[kRegThreads], s_over[kRegThreads];
     double lr = 0.0, lo = 0.0;
     for (int n = threadIdx.x; n < N; n += kRegThreads) {
-        double cb = 0.0, mu = 0.0, mo = 0.0, ov = 0.0;
-        for (int b = 0; b < B; ++b) {
-            const size_t i = (size_t)b * N + n;
-            const double cnt = (double)min(out_n[i], s_max);
-            cb += cnt;
-            mu += ub[i];
-            mo += ob[i];
-            ov += fmax(cnt / c_target - 1.0, 0.0) * ob[i];
-        }
-        cb /= (double)B;
-        const double gu = fmax(1.0 - cb / c_target, 0.0), go = fmax(cb / c_target - 1.0, 0.0);
-        lr += gu * (mu / (double)B) + go * (mo / (double)B);
-        lo += ov;
-        if (gates) gates[n] = make_double2(gu, go);
+        lr += ub[n];
+        lo += ob[n];
     }
     s_reg[threadIdx.x] = lr;
     s_over[threadIdx.x] = lo;
@@ -1863,17 +1913,18 @@ __global__ __launch_bounds__(kRegThreads) void k_reg_loss(const double* __restri
         }
         __syncthreads();
     }
-    if (threadIdx.x == 0 && loss) {
+    if (threadIdx.x == 0) {
         loss[0] = (float)(s_reg[0] / (double)N);
         loss[1] = (float)(s_over[0] / (double)N);
     }
 }
 
-void launch_reg_loss(const double* ub, const double* ob, const int32_t* out_n, int B, int N, int s_max,
-                     double c_target, float* loss, double2* gates, hipStream_t stream)
+void launch_reg_loss(double* ub, double* ob, const int32_t* out_n, int B, int N, int s_max, double c_target,
+                     float* loss, double2* gates, hipStream_t stream)
 {
-    TIMED_LAUNCH("reg_loss", k_reg_loss, dim3(1), dim3(kRegThreads), 0, stream, ub, ob, out_n, B, N, s_max, c_target,
-                 loss, gates);
+    TIMED_LAUNCH("reg_mean", k_reg_mean, dim3((unsigned)((N + kMeanN - 1) / kMeanN)), dim3(kRegThreads), 0, stream, ub,
+                 ob, out_n, B, N, s_max, c_target, gates);
+    if (loss) TIMED_LAUNCH("reg_loss", k_reg_loss, dim3(1), dim3(kRegThreads), 0, stream, ub, ob, N, loss);
 }
 
 struct RegLayout {
@@ -1948,7 +1999,7 @@ extern "C" int lif_spike_count_reg(const float* ev_t, const int32_t* ev_src, con
         }
         const int tl = (N_out + kWave - 1) / kWave;
         const size_t it = (size_t)B * R.f.S * tl;
-        TIMED_LAUNCH("reg_walk", k_reg_walk, dim3((unsigned)((it + kWalkWaves - 1) / kWalkWaves)),
+        TIMED_LAUNCH("reg_walk", (k_reg_walk<false, false>), dim3((unsigned)((it + kWalkWaves - 1) / kWalkWaves)),
                      dim3(kWave * kWalkWaves), 0, stream, ev_t, ev_src, ev_n, E_max, R.f.E_pad, WT, C_in, N_out, tl,
                      R.f.S, (int)it, m, P.dec, P.carry, out_t, out_n, out_k, part, nullptr, nullptr);
     }
@@ -1956,8 +2007,7 @@ extern "C" int lif_spike_count_reg(const float* ev_t, const int32_t* ev_src, con
         TIMED_LAUNCH("reg_reduce", k_reg_reduce, dim3((unsigned)((nn + 255) / 256)), dim3(256), 0, stream, part, ev_n,
                      B, E_max, N_out, R.f.S, m.th, ub, ob, under, over, nullptr);
     if (B > 0)
-        TIMED_LAUNCH("reg_loss", k_reg_loss, dim3(1), dim3(kRegThreads), 0, stream, ub, ob, out_n, B, N_out, m.s_max,
-                     c_target, loss, nullptr);
+        launch_reg_loss(ub, ob, out_n, B, N_out, m.s_max, c_target, loss, nullptr, stream);
     return check_launch();
 }
 
@@ -2027,18 +2077,23 @@ void launch_regg_coef(const double2* counts, const double2* gates, const int32_t
 // 2 kappa M (M = the largest bound of k_regg_coef; the float32 decays of the
 // records add far less than the bit of headroom), an element sums at most
 // one per event of the batch: scale = 2^(61 - ceil(log2(2 kappa M events))).
-__global__ __launch_bounds__(kRegThreads) void k_regg_scale(const double* __restrict__ musum, size_t nn,
+// A chain of load latencies: 1024 threads with eight loads in flight, 64 -> 10 us
+// for 65536 bounds.
+constexpr int kScaleThreads = 1024;
+
+__global__ __launch_bounds__(kScaleThreads) void k_regg_scale(const double* __restrict__ musum, size_t nn,
                                                             const int32_t* __restrict__ ev_n, int B, int E_max,
                                                             double kappa, double* __restrict__ scale)
 {
-    __shared__ double s_max[kRegThreads], s_ev[kRegThreads];
+    __shared__ double s_max[kScaleThreads], s_ev[kScaleThreads];
     double mx = 0.0, ev = 0.0;
-    for (size_t i = threadIdx.x; i < nn; i += kRegThreads) mx = fmax(mx, musum[i]);
-    for (int b = threadIdx.x; b < B; b += kRegThreads) ev += (double)clamp_count(ev_n[b], E_max);
+#pragma unroll 8
+    for (size_t i = threadIdx.x; i < nn; i += kScaleThreads) mx = fmax(mx, musum[i]);
+    for (int b = threadIdx.x; b < B; b += kScaleThreads) ev += (double)clamp_count(ev_n[b], E_max);
     s_max[threadIdx.x] = mx;
     s_ev[threadIdx.x] = ev;
     __syncthreads();
-    for (int off = kRegThreads / 2; off > 0; off >>= 1) {
+    for (int off = kScaleThreads / 2; off > 0; off >>= 1) {
         if ((int)threadIdx.x < off) {
             s_max[threadIdx.x] = fmax(s_max[threadIdx.x], s_max[threadIdx.x + off]);
             s_ev[threadIdx.x] += s_ev[threadIdx.x + off];
@@ -2380,22 +2435,25 @@ extern "C" int lif_spike_count_reg_backward(const float* ev_t, const int32_t* ev
         default: launch_walks<1>(R.f, P, ev_t, ev_src, ev_n, B, E_max, WT, C_in, N_out, m, st, false, nullptr,
                                  nullptr, nullptr, nullptr, stream, false); break;
         }
-        TIMED_LAUNCH("reg_walk", k_reg_walk, dim3(wblocks), dim3(kWave * kWalkWaves), 0, stream, ev_t, ev_src, ev_n,
-                     E_max, R.f.E_pad, WT, C_in, N_out, tl, R.f.S, (int)items_max, m, P.dec, P.carry, out_t, out_n,
-                     out_k, part, rec, local);
+        auto walk = [&](auto kern) {
+            TIMED_LAUNCH("reg_walk", kern, dim3(wblocks), dim3(kWave * kWalkWaves), 0, stream, ev_t, ev_src, ev_n,
+                         E_max, R.f.E_pad, WT, C_in, N_out, tl, R.f.S, (int)items_max, m, P.dec, P.carry, out_t, out_n,
+                         out_k, part, rec, local);
+        };
+        if (grad_ev_t) walk(k_reg_walk<true, true>);
+        else walk(k_reg_walk<true, false>);
     }
     if (nn)
         TIMED_LAUNCH("reg_reduce", k_reg_reduce, dim3((unsigned)((nn + 255) / 256)), dim3(256), 0, stream, part, ev_n,
                      B, E_max, N_out, R.f.S, m.th, ub, ob, nullptr, nullptr, counts);
     if (B > 0)
-        TIMED_LAUNCH("reg_loss", k_reg_loss, dim3(1), dim3(kRegThreads), 0, stream, ub, ob, out_n, B, N_out, m.s_max,
-                     c_target, loss, gates);
+        launch_reg_loss(ub, ob, out_n, B, N_out, m.s_max, c_target, loss, gates, stream);
     size_t work = nW > nn ? nW : nn;
     size_t blocks = (work + 255) / 256;
     blocks = blocks < 1 ? 1 : (blocks > 2048 ? 2048 : blocks);
     TIMED_LAUNCH("regg_coef", k_regg_coef, dim3((unsigned)blocks), dim3(256), 0, stream, counts, gates, out_n, B,
                  N_out, m.s_max, c_target, lam_reg, lam_over, coef, musum, gw, nW);
-    TIMED_LAUNCH("regg_scale", k_regg_scale, dim3(1), dim3(kRegThreads), 0, stream, musum, nn, ev_n, B, E_max,
+    TIMED_LAUNCH("regg_scale", k_regg_scale, dim3(1), dim3(kScaleThreads), 0, stream, musum, nn, ev_n, B, E_max,
                  m.kappa, scale);
     if (items_max > 0) {
         TIMED_LAUNCH("regg_carry", k_regg_carry, dim3((unsigned)tl, (unsigned)B), dim3(kWave), 0, stream, ev_n, E_max,

@@ -53,6 +53,39 @@ __device__ __forceinline__ RegArg reg_vmax_arg(const Model& m, double V0, double
     return r;
 }
 
+// The same over an interval of finite length whose end state is at hand (V1, and
+// I1 = I0 Dd): the stationary point lies inside iff V' = (I - V)/tm is positive at
+// the start and negative at the end (V' has at most one zero), so the quotient
+// and its logarithm are taken by the lanes that need them only, and
+// e^{-u/tm} = ratio^{-kappa} directly (kappa = ts / (tm - ts) = c_tv / tm).
+__device__ __forceinline__ RegArg reg_vmax_in(const Model& m, double V0, double I0, double A, double Dd, double V1,
+                                              double I1)
+{
+    RegArg r;
+    r.at_end = V1 > V0;
+    r.at_start = !r.at_end;
+    r.vmax = r.at_end ? V1 : V0;
+    r.em = r.at_end ? A : 1.0;
+    r.es = r.at_end ? Dd : 1.0;
+    if (I0 > V0 && I1 < V1) {
+        const double kI = m.kappa * I0, a = V0 + kI;
+        const float ratio = (float)(kI * (m.tm * m.inv_ts) * __builtin_amdgcn_rcp(a));
+        const float emf = fminf(__builtin_amdgcn_exp2f(-(float)m.kappa * __builtin_amdgcn_logf(ratio)), 1.0f);
+        float esf;
+        switch (m.p_int) {
+        case 1: esf = emf * emf; break;
+        case 2: esf = emf * emf * emf; break;
+        case 3: { const float e2 = emf * emf; esf = e2 * e2; } break;
+        case 4: { const float e2 = emf * emf; esf = e2 * e2 * emf; } break;
+        default: esf = __builtin_amdgcn_exp2f((float)(m.tm * m.inv_ts) * __builtin_amdgcn_logf(emf)); break;
+        }
+        const double em = (double)emf, es = (double)esf;
+        const double Vu = fma(V0, em, kI * (em - es));
+        if (Vu > r.vmax) r = RegArg{Vu, em, es, false, false};
+    }
+    return r;
+}
+
 // Per-interval record for the regularisers' gradient, interval j of a
 // (sample, neuron), float2 {x, y} (the plain layer keeps them at
 // rec[(b (E_max + 1) + j) N + n], the delayed one at
@@ -64,16 +97,7 @@ __device__ __forceinline__ RegArg reg_vmax_arg(const Model& m, double V0, double
 // 0; the decays of an end are the interval's own), else e^{-u/tm} of a
 // stationary point inside (or of the end t_end of the open interval), with
 // y = e^{-u/ts}.
-enum RecKind { kRecInside = 0, kRecStart = 1, kRecEnd = 2 };
 constexpr float kRecStartCode = 2.0f, kRecEndCode = 3.0f;
-
-__device__ __forceinline__ float2 make_record(float sgn, int kind, double em, double es, double slope)
-{
-    if (sgn == 0.0f) return make_float2(0.0f, 0.0f);
-    if (kind == kRecStart) return make_float2(sgn * kRecStartCode, (float)slope);
-    if (kind == kRecEnd) return make_float2(sgn * kRecEndCode, (float)slope);
-    return make_float2(sgn * (float)em, (float)es);
-}
 
 // A record decoded with the interval's own decays (A, D): the multiplier mu
 // of its pseudo-spike (dL/dV_max; 0 for an inactive record), the decays at
