@@ -2320,6 +2320,224 @@ __global__ __launch_bounds__(kWave * kWalkWaves) void k_regg_walk(
     }
 }
 
+// The same walk with dL/dW in LDS: a workgroup takes 16 neurons of all C_in
+// channels (kTileRow bytes of LDS per channel) and every slices-th quadruple of
+// (segment, sample) items, one item per row of 16 lanes, and adds its sums to
+// gw once at the end.  Lane i of a row holds the decays and offsets of event i
+// of the current 16 (counted from the segment's last event backwards) and sends
+// them to its row by DPP.  Without the LDS the walk waits for its global 64-bit
+// atomics, 184 G/s on the whole chip however they are spread (about 20 times
+// that in LDS): 700 -> 512, B = 128, 10 k events, 4.05 -> 2.33 ms, now bound by
+// VALU issue (63 % busy, two waves per SIMD; three spill: 5.87 ms).
+constexpr int kTileN = 16, kTileRow = kTileN * (int)sizeof(long long), kTileWaves = 8;
+
+template <bool kTime>
+__global__ __launch_bounds__(kWave * kTileWaves) void k_regg_tile(
+    const float* __restrict__ ev_t, const int32_t* __restrict__ ev_src, const int32_t* __restrict__ ev_n, int B,
+    int E_max, int E_pad, const float* __restrict__ WT, int C_in, int N, int S, Model m,
+    const Decay* __restrict__ dec, const float2* __restrict__ rec, const double2* __restrict__ coef,
+    const double2* __restrict__ cin, const float* __restrict__ out_t, const int32_t* __restrict__ out_n,
+    const int32_t* __restrict__ out_k, const double* __restrict__ scale, long long* __restrict__ gw,
+    double* __restrict__ gtp, float* __restrict__ grad_spike)
+{
+    extern __shared__ unsigned long long s_gw[];
+    const int lane = (int)threadIdx.x % kWave, wv = (int)threadIdx.x / kWave;
+    const int rl = lane % kTileN;
+    const int nt = (int)blockIdx.x * kTileN + rl;
+    const bool in_n = nt < N;
+    const int n = in_n ? nt : N - 1;
+    for (int x = (int)threadIdx.x; x < C_in * kTileN; x += kWave * kTileWaves) s_gw[x] = 0ull;
+    __syncthreads();
+    const double sc = scale[0], kap = m.kappa, sk = -(m.dth * m.inv_tm);
+    const size_t rstep = (size_t)N * sizeof(float2);
+    const int quads = (int)(((long long)B * S + 3) / 4);
+    const __amdgpu_buffer_rsrc_t wrs =
+        __builtin_amdgcn_make_buffer_rsrc((void*)WT, (short)0, (int)((uint32_t)C_in * (uint32_t)N * 4u), kRsrcWord3);
+    for (int q = (int)blockIdx.y * kTileWaves + wv; q < quads; q += (int)gridDim.y * kTileWaves) {
+        // a row's item: segment-major, so that the four rows are four samples at
+        // the same segment, of equal length but for the samples' last segments
+        const long long item = (long long)q * 4 + lane / kTileN;
+        const int seg = (int)(item / B), b = (int)(item % B);
+        const int nb = item < (long long)B * S ? clamp_count(ev_n[b], E_max) : 0;
+        const int k0 = nb > seg * kSeg ? seg * kSeg : 0;
+        const int cnt = nb > seg * kSeg ? min(kSeg, nb - k0) : 0;
+        if (!__ballot(cnt > 0)) continue;
+        const bool live = in_n && cnt > 0;
+        const int k1 = k0 + max(cnt - 1, 0);
+        const Decay* d = dec + (size_t)b * E_pad;
+        const int32_t* ss = ev_src + (size_t)b * E_max;
+        const float2* rb = rec + (size_t)b * (E_max + 1) * N + n;
+        const size_t bn = (size_t)b * N + n;
+        double2 G = coef[bn];
+        if (!live) G = make_double2(0.0, 0.0);
+        // (P, Q) at event k1, as in k_regg_walk
+        const double2 ci = cin[((size_t)b * S + min(seg, S - 1)) * N + n];
+        double Pm = ci.x, Ps = ci.y;
+        const bool last = k1 + 1 >= nb;
+        Decay en{0.0, 0.0, 0.0, 0.0};
+        if (!last) en = d[k1 + 1];
+        RecTerm tn = rec_term(rb[(size_t)(k1 + 1) * N], G, en.A, en.D);
+        if (last) {
+            Pm = fma(tn.mu, tn.em, Pm);
+            Ps = fma(tn.mu, tn.es, Ps);
+        }
+        // the lane's spikes of the segment, last first, by their event's place i
+        // counted back from k1 (-1: none); bursts read them in the walk
+        const float* ts = out_t + bn * (size_t)m.s_max;
+        const int32_t* ks = out_k + bn * (size_t)m.s_max;
+        float* gsp = grad_spike + bn * (size_t)m.s_max;
+        int sp = 0;
+        {
+            int hi = live ? min(out_n[bn], m.s_max) : 0;
+            while (sp < hi) {
+                const int mid = (sp + hi) >> 1;
+                if (ks[mid] <= k1) sp = mid + 1; else hi = mid;
+            }
+        }
+        int pk[kRegPre];
+        float pt[kRegPre], pg[kRegPre];
+#pragma unroll
+        for (int u = 0; u < kRegPre; ++u) {
+            const int x = sp - 1 - u;
+            const int kq = x >= 0 ? ks[x] : -1;
+            const bool in = kq >= k0;
+            pk[u] = in ? k1 - kq : -1;
+            pt[u] = in ? ts[x] : 0.0f;
+            pg[u] = in ? gsp[x] : 0.0f;
+        }
+        const int qx = sp - 1 - kRegPre;
+        const bool burst = __ballot(qx >= 0 && ks[max(qx, 0)] >= k0) != 0ull;
+        double* gt = nullptr;
+        if constexpr (kTime) gt = gtp + ((size_t)blockIdx.x * B + b) * E_max + k1;
+        const float* te = ev_t + (size_t)b * E_max;
+        struct Meta {
+            double A, D;
+            int wo, lo;
+        };
+        // event 16 ch + rl of the row (past its first event that one again)
+        auto load_meta = [&](int ch) {
+            const int k = k0 + max(cnt - 1 - ch * kTileN - rl, 0);
+            const double2 ad = *reinterpret_cast<const double2*>(&d[k]);
+            const int src = clamp_src(ss[k], C_in);
+            return Meta{ad.x, ad.y, src * N * 4, src * kTileN};
+        };
+        const char* rp = reinterpret_cast<const char*>(rb + (size_t)k1 * N);
+        int left = cnt - 1;                       // records after the one at rp
+        auto load_half = [&](const Meta& me, auto half, float (&w)[kGrp], float2 (&r)[kGrp]) {
+            auto one = [&](auto jj) {
+                constexpr int J = decltype(jj)::value;
+                const int off = row_bcast<decltype(half)::value * kGrp + J>(me.wo) + n * 4;
+                w[J] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wrs, off, 0, 0));
+                r[J] = *reinterpret_cast<const float2*>(rp);
+                rp -= left > 0 ? rstep : 0;
+                --left;
+            };
+            one(std::integral_constant<int, 0>{}); one(std::integral_constant<int, 1>{});
+            one(std::integral_constant<int, 2>{}); one(std::integral_constant<int, 3>{});
+            one(std::integral_constant<int, 4>{}); one(std::integral_constant<int, 5>{});
+            one(std::integral_constant<int, 6>{}); one(std::integral_constant<int, 7>{});
+        };
+        int inext = pk[0];                        // the place of the lane's next spike, -1: none
+        auto half_walk = [&](int i0, const Meta& me, auto half, const float (&w)[kGrp], const float2 (&r)[kGrp]) {
+            double ca[kGrp];
+            auto one = [&](auto jj) {
+                constexpr int J = decltype(jj)::value, L = decltype(half)::value * kGrp + J;
+                const int i = i0 + J;
+                const double A = row_bcast<L>(me.A), D = row_bcast<L>(me.D);
+                const bool valid = live && i < cnt;
+                const RecTerm t = rec_term(r[J], G, A, D);
+                if constexpr (kTime) {
+                    double gk = (double)w[J] * kap * (Pm * m.inv_tm - Ps * m.inv_ts);
+                    gk = fma(tn.mu, tn.vs, gk);
+                    gk = fma(t.mu, t.ve, gk);
+                    ca[J] = valid ? gk : 0.0;
+                }
+                const long long gq = llrint(kap * (Pm - Ps) * sc);
+                const int at = row_bcast<L>(me.lo) + rl;
+                if (valid) atomicAdd(&s_gw[at], (unsigned long long)gq);
+                if (__ballot(inext == i)) {       // spikes between events i + 1 and i
+                    asm volatile("");
+                    if (inext == i) {
+                        const double tk = (double)te[k1 - i];
+                        if (burst) {
+                            while (sp > 0 && ks[sp - 1] == k1 - i) {
+                                --sp;
+                                gsp[sp] += (float)(sk * Pm * exp(-(tk - (double)ts[sp]) * m.inv_tm));
+                            }
+                            inext = sp > 0 && ks[sp - 1] >= k0 ? k1 - ks[sp - 1] : -1;
+                        } else {
+                            int nx = 0x7fffffff;
+#pragma unroll
+                            for (int u = 0; u < kRegPre; ++u) {
+                                if (pk[u] == i) pg[u] += (float)(sk * Pm * exp(-(tk - (double)pt[u]) * m.inv_tm));
+                                else if (pk[u] > i) nx = min(nx, pk[u]);
+                            }
+                            inext = nx;
+                        }
+                    }
+                }
+                Pm = fma(t.mu, t.em, Pm * A);
+                Ps = fma(t.mu, t.es, Ps * D);
+                tn = t;
+            };
+            one(std::integral_constant<int, 0>{}); one(std::integral_constant<int, 1>{});
+            one(std::integral_constant<int, 2>{}); one(std::integral_constant<int, 3>{});
+            one(std::integral_constant<int, 4>{}); one(std::integral_constant<int, 5>{});
+            one(std::integral_constant<int, 6>{}); one(std::integral_constant<int, 7>{});
+            if constexpr (kTime) {
+                const double sum = row_sum8(ca, lane);
+                const int i = i0 + rl / 2;
+                if ((rl & 1) == 0 && i < cnt) gt[-i] = sum;
+            }
+        };
+        // 16 events at a time; the next eight's weights and records, and the
+        // next 16's decays and sources, are in flight
+        using H0 = std::integral_constant<int, 0>;
+        using H1 = std::integral_constant<int, 1>;
+        int most = cnt;
+        most = max(most, __shfl_xor(most, 16, kWave));
+        most = max(most, __shfl_xor(most, 32, kWave));
+        most = __builtin_amdgcn_readfirstlane(most);
+        Meta m0 = load_meta(0), m1 = load_meta(1);
+        float wa[kGrp], wb[kGrp];
+        float2 ra[kGrp], rbuf[kGrp];
+        load_half(m0, H0{}, wa, ra);
+        for (int i0 = 0; i0 < most; i0 += kTileN) {
+            const Meta m2 = load_meta(i0 / kTileN + 2);
+            load_half(m0, H1{}, wb, rbuf);
+            half_walk(i0, m0, H0{}, wa, ra);
+            load_half(m1, H0{}, wa, ra);
+            half_walk(i0 + kGrp, m0, H1{}, wb, rbuf);
+            m0 = m1;
+            m1 = m2;
+        }
+        if (!burst) {
+#pragma unroll
+            for (int u = 0; u < kRegPre; ++u)
+                if (pk[u] >= 0) gsp[sp - 1 - u] = pg[u];
+        }
+    }
+    __syncthreads();
+    for (int x = (int)threadIdx.x; x < C_in * kTileN; x += kWave * kTileWaves) {
+        const int c = x / kTileN, nn = (int)blockIdx.x * kTileN + x % kTileN;
+        const unsigned long long v = s_gw[x];
+        if (v != 0ull && nn < N) atomicAdd((unsigned long long*)&gw[(size_t)c * N + nn], v);
+    }
+}
+
+// Whether a call's dL/dW is summed in LDS (k_regg_tile): the block fits, and the
+// walk is long enough to pay for clearing and adding the blocks (C_in x N elements
+// per slice).  Whole calls, global atomics against LDS: 1.0 M terms (B = 4,
+// 1000 events, N = 256) 81 against 93 us, 2.5 M 103 against 119 us, 8.2 M
+// (B = 8, 2000 events, N = 512) 131 against 122 us, 41 M 434 against 345 us.
+constexpr size_t kLdsMax = (size_t)160 << 10;        // LDS per CU
+constexpr int kCUs = 256;
+
+static bool reg_tiled(int B, int E_max, int C_in, int N)
+{
+    return (size_t)C_in * kTileRow <= kLdsMax && (size_t)B * E_max * N >= ((size_t)1 << 22);
+}
+
 // Fixed point -> float32 dL/dW; dL/dt summed over the tiles in order (0 past
 // each sample's last event).
 __global__ __launch_bounds__(256) void k_regg_convert(const long long* __restrict__ gw,
@@ -2354,7 +2572,7 @@ static RegGradLayout reg_grad_layout(int B, int E_max, int C_in, int N)
     size_t off = G.r.total;
     auto take = [&](size_t bytes) { size_t o = off; off += (bytes + 255) & ~(size_t)255; return o; };
     const size_t BS = (size_t)B * G.r.f.S;
-    const int tiles = (N + kWave - 1) / kWave;
+    const int tn = reg_tiled(B, E_max, C_in, N) ? kTileN : kWave, tiles = (N + tn - 1) / tn;
     G.rec = take((size_t)B * ((size_t)E_max + 1) * N * sizeof(float2));
     G.counts = take((size_t)B * N * sizeof(double2));
     G.gates = take((size_t)N * sizeof(double2));
@@ -2414,6 +2632,8 @@ extern "C" int lif_spike_count_reg_backward(const float* ev_t, const int32_t* ev
     double* ub = (double*)(base + R.ub);
     double* ob = (double*)(base + R.ob);
     int32_t* st = (int32_t*)(base + R.status);
+    const bool tiled = reg_tiled(B, E_max, C_in, N_out);
+    const int gtn = tiled ? kTileN : kWave, gtiles = (N_out + gtn - 1) / gtn;   // of the walk back
     float2* rec = (float2*)(base + G.rec);
     double2* counts = (double2*)(base + G.counts);
     double2* gates = (double2*)(base + G.gates);
@@ -2458,15 +2678,38 @@ extern "C" int lif_spike_count_reg_backward(const float* ev_t, const int32_t* ev
     if (items_max > 0) {
         TIMED_LAUNCH("regg_carry", k_regg_carry, dim3((unsigned)tl, (unsigned)B), dim3(kWave), 0, stream, ev_n, E_max,
                      N_out, R.f.S, P.segm, local, coef, cin);
-        TIMED_LAUNCH("regg_walk", k_regg_walk, dim3(wblocks), dim3(kWave * kWalkWaves), 0, stream, ev_t, ev_src, ev_n,
-                     B, E_max, R.f.E_pad, WT, C_in, N_out, tl, R.f.S, (int)items_max, m, P.dec, rec, coef, cin, out_t,
-                     out_n, out_k, scale, gw, gtp, grad_spike);
+        if (tiled) {
+            const size_t lds = (size_t)C_in * kTileRow;
+            const long long quads = ((long long)B * R.f.S + 3) / 4;
+            const int per = (int)((quads + kTileWaves - 1) / kTileWaves);
+            // slices of the items per tile: the fewest rounds of one workgroup per CU
+            // in units of a slice (a workgroup's sums cost C_in x 16 atomics, so
+            // no more than four rounds, and every wave has an item)
+            int slices = 1;
+            for (int q = 2; q <= per && (long long)q * gtiles <= 4 * kCUs; ++q)
+                if ((long long)((gtiles * q + kCUs - 1) / kCUs) * slices < (long long)((gtiles * slices + kCUs - 1) / kCUs) * q)
+                    slices = q;
+            auto walk = [&](auto kern) {
+                if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
+                    hipSuccess)
+                    return false;
+                TIMED_LAUNCH("regg_walk", kern, dim3((unsigned)gtiles, (unsigned)slices), dim3(kWave * kTileWaves), lds,
+                             stream, ev_t, ev_src, ev_n, B, E_max, R.f.E_pad, WT, C_in, N_out, R.f.S, m, P.dec, rec,
+                             coef, cin, out_t, out_n, out_k, scale, gw, gtp, grad_spike);
+                return true;
+            };
+            if (!(grad_ev_t ? walk(k_regg_tile<true>) : walk(k_regg_tile<false>))) return LIF_ERR_HIP;
+        } else {
+            TIMED_LAUNCH("regg_walk", k_regg_walk, dim3(wblocks), dim3(kWave * kWalkWaves), 0, stream, ev_t, ev_src, ev_n,
+                         B, E_max, R.f.E_pad, WT, C_in, N_out, tl, R.f.S, (int)items_max, m, P.dec, rec, coef, cin, out_t,
+                         out_n, out_k, scale, gw, gtp, grad_spike);
+        }
     }
     work = nW > (size_t)B * E_max ? nW : (size_t)B * E_max;
     blocks = (work + 255) / 256;
     blocks = blocks < 1 ? 1 : (blocks > 2048 ? 2048 : blocks);
     TIMED_LAUNCH("regg_convert", k_regg_convert, dim3((unsigned)blocks), dim3(256), 0, stream, gw, scale, nW, grad_WT,
-                 gtp, ev_n, B, E_max, tl, grad_ev_t);
+                 gtp, ev_n, B, E_max, gtiles, grad_ev_t);
     return check_launch();
 }
 

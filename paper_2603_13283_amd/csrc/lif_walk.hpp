@@ -208,4 +208,27 @@ __device__ __forceinline__ double group_sum8(const double (&v)[kGrp], int lane)
     return group_sum4(r4, lane);
 }
 
+// The lane's own a or b (hi: b) plus the other one of its partner of the row
+// under the DPP control Ctrl, an exchange that flips the bit that hi tests.
+template <int Ctrl>
+__device__ __forceinline__ double row_fold(double a, double b, bool hi)
+{
+    const double own = hi ? b : a;
+    const unsigned long long u = (unsigned long long)__double_as_longlong(hi ? a : b);
+    const unsigned x = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)u, Ctrl, 0xf, 0xf, true);
+    const unsigned y = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), Ctrl, 0xf, 0xf, true);
+    return own + __longlong_as_double((long long)(((unsigned long long)y << 32) | x));
+}
+
+// Sums of v[0..7] over each row of 16 lanes: a lane ends with the sum of v[j],
+// j = its index in the row over 2.
+__device__ __forceinline__ double row_sum8(const double (&v)[kGrp], int lane)
+{
+    const bool b3 = lane & 8, b2 = lane & 4, b1 = lane & 2;
+    const double r0 = row_fold<0x128>(v[0], v[4], b3), r1 = row_fold<0x128>(v[1], v[5], b3);   // rotate by 8
+    const double r2 = row_fold<0x128>(v[2], v[6], b3), r3 = row_fold<0x128>(v[3], v[7], b3);
+    const double q0 = row_fold<0x141>(r0, r2, b2), q1 = row_fold<0x141>(r1, r3, b2);           // half-row mirror
+    return dpp_sum<0xb1>(row_fold<0x1b>(q0, q1, b1));                     // quad reverse, then neighbours
+}
+
 }  // namespace lif

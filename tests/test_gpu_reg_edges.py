@@ -1,7 +1,8 @@
 """GPU parity of the spike-count regularisers' loss and gradient at the edges of
 their walks, against the float64 oracle (oracle/loss.py) on identical inputs:
 one neuron and sample, batches and layers one past the tiles of 16 and 64,
-queues around the segments of 128 events, ratios of the time constants that
+queues around the segments of 128 events, long padded queues (dL/dW in LDS up
+to 1280 channels, by global atomics past them), ratios of the time constants that
 are a whole number and not, with and without the input times' gradient."""
 import numpy as np
 import pytest
@@ -31,18 +32,26 @@ def _dev(torch, a):
 # decays (relative 2^-22 at the argmax, where V' = 0): 1e-5.  The gradients keep
 # the parity bar's 1e-4, with the band of compare_grad_band where the float32
 # hand-over of the spike times itself moves the oracle's gradient.
-@pytest.mark.parametrize("B,C,N,n_events,tau_syn,t_end,time_grad", [
-    (1, 3, 1, 129, 0.005, np.inf, True),
-    (17, 40, 17, 130, 0.005, 0.3, True),
-    (5, 1, 65, 127, 0.01, np.inf, False),
-    (3, 70, 33, 400, 0.0066, 0.5, True),
-    (2, 1200, 20, 500, 0.004, np.inf, True),
-    (2, 1300, 20, 500, 0.005, np.inf, True),
+@pytest.mark.parametrize("B,C,N,n_events,tau_syn,t_end,time_grad,e_max", [
+    (1, 3, 1, 129, 0.005, np.inf, True, 0),
+    (17, 40, 17, 130, 0.005, 0.3, True, 0),
+    (5, 1, 65, 127, 0.01, np.inf, False, 0),
+    (3, 70, 33, 400, 0.0066, 0.5, True, 0),
+    (2, 1200, 20, 500, 0.004, np.inf, True, 0),
+    (1, 3, 1, 129, 0.005, np.inf, True, 1 << 22),
+    (17, 40, 17, 130, 0.005, 0.3, True, 20000),
+    (5, 1, 65, 127, 0.01, np.inf, False, 20000),
+    (3, 70, 33, 400, 0.0066, 0.5, True, 50000),
+    (2, 1280, 48, 500, 0.004, np.inf, True, 50000),
+    (2, 1281, 48, 500, 0.005, np.inf, True, 50000),
 ])
-def test_regulariser_edges(env, B, C, N, n_events, tau_syn, t_end, time_grad):
+def test_regulariser_edges(env, B, C, N, n_events, tau_syn, t_end, time_grad, e_max):
     torch, lif = env
     cfg = W.random_small(60 + N, B=B, C=C, N=N, n_events=n_events, T=0.25, gain=6.0 if C > 3 else 1.5)
     ev, WT = cfg.events, cfg.layers[0].WT
+    if e_max:
+        pad = ((0, 0), (0, e_max - ev.E_max))
+        ev = W.EventBatch(np.pad(ev.ev_t, pad, constant_values=np.inf), np.pad(ev.ev_src, pad), ev.ev_n)
     kw = dict(s_max=32, t_end=t_end, tau_syn=tau_syn)
     P = oracle.LifParams(**kw)
     r = oracle.forward(ev.ev_t, ev.ev_src, ev.ev_n, WT, P)
