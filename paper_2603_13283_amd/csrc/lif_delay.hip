@@ -43,6 +43,8 @@
 #include "lif_reg.hpp"
 #include "lif_scan.hpp"
 
+#include <type_traits>
+
 namespace lif {
 
 constexpr int kQThreads = 256;
@@ -559,6 +561,7 @@ __global__ __launch_bounds__(kWave * kDlyWaves) void k_dly_adjoint(
 // once per workgroup, nonzero entries only.
 constexpr int kDlyLdsWaves = 8;
 constexpr int kDlyLdsMaxC = 4096;
+constexpr size_t kDlyLdsBytes = (size_t)64 << 10;     // dynamic LDS without an attribute
 
 __global__ __launch_bounds__(kWave * kDlyLdsWaves) void k_dly_adjoint_lds(
     const float* __restrict__ q_t, const int32_t* __restrict__ q_k, const int32_t* __restrict__ ev_src,
@@ -718,19 +721,62 @@ static void launch_gt_gather(const int32_t* q_k, const int32_t* ev_n, const int3
 // ---------------------------------------------------------------------------
 constexpr int kDRegWaves = 4;
 
-__global__ __launch_bounds__(kWave * kDRegWaves) void k_dreg_walk(
+// The synaptic decay over a gap L of membrane decay A: a power of A when
+// tau_m / tau_s = kP + 1 (kP = 0: its own exponential).
+template <int kP>
+__device__ __forceinline__ double syn_decay(const Model& m, double A, double L)
+{
+    if constexpr (kP == 0) return exp(-L * m.inv_ts);
+    else return syn_power<kP>(A);
+}
+
+// f called with Model::p_int as a compile-time constant.
+template <class F>
+static auto with_p(int p_int, F f)
+{
+    switch (p_int) {
+    case 1: return f(std::integral_constant<int, 1>{});
+    case 2: return f(std::integral_constant<int, 2>{});
+    case 3: return f(std::integral_constant<int, 3>{});
+    case 4: return f(std::integral_constant<int, 4>{});
+    default: return f(std::integral_constant<int, 0>{});
+    }
+}
+
+// kCol: a workgroup takes one neuron of kDRegWaves samples, with the neuron's
+// column of W^T in LDS; else kDRegWaves (sample, neuron) pairs, W^T from memory.
+// A step's 64 weights are 64 cache lines in memory, and those lookups bounded the
+// walk, not its arithmetic: 700 -> 512, B = 128, 10 k events: 7.75 -> 6.95 ms with
+// the column in LDS, -> 5.66 ms at five waves per SIMD (four before, 99 VGPRs);
+// now VALU issue.  (Powers for the synaptic decays and one scan of both maps
+// took 20 % of the instructions and no time before the column was in LDS.)
+template <int kP, bool kCol>
+__global__ __launch_bounds__(kWave * kDRegWaves, 5) void k_dreg_walk(
     const float* __restrict__ q_t, const int32_t* __restrict__ q_k, const int32_t* __restrict__ ev_src,
     const int32_t* __restrict__ ev_n, int B, int E_max, const float* __restrict__ WT, int C_in, int N, Model m,
     const float* __restrict__ out_t, const int32_t* __restrict__ out_n, const int32_t* __restrict__ out_k,
     double* __restrict__ ub, double* __restrict__ ob, float* __restrict__ under, float* __restrict__ over,
-    double2* __restrict__ counts, double* __restrict__ vpmax, float2* __restrict__ rec)
+    double2* __restrict__ counts, double* __restrict__ vpmax, float2* __restrict__ rec, int nbg)
 {
+    extern __shared__ float s_col[];               // kCol: [C_in]
     const int lane = (int)threadIdx.x % kWave;
     // wave-uniform (scalar registers): the neuron's spike list is read with
     // scalar loads, which do not wait behind the queue loads in flight
-    const size_t item = (size_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * kDRegWaves + threadIdx.x / kWave));
-    if (item >= (size_t)B * N) return;
-    const int b = (int)(item / (size_t)N), n = (int)(item % (size_t)N);
+    size_t item;
+    int b, n;
+    if constexpr (kCol) {
+        n = (int)(blockIdx.x / (unsigned)nbg);
+        b = __builtin_amdgcn_readfirstlane((int)(blockIdx.x % (unsigned)nbg) * kDRegWaves + (int)threadIdx.x / kWave);
+        for (int j = (int)threadIdx.x; j < C_in; j += kWave * kDRegWaves) s_col[j] = WT[(size_t)j * (size_t)N + n];
+        __syncthreads();
+        if (b >= B) return;
+        item = (size_t)b * (size_t)N + n;
+    } else {
+        item = (size_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * kDRegWaves + threadIdx.x / kWave));
+        if (item >= (size_t)B * N) return;
+        b = (int)(item / (size_t)N);
+        n = (int)(item % (size_t)N);
+    }
     const int nb = clamp_count(ev_n[b], E_max);
     const float* qa = q_t + item * (size_t)E_max;
     const int32_t* qi = q_k + item * (size_t)E_max;
@@ -777,7 +823,10 @@ __global__ __launch_bounds__(kWave * kDRegWaves) void k_dreg_walk(
         k_ = o ? min(max(qi[rr], 0), nb - 1) : 0;
     };
     auto ld_j = [&](int k_) { return clamp_src(src[k_], C_in); };
-    auto ld_w = [&](int ff, int j_) { return ff + lane < nb ? WT[(size_t)j_ * (size_t)N + n] : 0.0f; };
+    auto ld_w = [&](int ff, int j_) {
+        if constexpr (kCol) return s_col[j_];      // (past the last event: not used)
+        else return ff + lane < nb ? WT[(size_t)j_ * (size_t)N + n] : 0.0f;
+    };
     float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f, w0 = 0.0f;
     int k0 = 0, k1 = 0, k2 = 0, j1 = 0;
     if (nb > 0) {
@@ -803,26 +852,15 @@ __global__ __launch_bounds__(kWave * kDRegWaves) void k_dreg_walk(
         j1 = j2;
         a2 = a3;
         k2 = k3;
-        double ap = __shfl_up((double)af, 1, kWave);         // arrival of event r - 1
-        if (lane == 0) ap = a_prev;
+        const double ap = wave_shr1((double)af, a_prev);      // arrival of event r - 1
         const double a = (double)af;
         const double L = a - ap;
-        double A = 1.0, D = 1.0;
-        if (ok) {
-            A = exp(-L * m.inv_tm);
-            D = exp(-L * m.inv_ts);
-        }
+        const double A = ok ? exp(-L * m.inv_tm) : 1.0;
+        const double D = syn_decay<kP>(m, A, ok ? L : 0.0);
         double aU = A, bU = ok ? (double)w : 0.0, aJ = D, bJ = bU;
-        scan_maps_up(aU, bU, lane);
-        scan_maps_up(aJ, bJ, lane);
-        double eaU = __shfl_up(aU, 1, kWave), ebU = __shfl_up(bU, 1, kWave);
-        double eaJ = __shfl_up(aJ, 1, kWave), ebJ = __shfl_up(bJ, 1, kWave);
-        if (lane == 0) {
-            eaU = 1.0;
-            ebU = 0.0;
-            eaJ = 1.0;
-            ebJ = 0.0;
-        }
+        scan_pair<kP, true>(aU, bU, aJ, bJ, lane);
+        const double eaU = wave_shr1(aU, 1.0), ebU = wave_shr1(bU, 0.0);
+        const double eaJ = wave_shr1(aJ, 1.0), ebJ = wave_shr1(bJ, 0.0);
         const double U0 = fma(eaU, U, ebU), J0 = fma(eaJ, J, ebJ);     // at interval r's start
         // the deficit at interval r's start: the carried one decayed over
         // events f .. r - 1 (the product eaU), plus the spikes of intervals
@@ -842,14 +880,14 @@ __global__ __launch_bounds__(kWave * kDRegWaves) void k_dreg_walk(
         // the carry: the state after the step's last event, its arrival and
         // the deficit there
         const double Un = fma(aU, U, bU), Jn = fma(aJ, J, bJ);
-        const double a_last = __shfl(a, lv, kWave);
-        double Dn = Dc * __shfl(aU, lv, kWave);
+        const double a_last = read_lane_double(a, lv);
+        double Dn = Dc * read_lane_double(aU, lv);
         while (sp < ns && sk[sp] <= f + lv) {
             Dn += m.dth * exp(-(a_last - (double)st[sp]) * m.inv_tm);
             ++sp;
         }
-        U = __shfl(Un, lv, kWave);
-        J = __shfl(Jn, lv, kWave);
+        U = read_lane_double(Un, lv);
+        J = read_lane_double(Jn, lv);
         Dc = Dn;
         a_prev = a_last;
     }
@@ -932,12 +970,13 @@ __global__ __launch_bounds__(kDlyScaleThreads) void k_dregg_scale(const double* 
     }
 }
 
-// The backward walk of one (sample, neuron) item; add_wd(j, dL/dw_j,
+// The backward walk of one (sample, neuron) item; ld_wj(j) is its weight from
+// channel j, add_wd(j, dL/dw_j,
 // dL/dd_j) takes the weight and delay terms of an event from channel j.
-template <class AddWD>
+template <int kP, class LdW, class AddWD>
 __device__ __forceinline__ void dregg_walk(size_t item, const float* __restrict__ q_t,
                                            const int32_t* __restrict__ q_k, const int32_t* __restrict__ ev_src,
-                                           const int32_t* __restrict__ ev_n, int E_max, const float* __restrict__ WT,
+                                           const int32_t* __restrict__ ev_n, int E_max, LdW ld_wj,
                                            int C_in, int N, const Model& m, const float* __restrict__ out_t,
                                            const int32_t* __restrict__ out_n, const int32_t* __restrict__ out_k,
                                            float2* rec, const double2* __restrict__ coef,
@@ -945,7 +984,7 @@ __device__ __forceinline__ void dregg_walk(size_t item, const float* __restrict_
                                            int32_t* __restrict__ tcnt, float* __restrict__ grad_spike)
 {
     const int lane = (int)threadIdx.x % kWave;
-    const int b = (int)(item / (size_t)N), n = (int)(item % (size_t)N);
+    const int b = (int)(item / (size_t)N);
     const int nb = clamp_count(ev_n[b], E_max);
     const double2 G = coef[item];
     const bool live = nb > 0 && (G.x != 0.0 || G.y != 0.0);
@@ -980,7 +1019,7 @@ __device__ __forceinline__ void dregg_walk(size_t item, const float* __restrict_
         rc_ = o ? rb[rr] : make_float2(0.0f, 0.0f);
     };
     auto ld_j = [&](int k_) { return clamp_src(src[k_], C_in); };
-    auto ld_w = [&](int ff, int j_) { return ff >= 0 && ff + lane < nb ? WT[(size_t)j_ * (size_t)N + n] : 0.0f; };
+    auto ld_w = [&](int ff, int j_) { return ff >= 0 && ff + lane < nb ? ld_wj(j_) : 0.0f; };
     const int ftop = ((nb - 1) / kWave) * kWave;
     float a0, a1, a2, w0;
     int k0, k1, k2, j0, j1;
@@ -1011,14 +1050,11 @@ __device__ __forceinline__ void dregg_walk(size_t item, const float* __restrict_
         a1 = a2; k1 = k2; j1 = j2; c1 = c2;
         a2 = a3; k2 = k3; c2 = c3;
         const double a = (double)af;
-        double A = 1.0, D = 1.0;
-        RecTerm t{0.0, 0.0, 0.0, 0.0, 0.0};
-        if (ok) {
-            const double L = a - ap;
-            A = exp(-L * m.inv_tm);
-            D = exp(-L * m.inv_ts);
-            t = rec_term(rc, G, A, D);                    // interval r, closed by event r
-        }
+        const double L = a - ap;
+        const double A = ok ? exp(-L * m.inv_tm) : 1.0;
+        const double D = syn_decay<kP>(m, A, ok ? L : 0.0);
+        // interval r, closed by event r (past the last event the record is zero)
+        const RecTerm t = rec_term(rc, G, A, D);
         // the record after event r: lane r + 1's, or the carried one at the top
         RecTerm tx;
         tx.mu = wave_shl1(t.mu, 0.0);
@@ -1029,8 +1065,7 @@ __device__ __forceinline__ void dregg_walk(size_t item, const float* __restrict_
         }
         // P at event r: the maps of lanes r + 1 .. hi applied to P at event hi
         double am = A, bm = t.mu * t.em, as = D, bs = t.mu * t.es;
-        scan_maps_down(am, bm, lane);
-        scan_maps_down(as, bs, lane);
+        scan_pair<kP, false>(am, bm, as, bs, lane);
         const double xam = wave_shl1(am, 1.0), xbm = wave_shl1(bm, 0.0);
         const double xas = wave_shl1(as, 1.0), xbs = wave_shl1(bs, 0.0);
         const double Pmr = fma(xam, Pm, xbm), Psr = fma(xas, Ps, xbs);
@@ -1057,6 +1092,7 @@ __device__ __forceinline__ void dregg_walk(size_t item, const float* __restrict_
 }
 
 // dL/dW and dL/dD to global memory (C_in > kDlyLdsMaxC).
+template <int kP>
 __global__ __launch_bounds__(kWave * kDRegWaves) void k_dregg_walk(
     const float* __restrict__ q_t, const int32_t* __restrict__ q_k, const int32_t* __restrict__ ev_src,
     const int32_t* __restrict__ ev_n, int B, int E_max, const float* __restrict__ WT, int C_in, int N, Model m,
@@ -1074,12 +1110,17 @@ __global__ __launch_bounds__(kWave * kDRegWaves) void k_dregg_walk(
         fx_add(&gw[wi], vw, sW);
         if (gd) fx_add(&gd[wi], vd, sD);
     };
-    dregg_walk(item, q_t, q_k, ev_src, ev_n, E_max, WT, C_in, N, m, out_t, out_n, out_k, rec, coef, scale, add_wd,
+    auto ld_wj = [&](int j) { return WT[(size_t)j * (size_t)N + n]; };
+    dregg_walk<kP>(item, q_t, q_k, ev_src, ev_n, E_max, ld_wj, C_in, N, m, out_t, out_n, out_k, rec, coef, scale, add_wd,
                tcnt, grad_spike);
 }
 
 // C_in <= kDlyLdsMaxC: one workgroup per (neuron, kDlyLdsWaves samples), the
 // neuron's dL/dW and dL/dD column summed in LDS as in k_dly_adjoint_lds.
+// kCol: with the column of W^T there too, unless the queues are shorter than it
+// (as in launch_dreg_walk): 700 -> 512, B = 128, 10 k events, 8.28 -> 5.7 ms, now
+// bound by VALU issue.
+template <int kP, bool kCol>
 __global__ __launch_bounds__(kWave * kDlyLdsWaves) void k_dregg_walk_lds(
     const float* __restrict__ q_t, const int32_t* __restrict__ q_k, const int32_t* __restrict__ ev_src,
     const int32_t* __restrict__ ev_n, int B, int E_max, const float* __restrict__ WT, int C_in, int N, Model m,
@@ -1091,11 +1132,13 @@ __global__ __launch_bounds__(kWave * kDlyLdsWaves) void k_dregg_walk_lds(
     extern __shared__ long long s_wd[];            // [C_in] dL/dW sums, then [C_in] dL/dD sums
     long long* s_w = s_wd;
     long long* s_d = s_wd + C_in;
+    float* s_col = reinterpret_cast<float*>(s_wd + 2 * (size_t)C_in);   // kCol: [C_in]
     const int n = (int)(blockIdx.x / (unsigned)nbg), bg = (int)(blockIdx.x % (unsigned)nbg);
     const int tid = (int)threadIdx.x;
     for (int j = tid; j < C_in; j += (int)blockDim.x) {
         s_w[j] = 0;
         s_d[j] = 0;
+        if constexpr (kCol) s_col[j] = WT[(size_t)j * (size_t)N + n];
     }
     __syncthreads();
     const int b = __builtin_amdgcn_readfirstlane(bg * kDlyLdsWaves + tid / kWave);
@@ -1106,7 +1149,11 @@ __global__ __launch_bounds__(kWave * kDlyLdsWaves) void k_dregg_walk_lds(
             atomicAdd((unsigned long long*)&s_w[j], (unsigned long long)llrint(vw * sW));
             if (want_d) atomicAdd((unsigned long long*)&s_d[j], (unsigned long long)llrint(vd * sD));
         };
-        dregg_walk((size_t)b * N + n, q_t, q_k, ev_src, ev_n, E_max, WT, C_in, N, m, out_t, out_n, out_k, rec, coef,
+        auto ld_wj = [&](int j) {
+            if constexpr (kCol) return s_col[j];
+            else return WT[(size_t)j * (size_t)N + n];
+        };
+        dregg_walk<kP>((size_t)b * N + n, q_t, q_k, ev_src, ev_n, E_max, ld_wj, C_in, N, m, out_t, out_n, out_k, rec, coef,
                    scale, add_wd, tcnt, grad_spike);
     }
     __syncthreads();
@@ -1347,9 +1394,21 @@ static void launch_dreg_walk(const float* q_t, const int32_t* q_k, const int32_t
 {
     const size_t nn = (size_t)B * N;
     if (nn == 0) return;
-    TIMED_LAUNCH("dreg_walk", k_dreg_walk, dim3((unsigned)((nn + kDRegWaves - 1) / kDRegWaves)),
-                 dim3(kWave * kDRegWaves), 0, stream, q_t, q_k, ev_src, ev_n, B, E_max, WT, C_in, N, m, out_t, out_n,
-                 out_k, ub, ob, under, over, counts, vpmax, rec);
+    with_p(m.p_int, [&](auto p) {
+        constexpr int kP = decltype(p)::value;
+        auto walk = [&](auto kern, size_t blocks, int waves, size_t lds, int nbg) {
+            TIMED_LAUNCH("dreg_walk", kern, dim3((unsigned)blocks), dim3(kWave * waves), lds, stream, q_t, q_k, ev_src,
+                         ev_n, B, E_max, WT, C_in, N, m, out_t, out_n, out_k, ub, ob, under, over, counts, vpmax, rec,
+                         nbg);
+        };
+        const int nbg = (B + kDRegWaves - 1) / kDRegWaves;
+        const size_t col = (size_t)C_in * sizeof(float);
+        // the column costs C_in strided loads: not where a queue is shorter than
+        // that (4000 channels, 500 events, B = 16: 113 us without, 120 us with it)
+        if (B >= kDRegWaves && C_in <= min(kDlyLdsMaxC, E_max))
+            walk(k_dreg_walk<kP, true>, (size_t)N * nbg, kDRegWaves, col, nbg);
+        else walk(k_dreg_walk<kP, false>, (nn + kDRegWaves - 1) / kDRegWaves, kDRegWaves, 0, nbg);
+    });
 }
 
 }  // namespace lif
@@ -1426,18 +1485,26 @@ extern "C" int lif_spike_count_reg_delayed_backward(const float* q_t, const int3
         TIMED_LAUNCH("dregg_scale", k_dregg_scale, dim3(1), dim3(kDlyScaleThreads), 0, stream, musum, coef, vpmax, nn,
                      ev_n, B, E_max, N_out, m, wmax, scale);
         if (E_max > 0) {
-            if (C_in <= kDlyLdsMaxC) {
-                const int nbg = (B + kDlyLdsWaves - 1) / kDlyLdsWaves;
-                TIMED_LAUNCH("dregg_walk", k_dregg_walk_lds, dim3((unsigned)((size_t)N_out * nbg)),
-                             dim3(kWave * kDlyLdsWaves), (size_t)2 * C_in * sizeof(long long), stream, q_t, q_k,
-                             ev_src, ev_n, B, E_max, WT, C_in, N_out, m, out_t, out_n, out_k, rec, coef, scale, gw,
-                             grad_DT ? gd : nullptr, tcnt, grad_spike, nbg);
-            } else {
-                TIMED_LAUNCH("dregg_walk", k_dregg_walk, dim3((unsigned)((nn + kDRegWaves - 1) / kDRegWaves)),
-                             dim3(kWave * kDRegWaves), 0, stream, q_t, q_k, ev_src, ev_n, B, E_max, WT, C_in, N_out, m,
-                             out_t, out_n, out_k, rec, coef, scale, gw, grad_DT ? gd : nullptr, tcnt,
-                             grad_spike);
-            }
+            with_p(m.p_int, [&](auto p) {
+                constexpr int kP = decltype(p)::value;
+                if (C_in <= kDlyLdsMaxC) {
+                    const int nbg = (B + kDlyLdsWaves - 1) / kDlyLdsWaves;
+                    auto walk = [&](auto kern, size_t lds) {
+                        TIMED_LAUNCH("dregg_walk", kern, dim3((unsigned)((size_t)N_out * nbg)),
+                                     dim3(kWave * kDlyLdsWaves), lds, stream, q_t, q_k, ev_src, ev_n, B, E_max, WT,
+                                     C_in, N_out, m, out_t, out_n, out_k, rec, coef, scale, gw,
+                                     grad_DT ? gd : nullptr, tcnt, grad_spike, nbg);
+                    };
+                    const size_t sums = (size_t)2 * C_in * sizeof(long long), col = (size_t)C_in * sizeof(float);
+                    if (sums + col <= kDlyLdsBytes && C_in <= E_max) walk(k_dregg_walk_lds<kP, true>, sums + col);
+                    else walk(k_dregg_walk_lds<kP, false>, sums);
+                } else {
+                    TIMED_LAUNCH("dregg_walk", k_dregg_walk<kP>, dim3((unsigned)((nn + kDRegWaves - 1) / kDRegWaves)),
+                                 dim3(kWave * kDRegWaves), 0, stream, q_t, q_k, ev_src, ev_n, B, E_max, WT, C_in,
+                                 N_out, m, out_t, out_n, out_k, rec, coef, scale, gw, grad_DT ? gd : nullptr, tcnt,
+                                 grad_spike);
+                }
+            });
             if (grad_ev_t)
                 launch_gt_gather(q_k, ev_n, tcnt, (const long long*)rec, (size_t)E_max + 1, B, E_max, N_out, gt,
                                  stream);

@@ -84,4 +84,58 @@ __device__ __forceinline__ void scan_maps_down(double& a, double& b, int lane)
     }
 }
 
+// e^{-x/ts} from e^{-x/tm} when tau_m / tau_s = kP + 1.
+template <int kP>
+__device__ __forceinline__ double syn_power(double a)
+{
+    static_assert(kP >= 1 && kP <= 4);
+    const double a2 = a * a;
+    if constexpr (kP == 1) return a2;
+    else if constexpr (kP == 2) return a2 * a;
+    else if constexpr (kP == 3) return a2 * a2;
+    else return a2 * a2 * a;
+}
+
+// The scans of two maps (a, b) and (a^(kP + 1), c) together: the second's
+// factors are powers of the first's and are not carried (kP = 0: any factors
+// as, two separate scans).
+template <int kP, bool kUp>
+__device__ __forceinline__ void scan_pair(double& a, double& b, double& as, double& c, int lane)
+{
+    if constexpr (kP == 0) {
+        if constexpr (kUp) {
+            scan_maps_up(a, b, lane);
+            scan_maps_up(as, c, lane);
+        } else {
+            scan_maps_down(a, b, lane);
+            scan_maps_down(as, c, lane);
+        }
+    } else {
+        auto step = [&](double pa, double pb, double pc) {
+            b = fma(a, pb, b);
+            c = fma(syn_power<kP>(a), pc, c);
+            a *= pa;
+        };
+        constexpr int kShift = kUp ? 0x110 : 0x100;           // DPP row shift right / left
+        step(dpp_double<kShift + 1>(a, 1.0), dpp_double<kShift + 1>(b, 0.0), dpp_double<kShift + 1>(c, 0.0));
+        step(dpp_double<kShift + 2>(a, 1.0), dpp_double<kShift + 2>(b, 0.0), dpp_double<kShift + 2>(c, 0.0));
+        step(dpp_double<kShift + 4>(a, 1.0), dpp_double<kShift + 4>(b, 0.0), dpp_double<kShift + 4>(c, 0.0));
+        step(dpp_double<kShift + 8>(a, 1.0), dpp_double<kShift + 8>(b, 0.0), dpp_double<kShift + 8>(c, 0.0));
+        // the rows as in scan_maps_up and scan_maps_down
+        const int row = lane >> 4;
+        constexpr int l0 = kUp ? 15 : 16, l1 = kUp ? 47 : 48, l2 = kUp ? 31 : 32;
+        {
+            const double a0 = read_lane_double(a, l0), b0 = read_lane_double(b, l0), c0 = read_lane_double(c, l0);
+            const double a1 = read_lane_double(a, l1), b1 = read_lane_double(b, l1), c1 = read_lane_double(c, l1);
+            const bool low = row < 2;
+            if (((row & 1) != 0) == kUp) step(low ? a0 : a1, low ? b0 : b1, low ? c0 : c1);
+        }
+        {
+            const double a0 = read_lane_double(a, l2), b0 = read_lane_double(b, l2), c0 = read_lane_double(c, l2);
+            if ((row >= 2) == kUp) step(a0, b0, c0);
+        }
+        as = syn_power<kP>(a);
+    }
+}
+
 }  // namespace lif

@@ -80,3 +80,45 @@ def test_regulariser_edges(env, B, C, N, n_events, tau_syn, t_end, time_grad, e_
         compare_grad_band(gt.cpu().numpy(), gT, gT6, label="direct grad_t")
     else:
         assert gt is None
+
+
+# The delayed layer's walks: each whole ratio of the time constants and none, a
+# workgroup's samples (4 forward, 8 back) not full, W^T's columns in LDS (queues of
+# at least C_in events and 4 samples) and not, LDS too small for a column (3400).
+@pytest.mark.parametrize("B,C,N,n_events,tau_mem,tau_syn", [
+    (1, 20, 3, 65, 0.02, 0.01),
+    (5, 40, 9, 200, 0.015, 0.005),
+    (9, 30, 5, 128, 0.02, 0.004),
+    (6, 40, 9, 150, 0.02, 0.0066),
+    (4, 300, 5, 200, 0.02, 0.005),
+    (4, 3400, 2, 3500, 0.02, 0.005),
+])
+def test_delayed_regulariser_edges(env, B, C, N, n_events, tau_mem, tau_syn):
+    torch, lif = env
+    cfg = W.random_small(80 + N, B=B, C=C, N=N, n_events=n_events, T=0.25, gain=5.0)
+    ev, WT = cfg.events, cfg.layers[0].WT
+    DT = W.uniform_delays(80, C, N, d_max=0.05)
+    kw = dict(s_max=64, tau_mem=tau_mem, tau_syn=tau_syn)
+    P = oracle.LifParams(**kw)
+    r = oracle.forward_delayed(ev.ev_t, ev.ev_src, ev.ev_n, WT, DT, P)
+    r32 = r.rounded()
+    ct = float(np.median(r.out_n.mean(axis=0))) + 0.5
+    rp = OL.RegParams(c_target=ct, lam_reg=0.8, lam_over=0.3)
+    q_t, q_k = oracle.delay_queues(ev.ev_t, ev.ev_src, ev.ev_n, DT)
+    print(f"[case] delayed B={B} C={C} N={N} E_max={ev.E_max} tau={tau_mem}/{tau_syn} spikes={int(r.out_n.sum())}",
+          flush=True)
+    at32, at64 = (OL.spike_count_reg_delayed_grad(ev.ev_t, ev.ev_src, ev.ev_n, WT, q_t, q_k, x.out_t, r.out_k, r.out_n,
+                                                  P.tau_mem, P.tau_syn, P.v_th, P.v_reset, P.t_end, rp)
+                  for x in (r32, r))
+    t, s, n, w, d = (_dev(torch, a) for a in (ev.ev_t, ev.ev_src, ev.ev_n, WT, DT))
+    q = lif.delay_queues(t, s, n, d)
+    fwd = lif.ForwardOut(_dev(torch, r32.out_t.astype(np.float32)), _dev(torch, r.out_n),
+                         _dev(torch, r32.out_i.astype(np.float32)), None, _dev(torch, r.out_k))
+    loss, gs, gW, gD, gT = lif.spike_count_reg_delayed_backward(q, s, n, w, fwd, ct, 0.8, 0.3, lif.Params(**kw))
+    torch.cuda.synchronize()
+    for i in range(2):                        # inside the band of the hand-over, 1e-5 relative
+        lo, hi = sorted((at32[i], at64[i]))
+        assert lo - 1e-5 * abs(lo) - 1e-12 <= loss[i].item() <= hi + 1e-5 * abs(hi) + 1e-12
+    for got, j, label in ((gs, 5, "spike-time gradient"), (gW, 2, "direct grad_W"), (gD, 3, "direct grad_D"),
+                          (gT, 4, "direct grad_t")):
+        compare_grad_band(got.cpu().numpy(), at32[j], at64[j], label=f"delayed {label}")
