@@ -707,7 +707,7 @@ static void launch_gt_gather(const int32_t* q_k, const int32_t* ev_n, const int3
 //                 give each interval's no-reset start state from the step's
 //                 carried state; the reset deficit of the neuron's spikes is
 //                 the carried deficit decayed by the same products plus the
-//                 spikes of the step; V_max (reg_vmax_arg), the hinge sums and
+//                 spikes of the step; V_max (reg_vmax_in), the hinge sums and
 //                 counts, and the per-interval record.
 //   k_dregg_walk  backward: P_r = sum of the pseudo-spikes of the intervals
 //                 after event r (mu e^{-(argmax - a_r)/tm}, and with ts), by

@@ -2031,7 +2031,7 @@ extern "C" int lif_spike_count_reg(const float* ev_t, const int32_t* ev_src, con
 // by k_reg_walk on its forward walk, split by hinge so that the multipliers,
 // known only once the whole batch is walked, enter later), a reverse carry
 // over segments (k_regg_carry), and the walk back with the carry
-// (k_regg_walk).  dL/dW is added as 64-bit fixed-point integers (order
+// (k_regg_tile, k_regg_walk).  dL/dW is added as 64-bit fixed-point integers (order
 // free); dL/dt per neuron tile, the tiles added in order.
 // ---------------------------------------------------------------------------
 namespace lif {

@@ -1,5 +1,5 @@
-// lif_walk.hpp -- segment-walk helpers shared by the forward walks
-// (k_aggregate, k_check) and the backward adjoint walk (k_event_adjoint):
+// lif_walk.hpp -- segment-walk helpers shared by the walks of the forward
+// (k_aggregate, k_check) and of the regularisers, and sums over lanes:
 // work-item coordinates, per-wave staging of a segment's sources and decays,
 // and the weight gather of groups of events.
 #pragma once
