@@ -83,7 +83,9 @@ static BwdPlan bwd_plan(int B, int E_max, int C_in, int N)
     P.lds = P.nr <= kAdjMaxRanges;
     if (!P.lds) P.nr = 1;
     P.rows = (C_in + P.nr - 1) / P.nr;
-    P.nch = (E_max + kListChunk - 1) / kListChunk;
+    // (at least one chunk: the plan pass then writes every list's start, also of
+    // queues without room for an event, whose lists are empty)
+    P.nch = E_max > 0 ? (E_max + kListChunk - 1) / kListChunk : 1;
     // parts: enough (sample, part) units for four per wave of a full chip,
     // none longer than 1024 events and none much shorter than 128 (a unit
     // starts with a search in every neuron's spikes)

@@ -74,3 +74,23 @@ def test_adjoint_not_finite(env, n):
     # the bound of the fixed-point scale is not the same in the two calls
     assert torch.allclose(got[:, keep], base[:, keep], rtol=1e-5, atol=1e-6 * float(base.abs().max()))
     assert torch.isnan(gT[0]).any()
+
+
+@pytest.mark.parametrize("C", [1, 318, 319, 700])
+@pytest.mark.parametrize("time_grad", [True, False])
+def test_adjoint_empty_queues(env, C, time_grad):
+    """Queues without room for an event: dL/dW is zero whatever the workspace
+    held, on both sides of one channel range."""
+    torch, lif = env
+    B, N, P = 3, 70, lif.Params(s_max=8)
+    print(f"[case] empty queues C={C} time_grad={time_grad}", flush=True)
+    ev_t = torch.empty((B, 0), device="cuda:0")
+    ev_s = torch.empty((B, 0), dtype=torch.int32, device="cuda:0")
+    ev_n = torch.zeros(B, dtype=torch.int32, device="cuda:0")
+    WT = torch.ones((C, N), device="cuda:0")
+    out = lif.forward(ev_t, ev_s, ev_n, WT, P)
+    ws = torch.full((lif.lif_layer_backward_workspace_size(B, 0, C, N, P.c()),), 1, dtype=torch.uint8, device="cuda:0")
+    gW, gT = lif.backward(ev_t, ev_s, ev_n, WT, out, torch.ones_like(out.out_t), P, want_time_grad=time_grad, ws=ws)
+    torch.cuda.synchronize()
+    assert int(out.out_n.sum()) == 0 and not gW.any()
+    assert gT is None if not time_grad else gT.numel() == 0
