@@ -479,21 +479,22 @@ struct AdjArgs {
 
 // P at time tk from the R of a neuron's spikes s .. ns - 1 (its first spike is
 // entry so), exponentials and all: the general form of P = R H.  A spike whose
-// float32 time lies before tk counts with offset 0.  (A call: inlined, the
+// float32 time lies before tk counts with offset 0.  (len and inv_len are the
+// numbers that the table was built with: a spike time on a multiple of len may
+// fall on either side of it under any others.  A call: inlined, the
 // constants of its exponentials would hold registers all through the walk.)
-__device__ __noinline__ double2 p_at(const float* ts, const double2* rr, int s, int ns, double tk, double tau_m,
-                                     double tau_s)
+__device__ __noinline__ double2 p_at(const float* ts, const double2* rr, int s, int ns, double tk, double len,
+                                     double inv_len, double inv_tm, double inv_ts)
 {
-    const double len = kRefTs * tau_s, inv_tm = 1.0 / tau_m, inv_ts = 1.0 / tau_s;
     double am = 0.0, as = 0.0;
     double2 q1 = make_double2(0.0, 0.0);
     for (;; ++s) {
-        const double t1 = (double)ts[s], dr = ref_offset(t1, ref_index(t1, 1.0 / len), len);
+        const double t1 = (double)ts[s], dr = ref_offset(t1, ref_index(t1, inv_len), len);
         q1 = make_double2(rr[s].x * exp(dr * inv_tm), rr[s].y * exp(dr * inv_ts));       // Q_s
         const double du = t1 - tk;
         if (!(du < 0.0)) return make_double2(fma(q1.x, exp(-du * inv_tm), am), fma(q1.y, exp(-du * inv_ts), as));
         if (s + 1 >= ns) return make_double2(am + q1.x, as + q1.y);
-        const double t2 = (double)ts[s + 1], d2 = ref_offset(t2, ref_index(t2, 1.0 / len), len), dt = t2 - t1;
+        const double t2 = (double)ts[s + 1], d2 = ref_offset(t2, ref_index(t2, inv_len), len), dt = t2 - t1;
         am += q1.x - rr[s + 1].x * exp((d2 - dt) * inv_tm);                              // mu_s
         as += q1.y - rr[s + 1].y * exp((d2 - dt) * inv_ts);
     }
@@ -763,7 +764,7 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint(const AdjArgs a)
 #pragma unroll 1
                         for (int e = g * kGrp + ne - 1; e >= g * kGrp; --e) {
                             double2 P = make_double2(0.0, 0.0);
-                            if (sp < ns) P = p_at(a.out_t + so, a.r + so, sp, ns, (double)rl_f(cur.t, e), 1.0 / a.inv_tm, 1.0 / a.inv_ts);
+                            if (sp < ns) P = p_at(a.out_t + so, a.r + so, sp, ns, (double)rl_f(cur.t, e), a.len, a.inv_len, a.inv_tm, a.inv_ts);
                             add_w(fx_term<kWide>(P.x - P.y, ks), __builtin_amdgcn_readlane(row, e));
                             if constexpr (kTime) {
                                 const float we = __builtin_bit_cast(

@@ -52,6 +52,51 @@ def test_adjoint_long_and_late(env, B, C, N, n, T, gain, t0):
     print(f"[case] t0={t0} T={T} spikes={int(r32.out_n.sum())} rel(gW)={sW:.2e} rel(gT)={sT:.2e}", flush=True)
 
 
+def _handmade(torch, lif, label, ev_t, ev_src, WT, out_t, out_k, seed, **kw):
+    """The backward alone on a spike train given by hand, out_t and out_k
+    [B][N][S] with infinite times past the last spike."""
+    B, E = ev_t.shape
+    ev_n = np.full(B, E, np.int32)
+    rng = np.random.default_rng(seed)
+    valid = np.isfinite(out_t)
+    out_n = valid.sum(-1).astype(np.int32)
+    out_i = np.where(valid, 1.5 + rng.random(out_t.shape), 0.0).astype(np.float32)
+    g = (rng.standard_normal(out_t.shape) * valid).astype(np.float32)
+    S = out_t.shape[-1]
+    r = oracle.ForwardResult(out_t.astype(np.float64), out_i.astype(np.float64), out_n, None, None, None, out_k.astype(np.int32))
+    oW, oT = oracle.backward(ev_t, ev_src, ev_n, WT, r, g.astype(np.float64), oracle.LifParams(s_max=S, **kw))
+    d = [_dev(torch, a) for a in (ev_t, ev_src, ev_n, WT)]
+    fwd = lif.ForwardOut(_dev(torch, out_t.astype(np.float32)), _dev(torch, out_n), _dev(torch, out_i), None,
+                         _dev(torch, out_k.astype(np.int32)))
+    gW, gT = lif.backward(*d, fwd, _dev(torch, g), lif.Params(s_max=S, **kw))
+    torch.cuda.synchronize()
+    sW, sT = compare_grad(gW.cpu().numpy(), oW, label="gW"), compare_grad(gT.cpu().numpy(), oT, label="gT")
+    print(f"[case] {label} spikes={int(out_n.sum())} rel(gW)={sW:.2e} rel(gT)={sT:.2e}", flush=True)
+
+
+@pytest.mark.parametrize("tau_syn", [0.0038, 0.0076, 0.005])
+def test_adjoint_spikes_on_references(env, tau_syn):
+    """A stream over many references (multiples of 100 tau_s, to which the
+    exponentials are referred) with spikes at exactly such times: 25 of them
+    are 9.5 s and 19 s, which their reciprocals put on either side."""
+    torch, lif = env
+    rng = np.random.default_rng(64)
+    B, C, N, E = 2, 9, 66, 200
+    at = np.float32(2500 * tau_syn)
+    ev_t = np.sort(rng.random((B, E)) * 2 * at, -1).astype(np.float32)
+    ev_t[:, E // 2:] = np.maximum(ev_t[:, E // 2:], at)
+    ev_t[:, :E // 2] = np.minimum(ev_t[:, :E // 2], np.nextafter(at, np.float32(0)))
+    ev_t[:, E // 2 - 4:E // 2] = at - np.linspace(3, 0.5, 4, dtype=np.float32) * np.float32(tau_syn)
+    ev_t.sort(-1)
+    out_t = np.full((B, N, 2), np.inf)
+    out_k = np.zeros((B, N, 2), np.int32)
+    out_t[:, :, 0], out_k[:, :, 0] = at, E // 2
+    out_t[:, ::2, 1] = ev_t[:, -1:] + 0.5 * tau_syn
+    out_k[:, ::2, 1] = E
+    _handmade(torch, lif, f"tau_s={tau_syn}", ev_t, rng.integers(0, C, (B, E)).astype(np.int32),
+              rng.standard_normal((C, N)).astype(np.float32), out_t, out_k, 64, tau_syn=tau_syn)
+
+
 @pytest.mark.parametrize("n", [500, 5000])
 def test_adjoint_not_finite(env, n):
     """A NaN and an infinite upstream gradient on one neuron each leave every
