@@ -508,7 +508,8 @@ __device__ __noinline__ double2 p_at(const float* ts, const double2* rr, int s, 
 // spikes between the listed event before it and event k switches its R.  The
 // spikes that a group of kGrp events passes are looked up before the group, all
 // lanes together (at most two per lane).  A group where a lane passes more, or
-// one whose float32 time lies before the event below it, and a block of 64
+// one whose float32 time lies before the event below it, a group with events
+// after the time of a spike that they precede, and a block of 64
 // events over more than 3 len, go event by event through p_at.
 // kLds = false: dL/dW by global atomics; kTime: dL/dt wanted (else no weight is
 // read).
@@ -631,13 +632,16 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint(const AdjArgs a)
             };
             const int rmul = kLds ? kWave : a.N;
             double Rm = 0.0, Rs = 0.0;
+            float tc = INFINITY;                           // time of spike sp (none: infinite)
             float w[kGrp], wn[kGrp];
             int woff = cur.src * a.N * 4;
             load_w(woff, (cnt - 1) / kGrp, w);
             auto take = [&]() {                            // R of spike sp
                 Rm = Rs = 0.0;
+                tc = INFINITY;
                 if (sp < ns) {
-                    const double2 v = refer(a.r[so + sp], a.out_t[so + sp]);
+                    tc = a.out_t[so + sp];
+                    const double2 v = refer(a.r[so + sp], tc);
                     Rm = v.x;
                     Rs = v.y;
                 }
@@ -674,7 +678,9 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint(const AdjArgs a)
                     const int ne = min(kGrp, cnt - g * kGrp);
                     const bool pass = k1 > klo;
                     const bool any = __ballot(pass) != 0ull;
-                    bool any2 = false, slow = ref < 0;
+                    // (a handed-over spike time may lie before events that the
+                    // spike follows: their offsets count as 0)
+                    bool any2 = false, slow = ref < 0 || __ballot(tc < rl_f(cur.t, g * kGrp + ne - 1)) != 0ull;
                     int x1 = -1, x2 = -1;                  // R switched after event x of the group
                     double2 X1 = make_double2(0.0, 0.0), X2 = X1;
                     if (any && !slow) {
@@ -706,9 +712,11 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint(const AdjArgs a)
                             if (pass) {
                                 x1 = y1;
                                 X1 = refer(R1, t1);
+                                tc = t1;
                                 --sp;
                                 if (pass2) {
                                     X2 = refer(a.r[so + sp - 1], t2);
+                                    tc = t2;
                                     --sp;
                                 }
                                 refill();

@@ -97,6 +97,25 @@ def test_adjoint_spikes_on_references(env, tau_syn):
               rng.standard_normal((C, N)).astype(np.float32), out_t, out_k, 64, tau_syn=tau_syn)
 
 
+@pytest.mark.parametrize("C,n", [(40, 1500), (700, 3000)])
+@pytest.mark.parametrize("back", [2e-4, 5e-3])
+def test_adjoint_spike_times_before_their_events(env, C, n, back):
+    """Spike times moved back past some of the events that the spikes follow
+    (within a group of eight, across groups and blocks): out_k decides which
+    events count, with offsets of 0."""
+    torch, lif = env
+    B, N = 2, 70
+    cfg = W.random_small(65, B=B, C=C, N=N, n_events=n, T=0.5, gain=10.0, ragged=False)
+    ev, WT = cfg.events, cfg.layers[0].WT
+    r = oracle.forward(ev.ev_t, ev.ev_src, ev.ev_n, WT, oracle.LifParams(s_max=64)).rounded()
+    rng = np.random.default_rng(65)
+    t = r.out_t - np.where(rng.random(r.out_t.shape) < 0.5, rng.random(r.out_t.shape) * back, 0.0)
+    # (times stay in order, also in float32)
+    t = np.maximum.accumulate(np.maximum(t, 0.0).astype(np.float32), -1).astype(np.float64)
+    assert int((t < r.out_t).sum()) > 50
+    _handmade(torch, lif, f"C={C} back={back}", ev.ev_t, ev.ev_src, WT, t, r.out_k, 65)
+
+
 @pytest.mark.parametrize("n", [500, 5000])
 def test_adjoint_not_finite(env, n):
     """A NaN and an infinite upstream gradient on one neuron each leave every
