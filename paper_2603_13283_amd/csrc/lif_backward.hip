@@ -161,6 +161,13 @@ __device__ __forceinline__ ListEvent list_event(const Model& m, float t, int src
     return e;
 }
 
+// What a setup workgroup found: the largest finite sum_s |mu_s| of its neurons, and
+// whether one was not finite.
+struct BwdPart {
+    double mx;
+    int bad;
+};
+
 struct BwdLayout {
     BwdPlan P;
     size_t q, ns, part, scale, cnt, start, list, gw, gt, total;
@@ -176,7 +183,7 @@ static BwdLayout bwd_layout(int B, int E_max, int C_in, int N, int s_max)
     auto take = [&](size_t bytes) { size_t o = off; off += (bytes + 255) & ~(size_t)255; return o; };
     L.q = take((size_t)B * N * s_max * sizeof(double2));
     L.ns = take((size_t)B * N * sizeof(int32_t));
-    L.part = take(kSetupBlocks * sizeof(double));
+    L.part = take(kSetupBlocks * sizeof(BwdPart));
     L.scale = take(2 * sizeof(double));
     const bool lists = L.P.nr > 1;
     L.cnt = take(lists ? (size_t)B * L.P.nr * L.P.nch * sizeof(int32_t) : 0);
@@ -237,9 +244,8 @@ __device__ __forceinline__ double spike_suffix_sums(const Model& m, int ns, cons
 // fixed-point accumulators of dL/dW (where blocks are split) set to zero;
 // the suffix sums of every (sample, neuron)'s spike adjoints with its spike
 // count (0 when all its adjoints are exactly 0: such a neuron adds exactly 0
-// everywhere and is not walked; a NaN sum keeps it); per workgroup the largest
-// sum_s |mu_s| (NaN when one is NaN); and with one channel range the list of
-// every sample's events, else the events of each (sample, chunk) counted per
+// everywhere and is not walked; a NaN sum keeps it); per workgroup its BwdPart; and
+// with one channel range the list of every sample's events, else the events of each (sample, chunk) counted per
 // channel range, cnt[b][r][chunk], one wave per chunk.
 constexpr int kSetupThreads = 256;
 
@@ -247,7 +253,7 @@ __global__ __launch_bounds__(kSetupThreads) void k_bwd_setup(
     const float* __restrict__ ev_t, const int32_t* __restrict__ ev_src, const int32_t* __restrict__ ev_n, int B,
     int E_max, int C_in, int N, Model m, long long* __restrict__ gw, size_t nW, const float* __restrict__ out_t, const int32_t* __restrict__ out_n,
     const float* __restrict__ out_i, const int32_t* __restrict__ out_k, const float* __restrict__ grad_out_t,
-    double2* __restrict__ rtab, int32_t* __restrict__ ns_eff, double* __restrict__ part, int nr, int rows, int nch,
+    double2* __restrict__ rtab, int32_t* __restrict__ ns_eff, BwdPart* __restrict__ part, int nr, int rows, int nch,
     int32_t* __restrict__ cnt, ListEvent* __restrict__ list)
 {
     __shared__ double s_m[kSetupThreads / kWave];
@@ -259,24 +265,22 @@ __global__ __launch_bounds__(kSetupThreads) void k_bwd_setup(
         for (size_t i = gtid; i < nW; i += gs) gw[i] = 0;
     const size_t nn = (size_t)B * (size_t)N;
     double mx = 0.0;
+    int bad = 0;
     for (size_t idx = gtid; idx < nn; idx += gs) {
         const int ns = max(min(out_n[idx], m.s_max), 0);
         const size_t o = idx * (size_t)m.s_max;
         const double ms = spike_suffix_sums(m, ns, out_t + o, out_i + o, grad_out_t + o, rtab + o);
         ns_eff[idx] = ms != 0.0 ? ns : 0;
-        mx = ms != ms || mx != mx ? __builtin_nan("") : fmax(mx, ms);
+        if (isfinite(ms)) mx = fmax(mx, ms);
+        else bad = 1;
     }
 #pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-        const double o = __shfl_xor(mx, off, kWave);
-        mx = o != o || mx != mx ? __builtin_nan("") : fmax(mx, o);
-    }
+    for (int off = kWave / 2; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, kWave));
     if (lane == 0) s_m[wv] = mx;
-    __syncthreads();
+    bad = __syncthreads_or(bad);
     if (threadIdx.x == 0) {
-        for (int q = 1; q < kSetupThreads / kWave; ++q)
-            mx = s_m[q] != s_m[q] || mx != mx ? __builtin_nan("") : fmax(mx, s_m[q]);
-        part[blockIdx.x] = mx;
+        for (int q = 1; q < kSetupThreads / kWave; ++q) mx = fmax(mx, s_m[q]);
+        part[blockIdx.x] = BwdPart{mx, bad};
     }
     if (nr == 1) {
         for (size_t i = gtid; i < (size_t)B * E_max; i += gs) {
@@ -304,12 +308,13 @@ __global__ __launch_bounds__(kSetupThreads) void k_bwd_setup(
 // kappa (P^m - P^s) of a neuron is at most 2 kappa sum_s |mu_s| in size and a
 // sum takes at most one contribution per event of the batch, so with
 // bound = 2 kappa max_neuron(sum_s |mu_s|) (events in the batch) the scale
-// 2^(62 - ceil(log2 bound)) keeps every sum below 2^62.  A contribution is
+// 2^(62 - ceil(log2 bound)) keeps every sum below 2^62 (neurons whose sum is not
+// finite left out: their own columns have no value, the others keep theirs).  A contribution is
 // then below 2^62 / events; scale[1] = 1 marks a call where that may reach
 // 2^51, or where a sum is not finite: its terms take the full conversion
 // (fx_term).  Workgroup 1 + b: the exclusive prefix sum of sample b's event
 // counts in (range, chunk) order, and where each range's list starts.
-__global__ __launch_bounds__(kPlanThreads) void k_bwd_plan(const double* __restrict__ part, int nparts,
+__global__ __launch_bounds__(kPlanThreads) void k_bwd_plan(const BwdPart* __restrict__ part, int nparts,
                                                    const int32_t* __restrict__ ev_n, int B, int E_max, double kappa,
                                                    double* __restrict__ scale, int nr, int nch,
                                                    int32_t* __restrict__ cnt, int32_t* __restrict__ start)
@@ -320,8 +325,8 @@ __global__ __launch_bounds__(kPlanThreads) void k_bwd_plan(const double* __restr
         double mx = 0.0, ev = 0.0;
         bool bad = false;
         for (int i = tid; i < nparts; i += kPlanThreads) {
-            bad |= !isfinite(part[i]);
-            mx = fmax(mx, part[i]);
+            bad |= part[i].bad != 0;
+            mx = fmax(mx, part[i].mx);
         }
         for (int b = tid; b < B; b += kPlanThreads) ev += (double)clamp_count(ev_n[b], E_max);
 #pragma unroll
@@ -841,7 +846,7 @@ int backward_impl(const float* ev_t, const int32_t* ev_src, const int32_t* ev_n,
     char* base = (char*)(((uintptr_t)ws + 255) & ~(uintptr_t)255);
     double2* q = (double2*)(base + L.q);
     int32_t* ns = (int32_t*)(base + L.ns);
-    double* part = (double*)(base + L.part);
+    BwdPart* part = (BwdPart*)(base + L.part);
     double* scale = (double*)(base + L.scale);
     const bool lists = P.nr > 1;
     int32_t* cnt = lists ? (int32_t*)(base + L.cnt) : nullptr;
