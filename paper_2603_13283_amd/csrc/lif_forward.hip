@@ -2690,7 +2690,9 @@ extern "C" int lif_spike_count_reg_backward(const float* ev_t, const int32_t* ev
                 if ((long long)((gtiles * q + kCUs - 1) / kCUs) * slices < (long long)((gtiles * slices + kCUs - 1) / kCUs) * q)
                     slices = q;
             auto walk = [&](auto kern) {
-                if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
+                // the attribute belongs to the kernel, not to the call: always the
+                // same value, so that calls of other threads do not lower it
+                if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax) !=
                     hipSuccess)
                     return false;
                 TIMED_LAUNCH("regg_walk", kern, dim3((unsigned)gtiles, (unsigned)slices), dim3(kWave * kTileWaves), lds,

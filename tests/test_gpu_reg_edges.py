@@ -1,7 +1,7 @@
 """GPU parity of the spike-count regularisers' loss and gradient at the edges of
 their walks, against the float64 oracle (oracle/loss.py) on identical inputs:
 one neuron and sample, batches and layers one past the tiles of 16 and 64,
-queues around the segments of 128 events, long padded queues (dL/dW in LDS up
+queues around two segments of 64 events, long padded queues (dL/dW in LDS up
 to 1280 channels, by global atomics past them), ratios of the time constants that
 are a whole number and not, with and without the input times' gradient."""
 import numpy as np
@@ -122,3 +122,47 @@ def test_delayed_regulariser_edges(env, B, C, N, n_events, tau_mem, tau_syn):
     for got, j, label in ((gs, 5, "spike-time gradient"), (gW, 2, "direct grad_W"), (gD, 3, "direct grad_D"),
                           (gT, 4, "direct grad_t")):
         compare_grad_band(got.cpu().numpy(), at32[j], at64[j], label=f"delayed {label}")
+
+
+def test_regulariser_gradient_from_two_threads(env):
+    """Two host threads, each with its own stream and buffers, whose gradient
+    walks ask for different amounts of LDS (1280 and 300 channels): every call
+    gives the bits of the same call alone."""
+    import threading
+    torch, lif = env
+    dev = torch.device("cuda:0")
+    P = lif.Params(s_max=16)
+    jobs = []
+    for C in (1280, 300):
+        cfg = W.random_small(90, B=2, C=C, N=48, n_events=300, T=0.2, gain=20.0)
+        ev = cfg.events
+        pad = ((0, 0), (0, 50000 - ev.E_max))            # long queues: dL/dW in LDS
+        t, s, n, WT = (_dev(torch, a) for a in (np.pad(ev.ev_t, pad, constant_values=np.inf), np.pad(ev.ev_src, pad),
+                                                ev.ev_n, cfg.layers[0].WT))
+        out = lif.forward(t, s, n, WT, P)
+        ws = torch.empty(lif.lif_spike_count_reg_backward_workspace_size(2, 50000, C, 48), dtype=torch.uint8, device=dev)
+        def call(stream, t=t, s=s, n=n, WT=WT, out=out, ws=ws):
+            return lif.spike_count_reg_backward(t, s, n, WT, out, 2.0, params=P, want_time_grad=True, stream=stream, ws=ws)
+        ref = [x.clone() for x in call(None) if x is not None]
+        jobs.append((call, ref))
+    torch.cuda.synchronize()
+    assert all(float(ref[2].abs().sum()) > 0 for _, ref in jobs)
+    bad = []
+
+    def work(call, ref):
+        try:
+            stream = torch.cuda.Stream()
+            with torch.cuda.stream(stream):
+                for _ in range(40):
+                    got = [x for x in call(stream) if x is not None]
+                    stream.synchronize()
+                    if not all(torch.equal(a, b) for a, b in zip(got, ref)):
+                        bad.append("bits differ")
+        except Exception as e:                            # noqa: BLE001 (reported below)
+            bad.append(repr(e))
+    th = [threading.Thread(target=work, args=j) for j in jobs]
+    for x in th:
+        x.start()
+    for x in th:
+        x.join()
+    assert not bad, bad[:3]
