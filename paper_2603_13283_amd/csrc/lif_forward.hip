@@ -85,8 +85,10 @@ __device__ __forceinline__ float key_bound(const Model& m, double z, double t_la
 
 // Per-sample counters (pool use, work-list length) each take their
 // own 128-byte line: many waves update them with atomics, and atomics on one
-// line are serialised.
+// line are serialised.  The resolve pass's list counter is word kTaken of the first
+// line, whose own word is only read by then.
 constexpr int kCtr = 32;
+constexpr int kTaken = 16;
 
 // ---------------------------------------------------------------------------
 // k_prep
@@ -1438,8 +1440,8 @@ FwdLayout fwd_layout(int B, int E_max, int N, int pool_cap)
     // segment aggregates, overwritten in place by the carried states
     L.carry = take(BS * N * sizeof(double2));
     L.mask = take(BS * N * sizeof(uint32_t));
-    // per sample: pool use, work-list length; then the resolve's list counter
-    L.n_counters = (2 * (size_t)B + 1) * kCtr;
+    // per sample: pool use, work-list length
+    L.n_counters = 2 * (size_t)B * kCtr;
     L.counters = take(L.n_counters * sizeof(uint32_t));
     L.listed = take((size_t)B * N * sizeof(uint32_t));
     L.work = take((size_t)B * N * sizeof(uint32_t));
@@ -1613,7 +1615,7 @@ int forward_impl(bool sequential, const float* ev_t, const int32_t* ev_src, cons
         if (both)
             TIMED_LAUNCH("resolve", wave, dim3(wgrid), dim3(kWave * kResolveWaves), 0, stream, ev_t, ev_src, ev_n, B,
                          E_max, WT, C_in, N, L.E_pad, L.S, m, P.dec, P.carry, P.mask, (uint32_t)L.pool_cap, P.pool,
-                         P.pool_count, P.work, P.nwork, P.counters + 2 * (size_t)B * kCtr, kRingMost, out_t, out_n,
+                         P.pool_count, P.work, P.nwork, P.counters + kTaken, kRingMost, out_t, out_n,
                          out_i, out_k, status);
         TIMED_LAUNCH("resolve", ring, dim3(rgrid), dim3(kWave * kRingWaves), 0, stream, ev_t, ev_src, ev_n, B,
                      E_max, WT, C_in, N, L.E_pad, L.S, m, P.dec, P.carry, P.mask, (uint32_t)L.pool_cap, P.pool,

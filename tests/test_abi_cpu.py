@@ -48,6 +48,20 @@ def test_version_and_workspace_sizes(lib):
     assert L.lif_merge_workspace_size(4, 20, 8, 100) > 0
 
 
+@pytest.mark.parametrize("B,E,N", [(24, 3072, 2786), (10, 19584, 992), (5, 16640, 2474)])
+def test_forward_layout_fills_the_fixed_array(lib, B, E, N):
+    """Shapes whose forward layout without pool entries is exactly the fixed
+    workspace array: they are accepted by lif_layer_forward_noalloc, so the
+    layout may not grow."""
+    up = lambda x: -(-x // 256) * 256
+    rows = B * (E // 64)
+    parts = (B * E * 32, rows * 16, rows * N * 16, rows * N * 4,      # decays, segment maps, carries, masks
+             2 * B * 128, B * N * 4, B * N * 4, 16)                   # counters, listed, work, one pool entry
+    want = sum(map(up, parts)) + 256
+    assert want == L.lif_layer_forward_noalloc_max_bytes()
+    assert L.lif_layer_forward_workspace_size(B, E, 10, N, L.Params(pool_cap=0).c()) == want
+
+
 def _fwd(fn, p, B=2, E=10, C=4, N=8, ws_bytes=10 ** 9, null=None):
     # ev_t, ev_src, ev_n, B, E_max, WT, C_in, N_out, p, out_t, out_n, out_i, out_k, status, ws, ws_bytes, stream
     args = [F, F, F, B, E, F, C, N, ctypes.byref(p), F, F, F, F, F, F, ws_bytes, None]
