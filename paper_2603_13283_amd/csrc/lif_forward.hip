@@ -70,6 +70,13 @@ __device__ __forceinline__ double crossing_key(const Model& m, double crit, doub
     return log(crit) + t0 * m.inv_tm;
 }
 
+// The hardware logarithm ln x of a double x, and how far it may be from it: the
+// rounding to float (2^-24), v_log_f32 (an ulp of log2 x), ln 2 as a float and the
+// product (half an ulp each), under 1.2e-5 at the ends of the float range and
+// under 1e-5 + |ln x| 2^-21 everywhere.  Past the float range it is the end of it.
+__device__ __forceinline__ double log_coarse(double x) { return (double)__logf(fminf((float)x, 3.0e38f)); }
+__device__ __forceinline__ double log_margin(double l) { return fma(fabs(l), 0x1p-21, 1e-5); }
+
 // Upper bound, as a float, of the crossing keys of a sub-block's intervals from
 // the largest value z of its screens (V / kappa; screen_value) and its last
 // event's time: an interval's crit is at most V_lin's tangent bound minus th, so
@@ -79,7 +86,9 @@ __device__ __forceinline__ double crossing_key(const Model& m, double crit, doub
 __device__ __forceinline__ float key_bound(const Model& m, double z, double t_last)
 {
     const double x = fmax(fma(m.kappa, z, -m.th), 0.0) + 1e-9 * fmax(1.0, m.th);
-    const float f = (float)((double)__logf((float)x) + 1e-5 + t_last * m.inv_tm);
+    if (!(x < 3.0e38)) return INFINITY;
+    const double l = log_coarse(x);
+    const float f = (float)(l + log_margin(l) + t_last * m.inv_tm);
     return f + fabsf(f) * 0x1p-22f;
 }
 
@@ -821,8 +830,8 @@ __device__ __forceinline__ WinIn win_load(const ResolveLds& sh, int c, int seg0,
 
 // Wave-uniform resolve state of one neuron: the reset deficit of the spikes
 // so far is D(t) = dref e^{-(t - tref)/tm} for t after the latest spike (dref =
-// 0: none yet), and K <= ln(dref) + tref/tm its key (a lower bound within
-// 1e-4, for the candidates' key bounds).
+// 0: none yet), and K <= ln(dref) + tref/tm its key (a lower bound, two log_margin
+// from it at most while dref is a float, for the candidates' key bounds).
 struct Chain {
     int ns;              // spikes so far
     double dref, tref, K;
@@ -1017,7 +1026,7 @@ __device__ int resolve_neuron(ResolveLds& sh, int b, int n, const float* __restr
             const double tf = (double)__builtin_bit_cast(
                 float, rl_int(__builtin_bit_cast(int, in.k > 0 ? in.ta : 0.0f), 0));
             const double Dp = fma(ch.dref, exp_lower(-(tf - ch.tref) * m.inv_tm), m.dth);
-            const double Kp = fmax(ch.K, (double)__logf(fminf((float)Dp, 3.0e38f)) - 1e-5 + tf * m.inv_tm);
+            const double lp = log_coarse(Dp), Kp = fmax(ch.K, lp - log_margin(lp) + tf * m.inv_tm);
             int c_n = select(Kp);
             WinIn nx = in;
             float wvn = 0.0f;
@@ -1117,8 +1126,8 @@ __device__ int resolve_neuron(ResolveLds& sh, int b, int n, const float* __restr
                         more = ch.ns < m.s_max;
                         if (!more) break;
                     }
-                    ch.K = ch.ns > 0 ? (double)__logf(fminf((float)ch.dref, 3.0e38f)) - 1e-5 + ch.tref * m.inv_tm
-                                     : -INFINITY;
+                    const double lk = log_coarse(ch.dref);
+                    ch.K = ch.ns > 0 ? lk - log_margin(lk) + ch.tref * m.inv_tm : -INFINITY;
                     if (!more) break;
                 }
                 if (!more) break;
