@@ -56,8 +56,13 @@ __device__ __forceinline__ RegArg reg_vmax_arg(const Model& m, double V0, double
 // The same over an interval of finite length whose end state is at hand (V1, and
 // I1 = I0 Dd): the stationary point lies inside iff V' = (I - V)/tm is positive at
 // the start and negative at the end (V' has at most one zero), so the quotient
-// and its logarithm are taken by the lanes that need them only, and
-// e^{-u/tm} = ratio^{-kappa} directly (kappa = ts / (tm - ts) = c_tv / tm).
+// and its logarithm are taken by the lanes that need them only, and directly
+// e^{-u/tm} = ratio^{-kappa}, e^{-u/ts} = ratio^{-(1 + kappa)} (kappa =
+// ts / (tm - ts) = c_tv / tm).  The ratio is at most 2^53 tm / ts (V0 + kappa I0
+// is a difference of doubles) and so a float.  Relative errors (rms) of e^{-u/tm},
+// e^{-u/ts} and V at ratios tm / ts of 4, 10/3 and 10.5: 3.4e-8, 1.4e-7, 1.5e-8;
+// 3.5e-8, 8.4e-8, 2.6e-8; 2.4e-8, 1.3e-7, 7.9e-9, none above reg_vmax_arg's (with
+// e^{-u/ts} as a power of the rounded e^{-u/tm}: 1.3e-7 and 2.7e-7 at the last two).
 __device__ __forceinline__ RegArg reg_vmax_in(const Model& m, double V0, double I0, double A, double Dd, double V1,
                                               double I1)
 {
@@ -69,18 +74,24 @@ __device__ __forceinline__ RegArg reg_vmax_in(const Model& m, double V0, double 
     r.es = r.at_end ? Dd : 1.0;
     if (I0 > V0 && I1 < V1) {
         const double kI = m.kappa * I0, a = V0 + kI;
-        const float ratio = (float)(kI * (m.tm * m.inv_ts) * __builtin_amdgcn_rcp(a));
-        const float emf = fminf(__builtin_amdgcn_exp2f(-(float)m.kappa * __builtin_amdgcn_logf(ratio)), 1.0f);
-        float esf;
+        const float lg = __builtin_amdgcn_logf((float)(kI * (m.tm * m.inv_ts) * __builtin_amdgcn_rcp(a)));
+        const float emf = fminf(__builtin_amdgcn_exp2f(-(float)m.kappa * lg), 1.0f);
+        float esf, esp = 0.0f;               // the record's e^{-u/ts}; (e^{-u/tm})^(tm/ts)
         switch (m.p_int) {
-        case 1: esf = emf * emf; break;
-        case 2: esf = emf * emf * emf; break;
-        case 3: { const float e2 = emf * emf; esf = e2 * e2; } break;
-        case 4: { const float e2 = emf * emf; esf = e2 * e2 * emf; } break;
-        default: esf = __builtin_amdgcn_exp2f((float)(m.tm * m.inv_ts) * __builtin_amdgcn_logf(emf)); break;
+        case 1: esf = esp = emf * emf; break;
+        case 2: esf = esp = emf * emf * emf; break;
+        case 3: { const float e2 = emf * emf; esf = esp = e2 * e2; } break;
+        case 4: { const float e2 = emf * emf; esf = esp = e2 * e2 * emf; } break;
+        default:
+            esf = fminf(__builtin_amdgcn_exp2f((float)(-(1.0 + m.kappa) * (double)lg)), 1.0f);
+            esp = m.kappa < 1.0 ? __builtin_amdgcn_exp2f((float)(m.tm * m.inv_ts) * __builtin_amdgcn_logf(emf)) : esf;
+            break;
         }
+        // V at the point whose e^{-u/tm} is emf: next to the maximum, so that the
+        // rounding of emf enters squared (for ratios below 2 the rounding of the
+        // power itself is the larger error)
         const double em = (double)emf, es = (double)esf;
-        const double Vu = fma(V0, em, kI * (em - es));
+        const double Vu = fma(V0, em, kI * (em - (double)esp));
         if (Vu > r.vmax) r = RegArg{Vu, em, es, false, false};
     }
     return r;
