@@ -198,25 +198,31 @@ static BwdLayout bwd_layout(int B, int E_max, int C_in, int N, int s_max)
 // Suffix sums of one neuron's spike adjoints, last spike first (lambda_s and
 // mu_s as in spike_adjoints): ro[s] = (R^m_s, R^s_s), the sums over s' >= s of
 // mu_s' e^{-(t_s' - ref)/tm} and with ts, ref the spike's own reference.  Spikes are read kSufBatch at a time
-// (the recurrence waits for loads once per batch).  Returns sum_s |mu_s|.
+// (the recurrence waits for loads once per batch).  Returns sum_s |mu_s|; early is
+// set when a (handed-over) spike time lies before the event before it, et[k - 1].
 constexpr int kSufBatch = 4;
 
 __device__ __forceinline__ double spike_suffix_sums(const Model& m, int ns, const float* __restrict__ ts,
                                                     const float* __restrict__ is, const float* __restrict__ g,
-                                                    double2* __restrict__ ro)
+                                                    double2* __restrict__ ro, const int32_t* __restrict__ ks,
+                                                    const float* __restrict__ et, int nb, bool& early)
 {
     const double len = kRefTs * m.ts;
     const double jump = (m.th - m.vr) * m.inv_tm;
     double Qm = 0.0, Qs = 0.0, tn = 0.0, asum = 0.0;
     for (int s1 = ns - 1; s1 >= 0; s1 -= kSufBatch) {
-        float tb[kSufBatch], ib[kSufBatch], gb[kSufBatch];
+        float tb[kSufBatch], ib[kSufBatch], gb[kSufBatch], eb[kSufBatch];
+        int kb[kSufBatch];
 #pragma unroll
         for (int u = 0; u < kSufBatch; ++u) {
             const int s = max(s1 - u, 0);
+            kb[u] = ks[s];
             tb[u] = ts[s];
             ib[u] = is[s];
             gb[u] = g[s];
         }
+#pragma unroll
+        for (int u = 0; u < kSufBatch; ++u) eb[u] = nb > 0 ? et[min(max(kb[u], 1), nb) - 1] : 0.0f;
 #pragma unroll
         for (int u = 0; u < kSufBatch; ++u) {
             const int s = s1 - u;
@@ -235,6 +241,7 @@ __device__ __forceinline__ double spike_suffix_sums(const Model& m, int ns, cons
             asum += fabs(mu);
             const double dr = ref_offset(tn, ref_index(tn, 1.0 / len), len);
             ro[s] = make_double2(Qm * exp(-dr * m.inv_tm), Qs * exp(-dr * m.inv_ts));
+            early = early || (kb[u] > 0 && tb[u] < eb[u]);
         }
     }
     return asum;
@@ -244,7 +251,8 @@ __device__ __forceinline__ double spike_suffix_sums(const Model& m, int ns, cons
 // fixed-point accumulators of dL/dW (where blocks are split) set to zero;
 // the suffix sums of every (sample, neuron)'s spike adjoints with its spike
 // count (0 when all its adjoints are exactly 0: such a neuron adds exactly 0
-// everywhere and is not walked; a NaN sum keeps it); per workgroup its BwdPart; and
+// everywhere and is not walked; a NaN sum keeps it; the complement of the count
+// when a spike time of its lies before an event that the spike follows); per workgroup its BwdPart; and
 // with one channel range the list of every sample's events, else the events of each (sample, chunk) counted per
 // channel range, cnt[b][r][chunk], one wave per chunk.
 constexpr int kSetupThreads = 256;
@@ -269,8 +277,11 @@ __global__ __launch_bounds__(kSetupThreads) void k_bwd_setup(
     for (size_t idx = gtid; idx < nn; idx += gs) {
         const int ns = max(min(out_n[idx], m.s_max), 0);
         const size_t o = idx * (size_t)m.s_max;
-        const double ms = spike_suffix_sums(m, ns, out_t + o, out_i + o, grad_out_t + o, rtab + o);
-        ns_eff[idx] = ms != 0.0 ? ns : 0;
+        const int b = (int)(idx / (size_t)N);
+        bool early = false;
+        const double ms = spike_suffix_sums(m, ns, out_t + o, out_i + o, grad_out_t + o, rtab + o, out_k + o,
+                                            ev_t + (size_t)b * E_max, clamp_count(ev_n[b], E_max), early);
+        ns_eff[idx] = ms != 0.0 ? (early ? ~ns : ns) : 0;
         if (isfinite(ms)) mx = fmax(mx, ms);
         else bad = 1;
     }
@@ -512,10 +523,10 @@ __device__ __noinline__ double2 p_at(const float* ts, const double2* rr, int s, 
 // the sum over lanes of w kappa (P^m/tm - P^s/ts), is stored; then a lane with
 // spikes between the listed event before it and event k switches its R.  The
 // spikes that a group of kGrp events passes are looked up before the group, all
-// lanes together (at most two per lane).  A group where a lane passes more, or
-// one whose float32 time lies before the event below it, a group with events
-// after the time of a spike that they precede, and a block of 64
-// events over more than 3 len, go event by event through p_at.
+// lanes together (at most two per lane); a group where a lane passes more goes
+// event by event through p_at, as do groups with events after the time of a spike
+// that they precede (setup looks for these; a check in every group of the walk
+// cost it 4 %).
 // kLds = false: dL/dW by global atomics; kTime: dL/dt wanted (else no weight is
 // read).
 // Bound by VALU issue (82 % busy at the first shape below, 69 % at the second):
@@ -571,7 +582,9 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint(const AdjArgs a)
             return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
         };
         const size_t bn = (size_t)b * a.N + nc;
-        const int ns = live ? a.ns[bn] : 0;
+        int ns = live ? a.ns[bn] : 0;
+        const bool early = __ballot(ns < 0) != 0ull;
+        ns = ns < 0 ? ~ns : ns;
         const size_t so = bn * (size_t)a.s_max;            // the neuron's spikes
         double* gt = kTime ? a.gt + (size_t)tile * a.nT + (size_t)b * a.E_max : nullptr;
         int lb = l0 + ((l1 - l0 - 1) / kWave) * kWave;     // the topmost block
@@ -594,25 +607,31 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint(const AdjArgs a)
             }
             sp = lo;
         }
-        // the next spike the walk meets, sp - 1, and k of the one after it
-        // (k = -1: none)
-        int k1 = -1, k2 = -1;
+        // the next spike the walk meets, sp - 1 (when sp >= 1), and k of the one
+        // after it.  Loaded under the lanes' condition and nothing else, straight
+        // into place: selects on the loaded values wait for the loads (5 % of the
+        // walk at the second shape).
+        int k1 = 0, k2 = 0;
         float t1 = 0.0f;
         double2 R1 = make_double2(0.0, 0.0);
         auto refill = [&]() {
-            k1 = k2 = -1;
-            if (sp >= 1) {
-                k1 = a.out_k[so + sp - 1];
-                t1 = a.out_t[so + sp - 1];
-                R1 = a.r[so + sp - 1];
-            }
-            if (sp >= 2) k2 = a.out_k[so + sp - 2];
+            const size_t i1 = so + max(sp - 1, 0), i2 = so + max(sp - 2, 0);
+            k1 = a.out_k[i1];
+            t1 = a.out_t[i1];
+            R1 = a.r[i1];
+            k2 = a.out_k[i2];
         };
         if (ns > 0) refill();
-        // R of a spike at time t referred to the block's reference
-        int ref = -1;                                      // -1: none
-        auto refer = [&](double2 v, float t) {
-            const int d = ref_index((double)t, a.inv_len) - ref;
+        // The unit's reference is its first event's.  A unit over more than 3 len
+        // (sparse streams, lists of few channels) has none: there the walk
+        // carries P itself instead of R, with the decays from event to event;
+        // that walk also looks out for spike times before events that the spikes
+        // follow (offsets of 0: p_at).
+        const int ref = __builtin_amdgcn_readfirstlane(ll[l0].ref);
+        const bool other = early || __builtin_amdgcn_readlane(cur.ref, cnt - 1) - ref > 3;
+        // R of a spike at time t referred to reference r
+        auto refer = [&](double2 v, float t, int r) {
+            const int d = ref_index((double)t, a.inv_len) - r;
             if (__builtin_expect(d != 0, 0)) {
                 v.x *= ref_pow(a.fm, a.gm, d);
                 v.y *= ref_pow(a.fs, a.gs, d);
@@ -628,108 +647,146 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint(const AdjArgs a)
                                                          __builtin_amdgcn_readlane(woff, g * kGrp + j), 0));
             }
         };
-        // the walk: kWide as in fx_term
-        auto walk = [&](auto wide_tag) {
-            constexpr bool kWide = decltype(wide_tag)::value;
+        // the walk: kWide as in fx_term, kRef with a reference
+        auto walk = [&](auto wide_tag, auto ref_tag) {
+            constexpr bool kWide = decltype(wide_tag)::value, kRef = decltype(ref_tag)::value;
             auto add_w = [&](unsigned long long x, int ro) {
                 if constexpr (kLds) atomicAdd(&s_acc[ro + lane], x);
                 else if (x != 0ull) atomicAdd((unsigned long long*)&a.gw[(size_t)ro + n], x);
             };
             const int rmul = kLds ? kWave : a.N;
             double Rm = 0.0, Rs = 0.0;
-            float tc = INFINITY;                           // time of spike sp (none: infinite)
             float w[kGrp], wn[kGrp];
             int woff = cur.src * a.N * 4;
             load_w(woff, (cnt - 1) / kGrp, w);
-            auto take = [&]() {                            // R of spike sp
+            // R of spike sp, or its P at event e of the block; then 1 when a
+            // lane's spike lies before that event
+            auto take = [&](int e) {
                 Rm = Rs = 0.0;
-                tc = INFINITY;
+                bool early = false;
                 if (sp < ns) {
-                    tc = a.out_t[so + sp];
-                    const double2 v = refer(a.r[so + sp], tc);
-                    Rm = v.x;
-                    Rs = v.y;
+                    const float t = a.out_t[so + sp];
+                    const double2 v = refer(a.r[so + sp], t, kRef ? ref : __builtin_amdgcn_readlane(cur.ref, e));
+                    Rm = kRef ? v.x : v.x * read_lane_double(cur.Hm, e);
+                    Rs = kRef ? v.y : v.y * read_lane_double(cur.Hs, e);
+                    early = t < rl_f(cur.t, e);
+                    // (waited for here: a load into Rm or Rs still in flight on
+                    // some path has every group wait for its newest loads)
+                    asm volatile("" : "+v"(Rm), "+v"(Rs));
                 }
+                return __ballot(early) != 0ull ? 1 : 0;
             };
+            int late = take(cnt - 1), again = 0;           // the last take's; R to be taken at the next block
             for (;;) {
                 const bool more = lb > l0;
                 ListEvent nxt = cur;
                 if (more) nxt = load(lb - kWave);
-                // the block's reference is its first event's; none (event by
-                // event) when the block spans more than 3 len
-                {
-                    int nref = __builtin_amdgcn_readlane(cur.ref, 0);
-                    if (__builtin_amdgcn_readlane(cur.ref, cnt - 1) - nref > 3) nref = -1;
-                    const bool moved = nref != ref;
-                    ref = nref;
-                    if (moved && ref >= 0) take();
-                }
-                // H of the block's events, referred to the block's reference
+                // factors of the block's events: H referred to the unit's
+                // reference, or the decays to the listed event below
                 double hm = cur.Hm, hs = cur.Hs;
-                if (ref >= 0 && __ballot(cur.ref != ref)) {
-                    asm volatile("");
-                    const int d = min(max(cur.ref - ref, 0), 3);
-                    hm *= ref_pow(a.gm, a.fm, d);
-                    hs *= ref_pow(a.gs, a.fs, d);
+                if constexpr (kRef) {
+                    if (__ballot(cur.ref != ref)) {
+                        asm volatile("");
+                        const int d = min(max(cur.ref - ref, 0), 3);
+                        hm *= ref_pow(a.gm, a.fm, d);
+                        hs *= ref_pow(a.gs, a.fs, d);
+                    }
+                } else {
+                    float tb = __shfl_up(cur.t, 1, kWave);
+                    if (lane == 0) tb = rl_f(more ? nxt.t : cur.t, more ? kWave - 1 : 0);
+                    const double dt = fmax((double)cur.t - (double)tb, 0.0);
+                    hm = exp(-dt * a.inv_tm);
+                    hs = exp(-dt * a.inv_ts);
                 }
                 const int row = (cur.src - c0) * rmul;
                 const int woff_n = nxt.src * a.N * 4;
                 // k and time of the event below the block (past the unit's
                 // first event spikes do not matter)
                 const int kbelow = __builtin_amdgcn_readlane(more ? nxt.k : cur.k, more ? kWave - 1 : 0);
-                const float tbelow = rl_f(more ? nxt.t : cur.t, more ? kWave - 1 : 0);
+                float tbelow = 0.0f;
+                if constexpr (!kRef) tbelow = rl_f(more ? nxt.t : cur.t, more ? kWave - 1 : 0);
                 for (int g = (cnt - 1) / kGrp; g >= 0; --g) {
                     const int klo = g > 0 ? __builtin_amdgcn_readlane(cur.k, g > 0 ? g * kGrp - 1 : 0) : kbelow;
                     const int ne = min(kGrp, cnt - g * kGrp);
-                    const bool pass = k1 > klo;
+                    const bool pass = sp >= 1 && k1 > klo;
                     const bool any = __ballot(pass) != 0ull;
-                    // (a handed-over spike time may lie before events that the
-                    // spike follows: their offsets count as 0)
-                    bool any2 = false, slow = ref < 0 || __ballot(tc < rl_f(cur.t, g * kGrp + ne - 1)) != 0ull;
+                    // (scalars: the branches below and the flags set under them are uniform)
+                    bool any2 = false, slow = false;
+                    if constexpr (!kRef) slow = __builtin_amdgcn_readfirstlane(late) != 0;
                     int x1 = -1, x2 = -1;                  // R switched after event x of the group
                     double2 X1 = make_double2(0.0, 0.0), X2 = X1;
-                    if (any && !slow) {
-                        const bool pass2 = pass && k2 > klo;
+                    if (any && (kRef || !slow)) {
+                        const bool pass2 = pass && sp >= 2 && k2 > klo;
                         any2 = __ballot(pass2) != 0ull;
                         int y1 = 0;
 #pragma unroll
                         for (int j = 0; j < kGrp; ++j)
                             y1 += __builtin_amdgcn_readlane(cur.k, g * kGrp + j) < k1 ? 1 : 0;
-                        // the time of the listed event below (of event y1 - 1)
+                        // what R is referred to below event e + 1: the unit's
+                        // reference, or (P) the time of the listed event e
+                        auto below = [&](double2 v, float t, int e) {
+                            if constexpr (kRef) return refer(v, t, ref);
+                            const int l = max(e, 0);
+                            int rb = __shfl(cur.ref, l, kWave);
+                            double Hm = __shfl(cur.Hm, l, kWave), Hs = __shfl(cur.Hs, l, kWave);
+                            if (e < 0) {
+                                rb = __builtin_amdgcn_readlane(nxt.ref, kWave - 1);
+                                Hm = read_lane_double(nxt.Hm, kWave - 1);
+                                Hs = read_lane_double(nxt.Hs, kWave - 1);
+                            }
+                            v = refer(v, t, rb);
+                            return make_double2(v.x * Hm, v.y * Hs);
+                        };
+                        // the listed event below, event y1 - 1
                         const int el = g * kGrp + min(y1, kGrp - 1) - 1;
-                        const float te = __shfl(cur.t, max(el, 0), kWave);
-                        bool bad = pass && t1 < (el < 0 ? tbelow : te);
+                        bool bad = false;
+                        if constexpr (!kRef) {
+                            const float te = __shfl(cur.t, max(el, 0), kWave);
+                            bad = pass && t1 < (el < 0 ? tbelow : te);
+                        }
                         float t2 = 0.0f;
+                        int el2 = -1;
                         if (__builtin_expect(any2, 0)) {
                             int y2 = 0;
                             if (pass2) t2 = a.out_t[so + sp - 2];
 #pragma unroll
                             for (int j = 0; j < kGrp; ++j)
                                 y2 += __builtin_amdgcn_readlane(cur.k, g * kGrp + j) < k2 ? 1 : 0;
-                            const int el2 = g * kGrp + min(y2, kGrp - 1) - 1;
-                            const float te2 = __shfl(cur.t, max(el2, 0), kWave);
-                            bad = bad || (pass2 && (t2 < (el2 < 0 ? tbelow : te2) ||
-                                                    (sp >= 3 && a.out_k[so + max(sp - 3, 0)] > klo)));
+                            el2 = g * kGrp + min(y2, kGrp - 1) - 1;
+                            bad = bad || (pass2 && sp >= 3 && a.out_k[so + max(sp - 3, 0)] > klo);
+                            if constexpr (!kRef) {
+                                const float te2 = __shfl(cur.t, max(el2, 0), kWave);
+                                bad = bad || (pass2 && t2 < (el2 < 0 ? tbelow : te2));
+                            }
                             x2 = pass2 ? y2 : -1;
                         }
                         slow = __ballot(bad) != 0ull;
                         if (!slow) {
+                            if constexpr (!kRef) {         // (all lanes: the shuffles)
+                                X1 = below(R1, t1, el);
+                                if (any2) X2 = below(pass2 ? a.r[so + sp - 2] : X2, t2, el2);
+                            }
                             if (pass) {
                                 x1 = y1;
-                                X1 = refer(R1, t1);
-                                tc = t1;
+                                if constexpr (kRef) {
+                                    // (a copy: the next R1 then loads into R1's registers)
+                                    double2 q = R1;
+                                    asm volatile("" : "+v"(q.x), "+v"(q.y));
+                                    X1 = below(q, t1, el);
+                                }
                                 --sp;
                                 if (pass2) {
-                                    X2 = refer(a.r[so + sp - 1], t2);
-                                    tc = t2;
+                                    if constexpr (kRef) X2 = below(a.r[so + sp - 1], t2, el2);
                                     --sp;
                                 }
                                 refill();
                             }
                         }
                     }
-                    if (g > 0) load_w(woff, g - 1, wn);
-                    else if (more) load_w(woff_n, kWave / kGrp - 1, wn);
+                    // (one set of loads for the group below in this block or the
+                    // next: in two branches the compiler copies the loaded
+                    // values, and waits for them, right away)
+                    load_w(g > 0 ? woff : woff_n, g > 0 ? g - 1 : (more ? kWave / kGrp - 1 : 0), wn);
                     if (__builtin_expect(!slow, 1)) {
                         double ca[kGrp / 2], c4[kGrp / 2];
                         auto events = [&](auto full_tag) {
@@ -739,9 +796,14 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint(const AdjArgs a)
                                 double cj = 0.0;
                                 if (kFull || jj < ne) {
                                     const int e = g * kGrp + jj;
-                                    const double Pm = Rm * read_lane_double(hm, e), Ps = Rs * read_lane_double(hs, e);
+                                    const double fm = read_lane_double(hm, e), fs = read_lane_double(hs, e);
+                                    const double Pm = kRef ? Rm * fm : Rm, Ps = kRef ? Rs * fs : Rs;
                                     add_w(fx_term<kWide>(Pm - Ps, ks), __builtin_amdgcn_readlane(row, e));
                                     if constexpr (kTime) cj = (double)w[jj] * fma(ktm, Pm, kts * Ps);
+                                    if constexpr (!kRef) {
+                                        Rm *= fm;
+                                        Rs *= fs;
+                                    }
                                     if (any && __ballot(x1 == jj)) {
                                         asm volatile("");          // a branch, not eight selects per event
                                         if (x1 == jj) {
@@ -777,7 +839,9 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint(const AdjArgs a)
 #pragma unroll 1
                         for (int e = g * kGrp + ne - 1; e >= g * kGrp; --e) {
                             double2 P = make_double2(0.0, 0.0);
-                            if (sp < ns) P = p_at(a.out_t + so, a.r + so, sp, ns, (double)rl_f(cur.t, e), a.len, a.inv_len, a.inv_tm, a.inv_ts);
+                            if (sp < ns)
+                                P = p_at(a.out_t + so, a.r + so, sp, ns, (double)rl_f(cur.t, e), a.len, a.inv_len,
+                                         a.inv_tm, a.inv_ts);
                             add_w(fx_term<kWide>(P.x - P.y, ks), __builtin_amdgcn_readlane(row, e));
                             if constexpr (kTime) {
                                 const float we = __builtin_bit_cast(
@@ -791,12 +855,17 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint(const AdjArgs a)
                             const int kp = e > g * kGrp ? __builtin_amdgcn_readlane(cur.k, max(e - 1, 0)) : klo;
                             while (sp > 0 && ns > 0 && a.out_k[so + sp - 1] > kp) --sp;
                         }
-                        if (ref >= 0) take();
+                        // R at the listed event below
+                        if (kRef || g > 0) late = take(max(g * kGrp - 1, 0));
+                        else again = 1;
                         if (ns > 0) refill();
                     }
                     if constexpr (kTime) {
 #pragma unroll
-                        for (int j = 0; j < kGrp; ++j) w[j] = wn[j];
+                        for (int j = 0; j < kGrp; ++j) {
+                            asm volatile("" : "+v"(wn[j]));    // the wait for the loads here, not among the events
+                            w[j] = wn[j];
+                        }
                     }
                 }
                 if (!more) break;
@@ -804,10 +873,15 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint(const AdjArgs a)
                 woff = woff_n;
                 lb -= kWave;
                 cnt = kWave;
+                if (!kRef && again) {
+                    late = take(cnt - 1);
+                    again = 0;
+                }
             }
         };
-        if (__builtin_expect(wide, 0)) walk(std::true_type{});
-        else walk(std::false_type{});
+        if (__builtin_expect(other, 0)) walk(std::true_type{}, std::false_type{});
+        else if (__builtin_expect(wide, 0)) walk(std::true_type{}, std::true_type{});
+        else walk(std::false_type{}, std::true_type{});
     }
     if constexpr (kLds) {
         __syncthreads();

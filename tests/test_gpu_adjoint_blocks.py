@@ -52,6 +52,37 @@ def test_adjoint_long_and_late(env, B, C, N, n, T, gain, t0):
     print(f"[case] t0={t0} T={T} spikes={int(r32.out_n.sum())} rel(gW)={sW:.2e} rel(gT)={sT:.2e}", flush=True)
 
 
+# From several events to a reference (100 tau_s) to a thousand references between
+# events, as one list and as the lists of three channel ranges, where a group of
+# eight events spans more of them; groups that lie in one reference next to ones
+# that do not; bursts between long silences.
+@pytest.mark.parametrize("C", [40, 700])
+@pytest.mark.parametrize("tau_syn", [0.005, 0.0038])
+@pytest.mark.parametrize("kind,T", [("even", 6.0), ("even", 40.0), ("even", 3000.0), ("bursts", 40.0)])
+def test_adjoint_sparse_streams(env, C, tau_syn, kind, T):
+    torch, lif = env
+    B, N, E = 2, 70, 700
+    rng = np.random.default_rng(66)
+    t = rng.random((B, E)) * T
+    if kind == "bursts":
+        t = np.floor(t / 5.0) * 5.0 + rng.random((B, E)) * 0.03
+    ev_t = np.sort(t, -1).astype(np.float32)
+    ev_src = rng.integers(0, C, (B, E)).astype(np.int32)
+    WT = (rng.standard_normal((C, N)) * 5.0).astype(np.float32)
+    # one to three spikes of a neuron after some of the events
+    out_t, out_k = np.full((B, N, 256), np.inf), np.zeros((B, N, 256), np.int32)
+    for b in range(B):
+        for i in range(N):
+            ks = np.sort(rng.choice(np.arange(1, E + 1), 60, replace=False))
+            ks = np.repeat(ks, rng.integers(1, 4, ks.size))[:200]
+            ts = ev_t[b, ks - 1].astype(np.float64)
+            nxt = np.append(ev_t[b], ev_t[b, -1] + 1.0)[ks].astype(np.float64)
+            ts = ts + np.minimum(nxt - ts, 4 * tau_syn) * (0.2 + 0.3 * rng.random(ks.size))
+            out_t[b, i, :ks.size] = np.maximum.accumulate(ts.astype(np.float32))
+            out_k[b, i, :ks.size] = ks
+    _handmade(torch, lif, f"C={C} tau_s={tau_syn} {kind} T={T}", ev_t, ev_src, WT, out_t, out_k, 66, tau_syn=tau_syn)
+
+
 def _handmade(torch, lif, label, ev_t, ev_src, WT, out_t, out_k, seed, **kw):
     """The backward alone on a spike train given by hand, out_t and out_k
     [B][N][S] with infinite times past the last spike."""
