@@ -29,6 +29,70 @@ def test_adjoint_edges(env, B, C, N, n, T, gain):
     _fwd_bwd(env, cfg.events, cfg.layers[0].WT, 61, s_max=512, label=f"B{B} C{C} N{N} n{n} T{T}")
 
 
+def _padded(ev, E):
+    pad = ((0, 0), (0, E - ev.E_max))
+    return W.EventBatch(np.pad(ev.ev_t, pad, constant_values=np.inf), np.pad(ev.ev_src, pad), ev.ev_n)
+
+
+# Calls large enough for the walk over LDS blocks: past 2^23 (event, neuron) pairs
+# with the queues' padding, and with adjoints on more than N events / 13 + 2^21 of
+# the pairs without it.  The sizes are those at which the blocks, lists, tiles and
+# groups end.
+@pytest.mark.parametrize("B,C,N,n,T,gain,e_max", [
+    (50, 318, 64, 1024, 0.2, 14.0, 7000),        # one range, a full list chunk
+    (50, 319, 65, 1025, 0.2, 14.0, 7000),        # two ranges, a chunk and an event, a tile and a neuron
+    (26, 637, 70, 1999, 0.3, 12.0, 7000),        # three ranges
+    (9, 700, 130, 3000, 0.4, 12.0, 9000),        # workgroups that share a block
+    (28, 40, 70, 2500, 0.05, 60.0, 9000),        # bursts: more than two spikes per lane and group
+    (7, 3000, 200, 3000, 30.0, 60.0, 9000),      # ten ranges, lists over many references
+])
+@pytest.mark.parametrize("early", [False, True])
+def test_adjoint_blocks(env, B, C, N, n, T, gain, e_max, early):
+    """early: the backward alone, with some spike times moved before events that
+    the spikes follow."""
+    torch, lif = env
+    cfg = W.random_small(67, B=B, C=C, N=N, n_events=n, T=T, gain=gain, ragged=False)
+    ev, WT = _padded(cfg.events, e_max), cfg.layers[0].WT
+    r = oracle.forward(ev.ev_t, ev.ev_src, ev.ev_n, WT, oracle.LifParams(s_max=256))
+    live, events = int((r.out_n > 0).sum()), int(ev.ev_n.sum())
+    assert B * e_max * N > 1 << 23 and live * events > B * events * N / 13 + (B << 21)
+    label = f"blocks B{B} C{C} N{N} n{n} live {live / (B * N):.2f}"
+    if not early and T < 1.0:
+        _fwd_bwd(env, ev, WT, 67, s_max=256, label=label)
+        return
+    # (the long stream alone too: its train's own rounding, an ulp of 1.9e-6 s at
+    # 30 s, is above the end-to-end bound)
+    rng = np.random.default_rng(67)
+    r = r.rounded()
+    t = r.out_t - np.where(rng.random(r.out_t.shape) < (0.02 if early else 0.0), rng.random(r.out_t.shape) * 1e-3, 0.0)
+    t = np.maximum.accumulate(np.maximum(t, 0.0).astype(np.float32), -1).astype(np.float64)
+    _handmade(torch, lif, label, ev.ev_t, ev.ev_src, WT, t, r.out_k, 67, ev_n=ev.ev_n, out_i=r.out_i)
+
+
+def test_adjoint_one_neuron_fires(env):
+    """A wide call in which few neurons have adjoints, and one in which none has."""
+    torch, lif = env
+    cfg = W.random_small(68, B=9, C=700, N=130, n_events=3000, T=0.4, gain=12.0, ragged=False)
+    ev, WT = _padded(cfg.events, 9000), cfg.layers[0].WT.copy()
+    d = [_dev(torch, a) for a in (ev.ev_t, ev.ev_src, ev.ev_n, WT)]
+    P, OP = lif.Params(s_max=128), oracle.LifParams(s_max=128)
+    out = lif.forward(*d, P)
+    r32 = oracle.forward(ev.ev_t, ev.ev_src, ev.ev_n, WT, OP).rounded()
+    rng = np.random.default_rng(68)
+    g = (rng.standard_normal(r32.out_t.shape) * np.isfinite(r32.out_t)).astype(np.float32)
+    for keep in ([77], [0, 64, 129], []):
+        h = g.copy()
+        h[:, [i for i in range(130) if i not in keep]] = 0.0
+        h[1:5] = 0.0                                     # samples without any
+        oW, oT = oracle.backward(ev.ev_t, ev.ev_src, ev.ev_n, WT, r32, h.astype(np.float64), OP)
+        for time_grad in (True, False):
+            gW, gT = lif.backward(*d, _dev_fwd(torch, lif, r32), _dev(torch, h), P, want_time_grad=time_grad)
+            torch.cuda.synchronize()
+            compare_grad(gW.cpu().numpy(), oW, label=f"gW {keep}")
+            if time_grad:
+                compare_grad(gT.cpu().numpy(), oT, label=f"gT {keep}")
+
+
 # (B, C, N, n, T, gain, t0): 64 events over thousands of tau_s; a stream that
 # starts 1500 s in (references far from 0 and, in float32, many spike times
 # rounded onto or before the event just before them)
@@ -83,15 +147,17 @@ def test_adjoint_sparse_streams(env, C, tau_syn, kind, T):
     _handmade(torch, lif, f"C={C} tau_s={tau_syn} {kind} T={T}", ev_t, ev_src, WT, out_t, out_k, 66, tau_syn=tau_syn)
 
 
-def _handmade(torch, lif, label, ev_t, ev_src, WT, out_t, out_k, seed, **kw):
+def _handmade(torch, lif, label, ev_t, ev_src, WT, out_t, out_k, seed, ev_n=None, out_i=None, **kw):
     """The backward alone on a spike train given by hand, out_t and out_k
     [B][N][S] with infinite times past the last spike."""
     B, E = ev_t.shape
-    ev_n = np.full(B, E, np.int32)
+    ev_n = np.full(B, E, np.int32) if ev_n is None else ev_n
     rng = np.random.default_rng(seed)
     valid = np.isfinite(out_t)
     out_n = valid.sum(-1).astype(np.int32)
-    out_i = np.where(valid, 1.5 + rng.random(out_t.shape), 0.0).astype(np.float32)
+    if out_i is None:
+        out_i = np.where(valid, 1.5 + rng.random(out_t.shape), 0.0)
+    out_i = out_i.astype(np.float32)
     g = (rng.standard_normal(out_t.shape) * valid).astype(np.float32)
     S = out_t.shape[-1]
     r = oracle.ForwardResult(out_t.astype(np.float64), out_i.astype(np.float64), out_n, None, None, None, out_k.astype(np.int32))
