@@ -274,8 +274,9 @@ int lif_layer_backward_delayed(const float* q_t, const int32_t* q_k, const int32
 /* dV/dt at each spike is floored at p->solver_reg.  Which input events a  */
 /* spike depends on is read from out_k, not from comparing the (float32)   */
 /* times, so an event that the rounding of a spike time puts at the same   */
-/* time still counts as before it.  grad_WT sums over samples with float64 */
-/* atomics, so its last bits can depend on timing.                         */
+/* time still counts as before it (a spike handed over with a time before  */
+/* an event that it follows by out_k counts with offset 0 from it).        */
+/* Bitwise reproducible (64-bit fixed-point sums).                         */
 /* --------------------------------------------------------------------- */
 size_t lif_layer_backward_workspace_size(int B, int E_max, int C_in, int N_out, const lif_params* p);
 

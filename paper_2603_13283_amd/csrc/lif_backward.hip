@@ -32,7 +32,7 @@
 //
 // dL/dW sums one term per (event, neuron) into element (source, neuron).  As
 // global atomics these adds bound the walk (184 G adds/s on this card wherever
-// the rows lie, against 3500 G adds/s into LDS), so a workgroup keeps
+// the rows lie, against 4100 G adds/s into LDS), so a workgroup keeps
 // the dL/dW block of 64 neurons and a range of at most kAdjRows channels in
 // LDS and walks, for those neurons, only the events of that range: the events
 // of each (sample, channel range) are listed in time order first
@@ -654,20 +654,21 @@ __device__ __noinline__ double2 p_at(const float* ts, const double2* rr, int s, 
 // the sum over lanes of w kappa (P^m/tm - P^s/ts), is stored; then a lane with
 // spikes between the listed event before it and event k switches its R.  The
 // spikes that a group of kGrp events passes are looked up before the group, all
-// lanes together (at most two per lane); a group where a lane passes more goes
-// event by event through p_at, as do groups with events after the time of a spike
-// that they precede (setup looks for these; a check in every group of the walk
-// cost it 4 %).
-// kLds = false: dL/dW by global atomics; kTime: dL/dt wanted (else no weight is
-// read).
-// Bound by VALU issue (82 % busy at the first shape below, 69 % at the second):
+// lanes together (at most two per lane); a group where a lane passes more takes its
+// last event by itself until they fit.  Units with spike times before events that
+// the spikes follow take the walk without a reference, with P from p_at there (setup
+// looks for these spikes; a check in every group of the common walk cost it 4 %).
+// kLds = false: the listed neurons, dL/dW by global atomics; kTime: dL/dt wanted
+// (else no weight is read).
+// Bound by VALU issue (78 % busy at the first shape below, 74 % at the second):
 // about 30 instructions per (event, 64 neurons), float64 four cycles each.  H
 // and the rows come by lane reads: as LDS broadcasts they shared the pipe
 // with the adds and bounded the walk (1.44 against 0.97 ms).  Twelve waves of up
-// to 168 registers against sixteen of 128 with spills: 7.0 -> 5.9 ms at the
-// second shape with three units per wave.  With dL/dt, 700 -> 512, B = 128,
-// 10 k events: 0.97 ms; 32768 -> 2048, B = 16, 100 k events: 5.9 ms (one wave per
-// 64 events with global atomics: 3.49 and 24.7 ms).
+// to 168 registers against sixteen of 128 with spills: 5.9 against 7.0 ms at the
+// second shape with three units per wave, when it took that long.  With dL/dt,
+// 700 -> 512, B = 128, 10 k events, 70 % firing: 0.99 ms; 32768 -> 2048, B = 16,
+// 100 k events: 5.4 ms (one wave per 64 events with global atomics: 3.69 and 22.4
+// ms).
 template <bool kLds, bool kTime>
 __device__ __forceinline__ void adjoint_units(const AdjArgs& a, unsigned long long* s_acc, int& s_next)
 {

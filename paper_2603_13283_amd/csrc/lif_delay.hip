@@ -805,6 +805,8 @@ __global__ __launch_bounds__(kWave * kDRegWaves, 5) void k_dreg_walk(
             const float code = ra.at_start ? kRecStartCode : (end ? kRecEndCode : (float)ra.em);
             const float y = ra.at_start || end ? sl : (float)ra.es;
             rb[j] = sgn == 0.0f ? make_float2(0.0f, 0.0f) : make_float2(sgn * code, y);
+            // (the gradient walk adds the float slopes of the records: their
+            // largest, exactly)
             vpm = fmaxf(vpm, sgn != 0.0f && (ra.at_start || end) ? fabsf(sl) : 0.0f);
         }
     };

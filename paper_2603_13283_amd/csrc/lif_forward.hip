@@ -1611,11 +1611,16 @@ int forward_impl(bool sequential, const float* ev_t, const int32_t* ev_src, cons
     // follows each chain with the least latency (700 -> 256, B = 32, 6 k flagged:
     // 33 us against 50 us); the wave-per-neuron pass skips by key bounds
     // (2312 -> 1024 in bursts, B = 64, 11 M flagged: 3.9 against 0.63 ms; 32768 ->
-    // 2048, B = 16, 18 M: 9.7 against 1.23 ms).  The ring pass costs about 0.4 ns
-    // a flagged sub-block beyond its chains, so the line lies where that reaches
-    // a chain's length (kRingMost).  The count is known on the device only: calls
-    // that could flag many launch both, and one of them leaves at once; calls whose
-    // dense bound is small launch the ring alone (the idle launch is 3 us).
+    // 2048, B = 16, 18 M: 9.7 against 1.23 ms).  The ring pass costs 0.3 to 0.4 ns
+    // a flagged sub-block beyond its chains (whole forwards of 700 -> 512, B = 128:
+    // 782 against 713 us at 225 k), so the line lies where that reaches a chain's
+    // length (kRingMost).  The count is known on the device only: calls that could
+    // flag many launch both, and one of them leaves at once.  That second launch costs
+    // a short call 3 to 6 us (700 -> 256, B = 32: 60 against 66 us), and the bounds
+    // gain where a large share of the sub-blocks is flagged (there, of 2.6 M: 217
+    // against 213 us at 115 k, 419 against 323 us at 350 k), so calls below
+    // kRingDense sub-blocks in all, whose layers fire at a few percent of that,
+    // launch the ring alone.
     const unsigned rgrid = (unsigned)(nn < 1024 ? nn : 1024);
     const bool both = bounds;
     const size_t rwg = (nn + kResolveWaves - 1) / kResolveWaves;
@@ -1691,10 +1696,10 @@ namespace lif {
 // kRec: records and local sums for the gradient; kSlope: with end-point slopes
 // (dL/dt wanted).  Nearly every interval of a wave is without a spike on all of
 // its lanes and takes the straight path, and the lookup of the lane's next spike
-// stays in a register.  Bound by VALU issue (47 % busy) and the records' stores:
+// stays in a register.  Bound by VALU issue (73 % busy) and the records' stores:
 // 700 -> 512, B = 128, 10 k events, 5.2 GB of records: 3.45 -> 1.89 ms (the
 // quotient, logarithm and spike lookups of every interval: 141 VALU, 92 scalar
-// instructions and 19 branches per event before, 71, 28 and 7 now).
+// instructions and 19 branches per event before, 73, 28 and 7 now).
 template <bool kRec, bool kSlope>
 __global__ __launch_bounds__(kWave * kWalkWaves) void k_reg_walk(
     const float* __restrict__ ev_t, const int32_t* __restrict__ ev_src, const int32_t* __restrict__ ev_n, int E_max,
@@ -2339,7 +2344,7 @@ __global__ __launch_bounds__(kWave * kWalkWaves) void k_regg_walk(
 // them to its row by DPP.  Without the LDS the walk waits for its global 64-bit
 // atomics, 184 G/s on the whole chip however they are spread (about 20 times
 // that in LDS): 700 -> 512, B = 128, 10 k events, 4.05 -> 2.33 ms, now bound by
-// VALU issue (63 % busy, two waves per SIMD; three spill: 5.87 ms).
+// VALU issue (64 % busy, two waves per SIMD; three spill: 5.87 ms).
 constexpr int kTileN = 16, kTileRow = kTileN * (int)sizeof(long long), kTileWaves = 8;
 
 template <bool kTime>

@@ -54,7 +54,7 @@ struct RingLds {
     float si[kWave];                             // I at the spike,
     int32_t sk[kWave];                           // events consumed before the spike
     double open_len;                             // length of the open interval (t_end - last event)
-    int ntot;                                    // candidates of the chunk (chain wave -> both)
+    int ntot;                                    // candidates of the chunk (chain wave -> all)
     int ready[kRing];                            // 1 + window index staged in each buffer
     double kmax[kRing];                          // largest key of each buffer's window (NaN keys left out)
     int consumed;                                // windows the chain has finished
@@ -319,10 +319,10 @@ __device__ __forceinline__ void chain_window(RingLds& sh, const WinBuf& w, const
     }
 }
 
-// Both waves of the workgroup call this for the same neuron and pass the
+// The four waves of the workgroup call this for the same neuron and pass the
 // same barriers (one per chunk; candidate counts and the stop flag pass
-// through LDS).  Returns the spike count on the chain wave, 0 on the
-// staging wave.
+// through LDS).  Returns the spike count on the chain wave, 0 on the three
+// staging waves.
 template <int PI>
 __device__ int ring_neuron(RingLds& sh, int b, int n, const float* __restrict__ ev_t,
                               const int32_t* __restrict__ ev_src, const int32_t* __restrict__ ev_n, int E_max,
@@ -478,7 +478,7 @@ __device__ int ring_neuron(RingLds& sh, int b, int n, const float* __restrict__ 
             }
         }
         wbase += nwin;
-        __syncthreads();                      // both waves are done with the chunk's list
+        __syncthreads();                      // all waves are done with the chunk's list
         stop = __builtin_amdgcn_readfirstlane(lds_load(&sh.stop)) != 0;
     }
     if (!chain) return 0;
@@ -508,7 +508,7 @@ __global__ __launch_bounds__(kWave * kRingWaves) void k_resolve_ring(
     // status words once at its end
     unsigned long long spikes = 0;
     uint32_t capped = 0;
-    // Both waves walk the list the same way.  Running sum of the list
+    // All waves walk the list the same way.  Running sum of the list
     // lengths over groups of 64 samples (one load per lane, a wave prefix
     // sum): entry w of the concatenated lists belongs to the first sample
     // whose running sum exceeds w.

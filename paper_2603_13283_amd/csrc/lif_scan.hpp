@@ -84,7 +84,8 @@ __device__ __forceinline__ void scan_maps_down(double& a, double& b, int lane)
     }
 }
 
-// e^{-x/ts} from e^{-x/tm} when tau_m / tau_s = kP + 1.
+// e^{-x/ts} from e^{-x/tm} when tau_m / tau_s = kP + 1 (within kP + 3 ulp of
+// float64: kP + 1 times the error of the given factor and a rounding per product).
 template <int kP>
 __device__ __forceinline__ double syn_power(double a)
 {

@@ -54,3 +54,12 @@ def test_few_flagged_take_the_ring(env):
     ev, WT = _layer(74, 4300, 0.6)
     s = check(env, ev, WT, "few flagged", both=False)
     assert s["par"]["status"][3] <= MOST
+
+
+def test_many_flagged_of_few_stay_on_the_ring(env):
+    """Below 2^22 sub-blocks in all the ring takes every call, also one that flags
+    more than the line between the passes."""
+    ev, WT = _layer(75, 4300, 9.0, B=20)
+    assert 20 * 256 * 4 * -(-ev.E_max // 64) <= 1 << 22
+    s = check(env, ev, WT, "dense ring", both=False, s_max=256)
+    assert s["par"]["status"][3] > MOST
