@@ -93,6 +93,34 @@ def test_adjoint_one_neuron_fires(env):
                 compare_grad(gT.cpu().numpy(), oT, label=f"gT {keep}")
 
 
+def test_adjoint_ways_under_capture(env):
+    """One captured call replayed with upstream gradients on all, few, none and
+    all neurons again: the way is the device's choice on every replay."""
+    torch, lif = env
+    cfg = W.random_small(69, B=9, C=700, N=130, n_events=3000, T=0.4, gain=12.0, ragged=False)
+    ev = _padded(cfg.events, 9000)
+    d = [_dev(torch, a) for a in (ev.ev_t, ev.ev_src, ev.ev_n, cfg.layers[0].WT)]
+    P = lif.Params(s_max=128)
+    out = lif.forward(*d, P)
+    full = torch.randn(out.out_t.shape, generator=torch.Generator(device="cuda:0").manual_seed(2), device="cuda:0")
+    few = torch.zeros_like(full)
+    few[:, 70:73] = full[:, 70:73]
+    g = full.clone()
+    ws = torch.empty(lif.lif_layer_backward_workspace_size(9, 9000, 700, 130, P.c()), dtype=torch.uint8, device="cuda:0")
+    ws2 = torch.empty_like(ws)
+    lif.backward(*d, out, g, P, ws=ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        gW, gT = lif.backward(*d, out, g, P, ws=ws)
+    for h in (full, few, torch.zeros_like(full), full):
+        g.copy_(h)
+        graph.replay()
+        want = lif.backward(*d, out, h, P, ws=ws2)
+        torch.cuda.synchronize()
+        assert torch.equal(gW, want[0]) and torch.equal(gT, want[1])
+
+
 # (B, C, N, n, T, gain, t0): 64 events over thousands of tau_s; a stream that
 # starts 1500 s in (references far from 0 and, in float32, many spike times
 # rounded onto or before the event just before them)
