@@ -1865,53 +1865,18 @@ __global__ __launch_bounds__(256) void k_reg_reduce(const double4* __restrict__ 
     if (counts) counts[i] = make_double2(nsil, nspk);
 }
 
-// The two loss terms.  Per neuron (a workgroup takes kMeanN of them, its rows
-// of threads every kMeanB-th sample) the batch means and the gates of the mean
+// The two loss terms.  Per neuron (a workgroup takes tiles of kMeanN of them, its
+// rows of threads every kMeanB-th sample) the batch means and the gates of the mean
 // spike count against the target; a neuron's two terms replace its first
-// sample's ub and ob, which only its own threads have read.  k_reg_loss then
-// takes the means over the neurons.  Every sum is in a fixed order.  One
-// workgroup walked the whole batch before: 112 -> 8 us at B = 128, N = 512.
-constexpr int kRegThreads = 256, kMeanN = 16, kMeanB = kRegThreads / kMeanN;
+// sample's ub and ob, which only its own threads have read.  The means over the
+// neurons follow in k_reg_loss, or (one workgroup, loss given) at once.  Every sum is
+// in a fixed order.  One workgroup walked the whole batch before: 112 -> 8 us at
+// B = 128, N = 512; with up to kMeanOne tiles and kMeanB samples one still does, the
+// second launch being the larger part there (delayed regularisers of 64 -> 64, B = 2:
+// 56.9 us with two launches, 54.1 us with one; of 64 -> 60, B = 40: 59 against 62 us).
+constexpr int kRegThreads = 256, kMeanN = 16, kMeanB = kRegThreads / kMeanN, kMeanOne = 4;
 
-__global__ __launch_bounds__(kRegThreads) void k_reg_mean(double* __restrict__ ub, double* __restrict__ ob,
-                                                          const int32_t* __restrict__ out_n, int B, int N, int s_max,
-                                                          double c_target, double2* __restrict__ gates)
-{
-    __shared__ double4 s_p[kMeanB][kMeanN];
-    const int nl = (int)threadIdx.x % kMeanN, bl = (int)threadIdx.x / kMeanN;
-    const int n = (int)blockIdx.x * kMeanN + nl;
-    double4 p = make_double4(0.0, 0.0, 0.0, 0.0);
-    if (n < N) {
-#pragma unroll 4
-        for (int b = bl; b < B; b += kMeanB) {
-            const size_t i = (size_t)b * N + n;
-            const double cnt = (double)min(out_n[i], s_max);
-            p.x += cnt;
-            p.y += ub[i];
-            p.z += ob[i];
-            p.w += fmax(cnt / c_target - 1.0, 0.0) * ob[i];
-        }
-    }
-    s_p[bl][nl] = p;
-    __syncthreads();
-    if (bl == 0 && n < N) {
-        for (int q = 1; q < kMeanB; ++q) {
-            const double4 o = s_p[q][nl];
-            p.x += o.x;
-            p.y += o.y;
-            p.z += o.z;
-            p.w += o.w;
-        }
-        const double cb = p.x / (double)B;
-        const double gu = fmax(1.0 - cb / c_target, 0.0), go = fmax(cb / c_target - 1.0, 0.0);
-        ub[n] = gu * (p.y / (double)B) + go * (p.z / (double)B);
-        ob[n] = p.w;
-        if (gates) gates[n] = make_double2(gu, go);
-    }
-}
-
-__global__ __launch_bounds__(kRegThreads) void k_reg_loss(const double* __restrict__ ub, const double* __restrict__ ob,
-                                                          int N, float* __restrict__ loss)
+__device__ __forceinline__ void reg_loss_means(const double* ub, const double* ob, int N, float* __restrict__ loss)
 {
     __shared__ double s_reg[kRegThreads], s_over[kRegThreads];
     double lr = 0.0, lo = 0.0;
@@ -1935,12 +1900,61 @@ __global__ __launch_bounds__(kRegThreads) void k_reg_loss(const double* __restri
     }
 }
 
+__global__ __launch_bounds__(kRegThreads) void k_reg_mean(double* ub, double* ob, const int32_t* __restrict__ out_n,
+                                                          int B, int N, int s_max, double c_target,
+                                                          double2* __restrict__ gates, float* __restrict__ loss)
+{
+    __shared__ double4 s_p[kMeanB][kMeanN];
+    const int nl = (int)threadIdx.x % kMeanN, bl = (int)threadIdx.x / kMeanN;
+    for (int n0 = (int)blockIdx.x * kMeanN; n0 < N; n0 += (int)gridDim.x * kMeanN) {
+        const int n = n0 + nl;
+        double4 p = make_double4(0.0, 0.0, 0.0, 0.0);
+        if (n < N) {
+#pragma unroll 4
+            for (int b = bl; b < B; b += kMeanB) {
+                const size_t i = (size_t)b * N + n;
+                const double cnt = (double)min(out_n[i], s_max);
+                p.x += cnt;
+                p.y += ub[i];
+                p.z += ob[i];
+                p.w += fmax(cnt / c_target - 1.0, 0.0) * ob[i];
+            }
+        }
+        s_p[bl][nl] = p;
+        __syncthreads();
+        if (bl == 0 && n < N) {
+            for (int q = 1; q < kMeanB; ++q) {
+                const double4 o = s_p[q][nl];
+                p.x += o.x;
+                p.y += o.y;
+                p.z += o.z;
+                p.w += o.w;
+            }
+            const double cb = p.x / (double)B;
+            const double gu = fmax(1.0 - cb / c_target, 0.0), go = fmax(cb / c_target - 1.0, 0.0);
+            ub[n] = gu * (p.y / (double)B) + go * (p.z / (double)B);
+            ob[n] = p.w;
+            if (gates) gates[n] = make_double2(gu, go);
+        }
+        __syncthreads();
+    }
+    if (loss) reg_loss_means(ub, ob, N, loss);
+}
+
+__global__ __launch_bounds__(kRegThreads) void k_reg_loss(const double* __restrict__ ub, const double* __restrict__ ob,
+                                                          int N, float* __restrict__ loss)
+{
+    reg_loss_means(ub, ob, N, loss);
+}
+
 void launch_reg_loss(double* ub, double* ob, const int32_t* out_n, int B, int N, int s_max, double c_target,
                      float* loss, double2* gates, hipStream_t stream)
 {
-    TIMED_LAUNCH("reg_mean", k_reg_mean, dim3((unsigned)((N + kMeanN - 1) / kMeanN)), dim3(kRegThreads), 0, stream, ub,
-                 ob, out_n, B, N, s_max, c_target, gates);
-    if (loss) TIMED_LAUNCH("reg_loss", k_reg_loss, dim3(1), dim3(kRegThreads), 0, stream, ub, ob, N, loss);
+    const int tiles = (N + kMeanN - 1) / kMeanN;
+    const bool one = loss && tiles <= kMeanOne && B <= kMeanB;
+    TIMED_LAUNCH("reg_mean", k_reg_mean, dim3(one ? 1u : (unsigned)tiles), dim3(kRegThreads), 0, stream, ub, ob, out_n,
+                 B, N, s_max, c_target, gates, one ? loss : nullptr);
+    if (loss && !one) TIMED_LAUNCH("reg_loss", k_reg_loss, dim3(1), dim3(kRegThreads), 0, stream, ub, ob, N, loss);
 }
 
 struct RegLayout {
